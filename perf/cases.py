@@ -72,8 +72,9 @@ def listed():
         # the benchmark's default workload
         _case("step_clumpy_4194304", "step", "clumpy", 4194304),
         # concentrated cluster with an untruncated halo: FP32 forces and the
-        # reverse pass
-        _case("grad_plummer_1048576_fp32", "grad", "plummer", 1048576, fp32=True),
+        # reverse pass (the list slots of twice as many particles would not
+        # leave room for other states on the card)
+        _case("grad_plummer_524288_fp32", "grad", "plummer", 524288, fp32=True),
         # the largest binary of the configurations, FP32 form
         _case("step_binary_16777216_fp32", "step", "binary", 16777216, fp32=True),
     ]
@@ -82,7 +83,9 @@ def listed():
 # largest n a drawn case takes, by operation and distribution: the halo of the
 # untruncated Plummer sphere makes its lists long, the reverse pass and the
 # mutual walk cost a few force evaluations each, and the centre-of-mass tree
-# keeps buffers for 2n - 1 cells
+# keeps buffers for 2n - 1 cells.  A large binary has two equal stars: with an
+# odd particle one leaf spans both, takes every leaf as near, and the list
+# slots of every leaf grow to that length.
 _MOST = {"step": 1 << 23, "kdk": 1 << 21, "grad": 1 << 20, "adjoint": 1 << 17, "census": 1 << 20}
 
 
@@ -93,10 +96,12 @@ def draw(rng):
     com = rng.random() < 0.15
     most = _MOST[op]
     if dist == "plummer":
-        most = min(most, 1 << 19)
+        most = min(most, 1 << 18)
     if mutual or com:
         most = min(most, 1 << 20)
     n = int(math.exp(rng.uniform(math.log(700), math.log(most))))
+    if dist == "binary" and n > 1 << 17:
+        n -= n % 2
     return _case(None, op, dist, n, fp32=rng.random() < 0.4, mutual=mutual,
                  dehnen=rng.random() < 0.15, com=com,
                  theta=rng.choice([0.3, 0.5, 0.5, 0.5, 0.7]) if n <= 1 << 17 else 0.5,
