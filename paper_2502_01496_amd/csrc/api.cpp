@@ -417,6 +417,10 @@ static fmm_status create_tree(int64_t n, const fmm_params &p, Tree **out)
     A(dalloc(*t, &t->pm, n + 1));  // + the null source record
     A(dalloc(*t, &t->hs, n));
     A(dalloc(*t, &t->ph, n + 1));
+    A(dalloc(*t, &t->pxy, n));
+    A(dalloc(*t, &t->pzm, n));
+    A(dalloc(*t, &t->phi, n));
+    A(dalloc(*t, &t->lbox, LBOX * (size_t)t->topo.leaf_cap));
     A(dalloc(*t, &t->pf, n));
     A(dalloc(*t, &t->pfh, n));
     A(dalloc(*t, &t->recA, NREC * nn));

@@ -38,6 +38,7 @@ constexpr int NREC = 8;   // doubles per node record (geometry / quadrupole)
 // high 32, -1 for a leaf) and slot 7 the leaf index (-1 for an internal
 // node), so that a walk reads one 64-byte record per visited cell.
 constexpr int REC_KIDS = 6, REC_LEAF = 7;
+constexpr int LBOX = 8;   // doubles per leaf box
 constexpr int NLOC = 20;  // doubles per local expansion (19 used)
 constexpr int LLEAF = 24;  // doubles per leaf record of the reverse pass's M2L^T source side
 
@@ -255,6 +256,11 @@ struct Tree {
     double4 *pm = nullptr;        // x, y, z, m
     double *hs = nullptr;         // h
     double4 *ph = nullptr;        // 1/h, 1/h^3, 4 h^2, h
+    // the same for the FP64 near field of the leaf <- cell lists, which reads a
+    // particle per lane: 64 consecutive records of 16 or 8 bytes are one
+    // contiguous access
+    double2 *pxy = nullptr, *pzm = nullptr;  // x, y; z, m
+    double *phi = nullptr;        // 1/h
     float4 *pf = nullptr;         // FP32 form: offset from the leaf centre of mass, m
     float4 *pfh = nullptr;        // FP32 form: 1/h, 1/h^3, 4 h^2, 0
 
@@ -262,6 +268,8 @@ struct Tree {
     double *recA = nullptr;       // per node: cx, cy, cz, M, s, hmax, 0, 0
     double *recQ = nullptr;       // per node: Qxx, Qxy, Qxz, Qyy, Qyz, Qzz, 0, 0
     float *recF = nullptr;        // per node FP32 mirror: M, Q[6], 0
+    double *lbox = nullptr;       // LBOX per leaf: bounding box of its particles (centre,
+                                  // half widths), their largest 4 h^2, 0
     uint64_t *s2bits = nullptr;
     uint64_t *s2part = nullptr;   // depth x ceil(n/64) per-wavefront maxima
     int32_t *big_nodes = nullptr;

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
     }
 }
 
-// ---------------------------------------------------------------- P2P + L2P, FP64
+// ---------------------------------------------------------------- P2P + L2P, FP64 (mutual walk)
 __device__ __forceinline__ double m4g_f64(double q, double hinv3, double u3)
 {
     // both pieces are evaluated and selected (no divergent branches)
@@ -412,8 +412,10 @@ __device__ __forceinline__ T reduce_scatter24(const T *v, int lane)
     return e;
 }
 
-// Near field.  One wavefront per sink leaf; P2P_NS sink particles per pass
-// are wave-uniform, and a step takes 8 source blocks (a near leaf gives
+// Near field of the mutual walk's lists.  One wavefront per sink leaf; P2P_NS
+// sink particles per pass are wave-uniform (with SKIP, for trees whose leaves
+// are not all full, absent ones are branched over: without absent ones the
+// branches cost 2 to 4 %), and a step takes 8 source blocks (a near leaf gives
 // ceil(leaf_size / 8) blocks of at most 8 particles): lane = 8 g + t holds
 // particle t of the g-th block, loaded once per pass.  The block ranges of
 // a chunk of the near list are staged in LDS (empty blocks dropped), and the
@@ -501,6 +503,7 @@ __device__ __forceinline__ void p2p_drain_f64(const double4 *__restrict__ pm,
     az -= fm * dz;
 }
 
+template <bool SKIP>
 __global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_src_f64(
     const double4 *__restrict__ pm, const double4 *__restrict__ ph,
     const int32_t *__restrict__ first, const int32_t *__restrict__ count,
@@ -585,6 +588,8 @@ __global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                 const double hmax4 = hj4 > H4 ? hj4 : H4;
 #pragma unroll
                 for (int q = 0; q < NS; ++q) {
+                    if (SKIP && q > 0 && sb + q >= c)
+                        continue;
                     const double dx = sx[q] - xj.x, dy = sy[q] - xj.y, dz = sz[q] - xj.z;
                     const double r2 = dx * dx + dy * dy + dz * dz;
                     // (every lane is active here: the softened mask is the
@@ -699,6 +704,7 @@ __device__ __forceinline__ int skip_gap(int k, int front, int gap)
     return k < front ? k : k + gap;
 }
 
+template <bool SKIP>
 __global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_src_f32(
     const float4 *__restrict__ pf, const float4 *__restrict__ pfh,
     const int32_t *__restrict__ first,
@@ -807,6 +813,8 @@ __global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                 }
 #pragma unroll
                 for (int q = 0; q < NS; ++q) {
+                    if (SKIP && q > 0 && sb + q >= c)
+                        continue;
                     const float dx = dc.x + (sx[q] - yj.x), dy = dc.y + (sy[q] - yj.y),
                                 dz = dc.z + (sz[q] - yj.z);
                     const float r2 = dx * dx + dy * dy + dz * dz;
@@ -856,6 +864,327 @@ __global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             aout[o] = G * (far_c + tot);
         }
         __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// ---------------------------------------------------------------- near field, leaf <- cell lists
+// The same with y cubed before the correction: (1 - e)^(-3/2) = 1 + 3/2 e +
+// 15/8 e^2 + O(e^3) (y is good to about 2^-23, so the remainder is below
+// 2^-66).  k15 is 1.5, in a register.
+__device__ __forceinline__ double m_over_r3_k(double r2, double m, double k15)
+{
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double y2 = y * y;
+    const double e = fma(-r2, y2, 1.0);
+    const double my3 = (m * y) * y2;
+    return fma(my3 * e, fma(e, 1.875, k15), my3);
+}
+
+// Near field.  One wavefront per sink leaf.  The leaf's sinks are laid over
+// the lanes two by two, each pair of sinks over the g = floor(64 / pairs)
+// lanes of a group, and a step takes g source particles from LDS, one per lane
+// of the group (for 8 sinks: 4 groups, 16 sources, 128 pairs a step).  So every
+// lane works whatever the leaf's count, the sums of a lane are six registers
+// (24 with a lane per source and all sinks in every lane), and two pairs per
+// lane are independent work.
+//
+// Sources reach LDS 64 at a time: 8 blocks of the near list (a near leaf gives
+// ceil(leaf_size / 8) blocks of at most 8 particles), a lane per particle.
+// Each is tested against the bounding box of the leaf: one whose distance from
+// the box is beyond the softening supports of eqs. (14)-(15) of itself and of
+// every sink is Newtonian for all of them and goes to one ring buffer, the
+// others go to a second one.  A step over the first ring is m / r^3 without a
+// test; a step over the second one takes the M4 kernel, which is exact on both
+// sides of the support, if any of its pairs is inside one.  A ring is emptied
+// g sources at a time, the rest stays for the next 64, so missing particles
+// and short blocks cost no lanes.
+//
+// VALU issue bounds it (89 % of its cycles, 44 instructions per 64 pairs: 12 to
+// bring sources to LDS and for the leaf's start and end, 13 for the Newtonian
+// steps, 17 for the second ring, which holds a third of the pairs with
+// 58-neighbour smoothing lengths).  Measured against k_p2p_src_f64, whose lanes
+// each take a source and all (eight, wave-uniform) sinks: 560 -> 509 us (binary,
+// 2^19), 4.56 -> 4.16 ms (clumpy cube, 2^22), 497 -> 304 us where leaves hold 4
+// to 10 particles (centre-of-mass tree, 200003).
+//
+// It takes the lists of the leaf <- cell walk.  Those of the mutual walk stay
+// with k_p2p_src_f64: their forces add up to zero but for rounding, and the sum
+// that is left (the momentum statistics) belongs to one order of additions.
+//
+// The order of all additions depends on the lists only, so results are bitwise
+// reproducible.
+// One wavefront per workgroup: the leaves' near lists differ in length, and a
+// workgroup's slots are only freed when its last wavefront ends.
+constexpr int P2P_SINKS = 16;  // sinks per pass, at most
+constexpr int P2P_RING = 128;  // sources a ring holds: less than g <= 64 left over, plus 64
+
+// Lanes per pair of sinks for 1..8 pairs: floor(64 / pairs).
+__device__ __forceinline__ int lanes_per_pair(int pairs)
+{
+    return (int)((0x08090a0c10152040ull >> (8 * (pairs - 1))) & 0xffull);
+}
+
+// at + the number of lanes below this one that are set in m.
+__device__ __forceinline__ int below(uint64_t m, int at)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
+}
+
+// Rotation by N lanes within each row of 16 lanes.
+template <int N>
+__device__ __forceinline__ double row_ror(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 | N, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 | N, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double v)
+{
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    v += row_ror<1>(v);
+    return v;
+}
+
+// The two rings of sources in LDS (x, y, z, m), and 1/h of the second one.
+// An index is ring * P2P_RING + position.
+struct NearRings {
+    double2 xy[2 * P2P_RING], zm[2 * P2P_RING];
+    double hi[P2P_RING];
+};
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_rings(
+    const double2 *__restrict__ pxy, const double2 *__restrict__ pzm,
+    const double *__restrict__ phi, const double *__restrict__ lbox, const int32_t *__restrict__ first,
+    const int32_t *__restrict__ count, const int32_t *__restrict__ leaf_node, int nunits,
+    const int32_t *__restrict__ near_cnt, const int32_t *__restrict__ near_src, int cap_near,
+    int nsub, const double *__restrict__ Lloc, const double *__restrict__ recA,
+    const int32_t *__restrict__ perm, double G, double *aout, const int2 *__restrict__ pieces,
+    int per, double *part, int part_stride)
+{
+    constexpr int RM = P2P_RING - 1;
+    __shared__ NearRings R;
+    const int unit = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
+    if (unit >= nunits)
+        return;
+    const int lane = lane_id();
+    const int grp = lane >> 3, slot = lane & 7;
+    const int2 pc = pieces ? pieces[unit] : make_int2(unit, 0);
+    const int leaf = pc.x;
+    const int v = leaf_node[leaf];
+    const int64_t f = first[v];
+    const int c = count[v];
+    const int nbf = max(0, min(near_cnt[leaf], cap_near)) * nsub;
+    const int b_lo = pieces ? pc.y * per : 0;
+    const int b_hi = pieces ? min(nbf, b_lo + per) : nbf;
+    const int32_t *nl = near_src + (int64_t)leaf * cap_near;
+    const double *rv = recA + (int64_t)NREC * v;
+    const double *Lv = Lloc + (int64_t)NLOC * v;
+    const double *lb = lbox + (int64_t)LBOX * leaf;
+    const double bx = lb[0], by = lb[1], bz = lb[2], wx = lb[3], wy = lb[4], wz = lb[5],
+                 H4 = lb[6];
+    const int npass = (c + P2P_SINKS - 1) / P2P_SINKS;
+    const int nsp = (c + npass - 1) / npass;  // sinks per pass
+    for (int sb = 0; sb < c; sb += nsp) {
+        const int cs = min(nsp, c - sb);
+        const int np = (cs + 1) >> 1;      // pairs of sinks
+        const int g = lanes_per_pair(np);  // lanes per pair
+        const int pr = np == 4 ? lane >> 4 : min(lane / g, np - 1);
+        const int k = lane - pr * g;       // k >= g: an idle lane
+        double sx[2], sy[2], sz[2], shi[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t is = f + sb + min(2 * pr + q, cs - 1);
+            const double2 xy = pxy[is], zm = pzm[is];
+            sx[q] = xy.x;
+            sy[q] = xy.y;
+            sz[q] = zm.x;
+            shi[q] = phi[is];
+        }
+        double k15 = 1.5;
+        asm("" : "+v"(k15));  // kept in a register, not set up for each pair
+        // pieces of `per` source blocks: each ends with its rings emptied and
+        // its sums reduced, and the piece sums add up in piece order (the
+        // same sums, bit for bit, whether a wavefront takes all of a leaf's
+        // pieces or one piece each)
+        double tot = 0.0;
+        for (int p0 = b_lo; p0 < b_hi; p0 += per) {
+            const int nb = min(b_hi, p0 + per);
+            double a[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+                a[q] = 0.0;
+            // fill and read positions of the two rings
+            int tn = 0, hn = 0, tc = 0, hc = 0;
+            // a step over the first ring; lanes from lim on take no source
+            auto newton = [&](int lim) {
+                const double2 xy = R.xy[(hn + k) & RM], zm = R.zm[(hn + k) & RM];
+                double4 s = make_double4(xy.x, xy.y, zm.x, zm.y);
+                const bool none = lim < 64 && k >= lim;
+                if (none)
+                    s = make_double4(sx[0], sy[0], sz[0], 0.0);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const double dx = sx[q] - s.x, dy = sy[q] - s.y, dz = sz[q] - s.z;
+                    double fm = m_over_r3_k(dx * dx + dy * dy + dz * dz, s.w, k15);
+                    if (none)
+                        fm = 0.0;
+                    a[3 * q] -= fm * dx;
+                    a[3 * q + 1] -= fm * dy;
+                    a[3 * q + 2] -= fm * dz;
+                }
+            };
+            auto soft = [&](int lim) {
+                const int i = (hc + k) & RM;
+                const double2 xy = R.xy[P2P_RING + i], zm = R.zm[P2P_RING + i];
+                double4 s = make_double4(xy.x, xy.y, zm.x, zm.y);
+                double hj = R.hi[i];
+                if (lim < 64 && k >= lim) {  // u = 0 or finite: adds zero
+                    s = make_double4(sx[0], sy[0], sz[0], 0.0);
+                    hj = 0.0;
+                }
+                double dx[2], dy[2], dz[2], u[2], qi[2], qj[2];
+                bool in = false;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    dx[q] = sx[q] - s.x;
+                    dy[q] = sy[q] - s.y;
+                    dz[q] = sz[q] - s.z;
+                    const double r2 = dx[q] * dx[q] + dy[q] * dy[q] + dz[q] * dz[q];
+                    u[q] = r2 > 0.0 ? rsqrt_pos(r2) : 0.0;
+                    const double r = r2 * u[q];
+                    qi[q] = r * shi[q];
+                    qj[q] = r * hj;
+                    in = in || fmin(qi[q], qj[q]) < 2.0;
+                }
+                const bool any = __ballot(in && k < g) != 0ull;
+                const double mh = 0.5 * s.w, hj3 = hj * hj * hj;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const double u3 = u[q] * u[q] * u[q];
+                    double fm = s.w * u3;
+                    if (any)
+                        fm = mh * (m4g_f64(qi[q], shi[q] * shi[q] * shi[q], u3) +
+                                   m4g_f64(qj[q], hj3, u3));
+                    a[3 * q] -= fm * dx[q];
+                    a[3 * q + 1] -= fm * dy[q];
+                    a[3 * q + 2] -= fm * dz[q];
+                }
+            };
+            for (int c0 = p0; c0 < nb; c0 += 64) {
+                // the particle ranges of 64 blocks, a lane each, the empty
+                // ones moved behind the others
+                int rx = 0, ry = 0;
+                if (c0 + lane < nb) {
+                    const int e = (c0 + lane) / nsub, u = (c0 + lane) - e * nsub;
+                    const int bn = nl[e];
+                    rx = first[bn] + 8 * u;
+                    ry = max(0, min(8, count[bn] - 8 * u));
+                }
+                const uint64_t mk = __ballot(ry > 0);
+                const int ne = __popcll(mk);
+                if (nsub > 1) {
+                    const int to = 4 * (ry > 0 ? below(mk, 0) : below(~mk, ne));
+                    rx = __builtin_amdgcn_ds_permute(to, rx);
+                    ry = __builtin_amdgcn_ds_permute(to, ry);
+                }
+                struct Src {
+                    int j;
+                    double2 xy, zm;
+                    double hi;
+                };
+                auto load = [&](int kb) {  // the lane's source of 8 blocks from kb on
+                    const int n = __builtin_amdgcn_ds_bpermute(4 * (kb + grp), ry);
+                    const int s0 = __builtin_amdgcn_ds_bpermute(4 * (kb + grp), rx);
+                    Src r;
+                    r.j = slot < n ? s0 + slot : -1;
+                    const int64_t i = max(r.j, 0);
+                    r.xy = pxy[i];
+                    r.zm = pzm[i];
+                    r.hi = phi[i];
+                    return r;
+                };
+                for (int kb = 0; kb < ne; kb += 8) {
+                    const Src r = load(kb);
+                    const double x = r.xy.x, y = r.xy.y, z = r.zm.x;
+                    const double ex = fmax(fabs(x - bx) - wx, 0.0),
+                                 ey = fmax(fabs(y - by) - wy, 0.0),
+                                 ez = fmax(fabs(z - bz) - wz, 0.0);
+                    const double d2 = ex * ex + ey * ey + ez * ez;
+                    const bool act = r.j >= 0, far = d2 >= H4 && (d2 * r.hi) * r.hi >= 4.0;
+                    const uint64_t ma = __ballot(act), mf = __ballot(far);
+                    const uint64_t mn = ma & mf, mc = ma & ~mf;
+                    const int i = far ? below(mn, tn) & RM : (below(mc, tc) & RM) | P2P_RING;
+                    if (act) {
+                        R.xy[i] = r.xy;
+                        R.zm[i] = r.zm;
+                        if (!far)
+                            R.hi[i & RM] = r.hi;
+                    }
+                    tn += __popcll(mn);
+                    tc += __popcll(mc);
+                    __builtin_amdgcn_wave_barrier();
+                    for (; tn - hn >= g; hn += g)
+                        newton(64);
+                    for (; tc - hc >= g; hc += g)
+                        soft(64);
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+            if (tn > hn)
+                newton(tn - hn);
+            if (tc > hc)
+                soft(tc - hc);
+            __builtin_amdgcn_wave_barrier();
+            // sums over the lanes of a group; lane k < 6 keeps value k
+            if (g == 16) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+                    a[q] = row_sum(a[q]);
+            } else {
+                for (int off = 32; off >= 1; off >>= 1) {
+                    if (off >= g)
+                        continue;
+                    const bool take = k < off && k + off < g;
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        const double o = __shfl_down(a[q], off);
+                        a[q] += take ? o : 0.0;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+                    a[q] = __shfl(a[q], pr * g);
+            }
+            double val = a[0];
+#pragma unroll
+            for (int q = 1; q < 6; ++q)
+                val = k == q ? a[q] : val;
+            tot += val;
+        }
+        const int q = k >= 3 ? 1 : 0, comp = k - 3 * q;
+        if (k < 6 && 2 * pr + q < cs) {
+            const int si = sb + 2 * pr + q;
+            if (pieces && nbf > per) {
+                part[(int64_t)unit * part_stride + 3 * si + comp] = tot;
+            } else {
+                // component comp of eq. (8) at the sink
+                double y0 = q ? sx[1] : sx[0], y1 = q ? sy[1] : sy[0], y2 = q ? sz[1] : sz[0];
+                y0 -= rv[0];
+                y1 -= rv[1];
+                y2 -= rv[2];
+                double Lr[19];
+#pragma unroll
+                for (int i = 0; i < 19; ++i)
+                    Lr[i] = Lv[i];
+                double fx, fy, fz;
+                l2p<double>(Lr, y0, y1, y2, fx, fy, fz);
+                const double far_c = comp == 0 ? fx : (comp == 1 ? fy : fz);
+                aout[3 * (int64_t)perm[f + si] + comp] = G * (far_c + tot);
+            }
+        }
     }
 }
 
@@ -1143,8 +1472,18 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s)
     const int per = (int)t.near_piece_blocks;
     const int stride = 3 * T.leaf_size;
     const int extra = pc ? nu - nl : 0;
+    // every leaf full (no absent sinks to branch over)?
+    const bool full = T.leaf_size == P2P_NS && T.n == (int64_t)P2P_NS * nl;
     if (t.p.precision == FMM_FP64) {
-        k_p2p_src_f64<<<(nu + P2P_WAVES - 1) / P2P_WAVES, P2P_WG, 0, s>>>(
+        // (lists_policy is set after the evaluation of a tree's new lists)
+        if (t.p.walk == FMM_WALK_PHANTOM)
+            k_p2p_rings<<<nu, 64, 0, s>>>(t.pxy, t.pzm, t.phi, t.lbox, t.first, t.count,
+                                          t.leaf_node, nu, t.near_cnt, t.near_src, (int)t.cap_near,
+                                          nsub, t.L, t.recA, t.perm, t.p.G, (double *)a, pl, per,
+                                          (double *)t.pnear.part, stride);
+        else
+            (full ? k_p2p_src_f64<false> : k_p2p_src_f64<true>)<<<
+                (nu + P2P_WAVES - 1) / P2P_WAVES, P2P_WG, 0, s>>>(
             t.pm, t.ph, t.first, t.count, t.leaf_node, nu, t.near_cnt, t.near_src,
             (int)t.cap_near, nsub, t.L, t.recA, t.perm, t.p.G, t.p.r_kern, T.n, (double *)a, pl,
             per, (double *)t.pnear.part, stride);
@@ -1154,7 +1493,8 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s)
                 (const double *)t.pnear.part, stride, t.L, t.recA, t.pm, t.pf, t.perm, t.p.G,
                 (double *)a);
     } else {
-        k_p2p_src_f32<<<(nu + P2P_WAVES - 1) / P2P_WAVES, P2P_WG, 0, s>>>(
+        (full ? k_p2p_src_f32<false> : k_p2p_src_f32<true>)<<<
+            (nu + P2P_WAVES - 1) / P2P_WAVES, P2P_WG, 0, s>>>(
             t.pf, t.pfh, t.first, t.count, t.leaf_node, nu, t.near_cnt, t.near_src,
             (int)t.cap_near, nsub, t.Lf, t.recA, t.perm, (float)t.p.G, t.p.r_kern, (float *)a, pl,
             per, (float *)t.pnear.part, stride);

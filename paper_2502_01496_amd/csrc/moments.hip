@@ -35,8 +35,9 @@ __global__ void k_clear_word(uint32_t *w) { *w = 0u; }
 
 __global__ void k_gather(const double *__restrict__ x, const double *__restrict__ m,
                          const double *__restrict__ h, int64_t n, const int32_t *__restrict__ perm,
-                         double4 *pm, double *hs, double4 *ph, uint32_t *err, int nnodes,
-                         uint64_t *s2bits, int32_t *upcnt, int want_fp32, float4 *pfh)
+                         double4 *pm, double *hs, double4 *ph, double2 *pxy, double2 *pzm,
+                         double *phi, uint32_t *err, int nnodes, uint64_t *s2bits, int32_t *upcnt,
+                         int want_fp32, float4 *pfh)
 {
     int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -54,6 +55,11 @@ __global__ void k_gather(const double *__restrict__ x, const double *__restrict_
         hs[p] = hh;
         double hi = 1.0 / hh;
         ph[p] = make_double4(hi, hi * hi * hi, 4.0 * hh * hh, hh);
+        if (pxy) {
+            pxy[p] = make_double2(xx, yy);
+            pzm[p] = make_double2(zz, mm);
+            phi[p] = hi;
+        }
         if (want_fp32)
             pfh[p] = make_float4((float)hi, (float)(hi * hi * hi), (float)(4.0 * hh * hh), 0.0f);
     }
@@ -84,14 +90,42 @@ __device__ __forceinline__ void quad_add(double *Q, double w, double y0, double 
     Q[5] += w * (3.0 * y2 * y2 - yy);
 }
 
+// Bounding box of a leaf, accumulated over its particles, and its record.
+struct LeafBox {
+    double lo0, lo1, lo2, hi0, hi1, hi2;
+    __device__ __forceinline__ void start(const double4 &q)
+    {
+        lo0 = hi0 = q.x;
+        lo1 = hi1 = q.y;
+        lo2 = hi2 = q.z;
+    }
+    __device__ __forceinline__ void add(const double4 &q)
+    {
+        lo0 = fmin(lo0, q.x);
+        lo1 = fmin(lo1, q.y);
+        lo2 = fmin(lo2, q.z);
+        hi0 = fmax(hi0, q.x);
+        hi1 = fmax(hi1, q.y);
+        hi2 = fmax(hi2, q.z);
+    }
+    __device__ __forceinline__ void store(double *o, double hmax) const
+    {
+        ((double4 *)o)[0] = make_double4(0.5 * (lo0 + hi0), 0.5 * (lo1 + hi1), 0.5 * (lo2 + hi2),
+                                         0.5 * (hi0 - lo0));
+        ((double4 *)o)[1] = make_double4(0.5 * (hi1 - lo1), 0.5 * (hi2 - lo2), 4.0 * hmax * hmax,
+                                         0.0);
+    }
+};
+
 // P2M of leaf v (node id): M, c, h_max and the quadrupole about c, written to
-// its records; the values are also returned for a caller that combines them.
+// its records, and the leaf's box; the values are also returned for a caller
+// that combines them.
 __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
                                          const double *__restrict__ hs, int v,
                                          const int32_t *__restrict__ first,
                                          const int32_t *__restrict__ count, double *recA,
-                                         double *recQ, int want_fp32, float4 *pf, double *outA,
-                                         double *outQ)
+                                         double *recQ, double *box, int want_fp32, float4 *pf,
+                                         double *outA, double *outQ)
 {
     int64_t f = first[v];
     int c = count[v];
@@ -102,6 +136,7 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
     constexpr int U = 8;
     double4 q[U];
     double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0, hm = 0.0;
+    LeafBox B;
     for (int k0 = 0; k0 < c; k0 += U) {
         double hh[U];
 #pragma unroll
@@ -110,6 +145,11 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
             q[j] = pm[i];
             hh[j] = hs[i];
         }
+        if (k0 == 0)
+            B.start(q[0]);
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            B.add(q[j]);
 #pragma unroll
         for (int j = 0; j < U; ++j)
             if (k0 + j < c) {
@@ -120,6 +160,7 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
                 hm = hh[j] > hm ? hh[j] : hm;
             }
     }
+    B.store(box, hm);
     double c0 = S0 / M, c1 = S1 / M, c2 = S2 / M;
     double Q[6] = {0, 0, 0, 0, 0, 0};
     for (int k0 = 0; k0 < c; k0 += U) {
@@ -157,13 +198,15 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
 __global__ __launch_bounds__(256) void k_leaf_moments(
     const double4 *__restrict__ pm, const double *__restrict__ hs,
     const int32_t *__restrict__ leaf_node, int nleaves, const int32_t *__restrict__ first,
-    const int32_t *__restrict__ count, double *recA, double *recQ, int want_fp32, float4 *pf)
+    const int32_t *__restrict__ count, double *recA, double *recQ, double *lbox, int want_fp32,
+    float4 *pf)
 {
     int lf = blockIdx.x * blockDim.x + threadIdx.x;
     if (lf >= nleaves)
         return;
     double a[5], q[6];
-    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ, want_fp32, pf, a, q);
+    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ, lbox + (int64_t)LBOX * lf, want_fp32,
+             pf, a, q);
 }
 
 // M2M for the internal nodes of one level (children were done by the
@@ -241,7 +284,8 @@ __global__ __launch_bounds__(256) void k_sub_moments(
     const int32_t *__restrict__ leaf_node, const int32_t *__restrict__ first,
     const int32_t *__restrict__ count, const int32_t *__restrict__ sub_root,
     const int32_t *__restrict__ sm_leaf, const int32_t *__restrict__ sm_lvl,
-    const int2 *__restrict__ sm_nodes, double *recA, double *recQ, int want_fp32, float4 *pf)
+    const int2 *__restrict__ sm_nodes, double *recA, double *recQ, double *lbox, int want_fp32,
+    float4 *pf)
 {
     __shared__ double sA[SM_MAXNODES][5];
     __shared__ double sQ[SM_MAXNODES][6];
@@ -250,7 +294,8 @@ __global__ __launch_bounds__(256) void k_sub_moments(
     const int lf0 = sm_leaf[2 * s], lf1 = sm_leaf[2 * s + 1];
     for (int lf = lf0 + t; lf < lf1; lf += 256) {
         const int v = leaf_node[lf];
-        leaf_p2m(pm, hs, v, first, count, recA, recQ, want_fp32, pf, sA[v - r], sQ[v - r]);
+        leaf_p2m(pm, hs, v, first, count, recA, recQ, lbox + (int64_t)LBOX * lf, want_fp32, pf,
+                 sA[v - r], sQ[v - r]);
     }
     const int32_t *g = sm_lvl + s * (SM_MAXL + 1);
     for (int k = 0; k < SM_MAXL; ++k) {
@@ -589,8 +634,36 @@ __global__ void k_import_offsets(int nleaves, const int32_t *__restrict__ leaf_n
     }
 }
 
+// The leaves' boxes of an imported tree.
+__global__ void k_import_boxes(const double4 *__restrict__ pm, const double *__restrict__ hs,
+                               const int32_t *__restrict__ leaf_node, int nleaves,
+                               const int32_t *__restrict__ first,
+                               const int32_t *__restrict__ count, double *lbox)
+{
+    const int lf = blockIdx.x * blockDim.x + threadIdx.x;
+    if (lf >= nleaves)
+        return;
+    const int64_t f = first[leaf_node[lf]];
+    const int c = count[leaf_node[lf]];
+    LeafBox B;
+    B.start(pm[f]);
+    double hm = 0.0;
+    for (int k = 0; k < c; ++k) {
+        B.add(pm[f + k]);
+        hm = fmax(hm, hs[f + k]);
+    }
+    B.store(lbox + (int64_t)LBOX * lf, hm);
+}
+
 // fmm_debug_import: tree-order particles from the imported permutation (with
 // the data checks of a moments call), then the imported cell records.
+// The arrays that only the near field of the leaf <- cell lists reads are
+// written for a tree that takes it (else nullptr).
+static double2 *lane_arrays(const Tree &t)
+{
+    return t.p.precision == FMM_FP64 && t.p.walk == FMM_WALK_PHANTOM ? t.pxy : nullptr;
+}
+
 hipError_t launch_import(Tree &t, const double *x, const double *m, const double *h,
                          const double *rec12, hipStream_t s)
 {
@@ -600,11 +673,13 @@ hipError_t launch_import(Tree &t, const double *x, const double *m, const double
     const int gs = (int)std::min<int64_t>((work + 255) / 256, 4096);
     const int want32 = t.p.precision == FMM_FP32;
     k_clear_word<<<1, 1, 0, s>>>(t.err + 1);
-    k_gather<<<gs, 256, 0, s>>>(x, m, h, n, t.perm, t.pm, t.hs, t.ph, t.err + 1, T.nnodes,
-                                t.s2bits, t.upcnt, want32, t.pfh);
+    k_gather<<<gs, 256, 0, s>>>(x, m, h, n, t.perm, t.pm, t.hs, t.ph, lane_arrays(t), t.pzm, t.phi,
+                                t.err + 1, T.nnodes, t.s2bits, t.upcnt, want32, t.pfh);
     k_import_records<<<(T.nnodes + 255) / 256, 256, 0, s>>>(T.nnodes, rec12, t.left, t.right,
                                                            t.node_leaf, t.recA, t.recQ, want32,
                                                            t.recF);
+    k_import_boxes<<<(T.nleaves + 255) / 256, 256, 0, s>>>(t.pm, t.hs, t.leaf_node, T.nleaves,
+                                                          t.first, t.count, t.lbox);
     if (want32)
         k_import_offsets<<<(T.nleaves + 255) / 256, 256, 0, s>>>(T.nleaves, t.leaf_node, t.first,
                                                                  t.count, t.recA, t.pm, t.pf);
@@ -620,13 +695,13 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
     int gs = (int)std::min<int64_t>((work + 255) / 256, 4096);
     int want32 = t.p.precision == FMM_FP32;
     k_clear_word<<<1, 1, 0, s>>>(t.err + 1);
-    k_gather<<<gs, 256, 0, s>>>(x, m, h, n, t.perm, t.pm, t.hs, t.ph, t.err + 1, T.nnodes, t.s2bits,
-                                t.upcnt, want32, t.pfh);
+    k_gather<<<gs, 256, 0, s>>>(x, m, h, n, t.perm, t.pm, t.hs, t.ph, lane_arrays(t), t.pzm, t.phi,
+                                t.err + 1, T.nnodes, t.s2bits, t.upcnt, want32, t.pfh);
     if (!T.com && T.sub_moments) {
         // the subtrees in one launch, then the cells above them level by level
         k_sub_moments<<<(int)T.sub_root.size(), 256, 0, s>>>(
             t.pm, t.hs, t.leaf_node, t.first, t.count, t.sub_root, t.sm_leaf, t.sm_lvl,
-            (const int2 *)t.sm_nodes, t.recA, t.recQ, want32, t.pf);
+            (const int2 *)t.sm_nodes, t.recA, t.recQ, t.lbox, want32, t.pf);
         if (T.top_fused) {
             if (!T.top_nodes.empty())
                 k_top_moments<<<1, 1024, 0, s>>>(t.top_slot_node, (int)T.sub_root.size(),
@@ -642,7 +717,7 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
         }
     } else {
         k_leaf_moments<<<(T.nleaves + 255) / 256, 256, 0, s>>>(
-            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, want32, t.pf);
+            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, t.lbox, want32, t.pf);
         for (int l = T.depth - 2; l >= 0; --l) {
             int o = T.lvl_int_off[l], cnt = T.lvl_int_off[l + 1] - o;
             if (cnt > 0)
