@@ -754,13 +754,13 @@ static fmm_status ensure_piece_base(Tree &t)
     return FMM_OK;
 }
 
-// The piece totals (near, far) to the pinned host buffer.
-static hipError_t read_piece_totals_async(Tree &t, hipStream_t s)
+// The piece totals (near, and far if asked) to the pinned host buffer.
+static hipError_t read_piece_totals_async(Tree &t, bool far, hipStream_t s)
 {
     const int nl = t.topo.nleaves;
     hipError_t e = hipMemcpyAsync(t.h_piece, t.pnear.off + nl, sizeof(int64_t),
                                   hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
+    if (e == hipSuccess && far)
         e = hipMemcpyAsync(t.h_piece + 1, t.pfar.off + nl, sizeof(int64_t), hipMemcpyDeviceToHost,
                            s);
     return e;
@@ -768,21 +768,23 @@ static hipError_t read_piece_totals_async(Tree &t, hipStream_t s)
 
 // Lay out the pieces of the current lists: counts and offsets (unless the
 // totals were already read back with them, have_totals), buffers for the
-// pieces and their partial sums, and the piece lists.
+// pieces and their partial sums, and the piece lists.  The lists of a mutual
+// walk: near lists only.
 static fmm_status build_pieces(Tree &t, hipStream_t s, bool have_totals)
 {
     fmm_status st = ensure_piece_base(t);
     if (st != FMM_OK)
         return st;
+    const bool far = t.lists_policy != FMM_WALK_MUTUAL;
     if (!have_totals) {
-        HIP_TRY(launch_piece_counts(t, s));
-        HIP_TRY(read_piece_totals_async(t, s));
+        HIP_TRY(launch_piece_counts(t, far, s));
+        HIP_TRY(read_piece_totals_async(t, far, s));
         HIP_TRY(hipStreamSynchronize(s));
     }
     const size_t strides[2] = {(size_t)3 * t.topo.leaf_size * sizeof(double),
                                (size_t)NLOC * sizeof(double)};
     Tree::Pieces *Ps[2] = {&t.pnear, &t.pfar};
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < (far ? 2 : 1); ++k) {
         Tree::Pieces &P = *Ps[k];
         const int64_t np = t.h_piece[k];
         if (np > P.cap) {
@@ -806,7 +808,7 @@ static fmm_status build_pieces(Tree &t, hipStream_t s, bool have_totals)
         P.n = np;
         P.part_stride = strides[k];
     }
-    HIP_TRY(launch_piece_fill(t, s));
+    HIP_TRY(launch_piece_fill(t, far, s));
     t.pieces_valid = true;
     return FMM_OK;
 }
@@ -895,6 +897,10 @@ static fmm_status forces_mutual(Tree &t, void *a, bool walk, bool vjp_only, hipS
         }
         if (!done)
             return fail(FMM_ERR_CAPACITY, "mutual walk buffers did not fit after resizing");
+        // the longest near list is known before the lists are evaluated
+        const int64_t mx = (int64_t)M.h_cnt[MW_MAXNEAR];
+        t.pieces_valid = false;
+        t.split_lists = mx * ((T.leaf_size + 7) / 8) > t.near_piece_blocks;
         t.has_lists = true;
         t.has_transposed = false;
         t.lists_policy = FMM_WALK_MUTUAL;
@@ -903,6 +909,11 @@ static fmm_status forces_mutual(Tree &t, void *a, bool walk, bool vjp_only, hipS
         t.n_near = M.n_near;
     } else {
         fmm_status st = ensure_mutual(t, 0, 0, 0);  // Lown of the current precision
+        if (st != FMM_OK)
+            return st;
+    }
+    if (t.split_lists && !t.pieces_valid) {
+        fmm_status st = build_pieces(t, s, false);
         if (st != FMM_OK)
             return st;
     }
@@ -1146,8 +1157,8 @@ fmm_status fmm_forces(fmm_tree *tree, void *a, int32_t flags, void *stream)
             fmm_status st = ensure_piece_base(t);
             if (st != FMM_OK)
                 return st;
-            HIP_TRY(launch_piece_counts(t, s));
-            HIP_TRY(read_piece_totals_async(t, s));
+            HIP_TRY(launch_piece_counts(t, true, s));
+            HIP_TRY(read_piece_totals_async(t, true, s));
         } else {
             if (far_needed) {
                 StageTimer tm(t, s, 3);

@@ -420,17 +420,16 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s);
 hipError_t launch_count_scan(const int32_t *cnt, int cap, int n, int64_t *tsum, int64_t *off,
                              hipStream_t s);
 int64_t count_scan_workspace(int n);
-hipError_t launch_piece_counts(Tree &t, hipStream_t s);
-hipError_t launch_piece_fill(Tree &t, hipStream_t s);
+hipError_t launch_piece_counts(Tree &t, bool far, hipStream_t s);
+hipError_t launch_piece_fill(Tree &t, bool far, hipStream_t s);
 hipError_t launch_piece_table(const int64_t *off, const int32_t *np, int nleaves, int2 *list,
                               hipStream_t s);
 
 // The forward lists are split into pieces (the last walk found a list
 // longer than one piece, and the piece tables describe the current lists).
-inline bool use_pieces(const Tree &t)
-{
-    return t.split_lists && t.pieces_valid && t.lists_policy == FMM_WALK_PHANTOM;
-}
+// After a mutual walk only the near lists have pieces (its far field is
+// evaluated per cell, over ranges of the sorted pairs).
+inline bool use_pieces(const Tree &t) { return t.split_lists && t.pieces_valid; }
 hipError_t launch_stats(const double *x, const double *v, const double *m, const void *a,
                         int a_fp32, int64_t n, double *red, double *d_out, double *h_out,
                         hipStream_t s);

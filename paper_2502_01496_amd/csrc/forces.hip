@@ -1509,27 +1509,29 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s)
 
 // Pieces per leaf of the current lists and their offsets (device; the totals
 // sit at off[nleaves]).
-hipError_t launch_piece_counts(Tree &t, hipStream_t s)
+hipError_t launch_piece_counts(Tree &t, bool far, hipStream_t s)
 {
     const int nl = t.topo.nleaves;
     const int nsub = (t.topo.leaf_size + 7) / 8;
     const int g = (nl + 255) / 256;
     k_piece_count<<<g, 256, 0, s>>>(t.near_cnt, (int)t.cap_near, nl, nsub, t.near_piece_blocks,
                                     t.pnear.np);
-    k_piece_count<<<g, 256, 0, s>>>(t.far_cnt, (int)t.cap_far, nl, 1, t.far_piece_entries,
+    if (far)
+        k_piece_count<<<g, 256, 0, s>>>(t.far_cnt, (int)t.cap_far, nl, 1, t.far_piece_entries,
                                     t.pfar.np);
     hipError_t e = launch_count_scan(t.pnear.np, INT32_MAX, nl, t.pnear.tsum, t.pnear.off, s);
-    if (e == hipSuccess)
+    if (e == hipSuccess && far)
         e = launch_count_scan(t.pfar.np, INT32_MAX, nl, t.pfar.tsum, t.pfar.off, s);
     return e;
 }
 
-hipError_t launch_piece_fill(Tree &t, hipStream_t s)
+hipError_t launch_piece_fill(Tree &t, bool far, hipStream_t s)
 {
     const int nl = t.topo.nleaves;
     const int g = (nl + 255) / 256;
     k_piece_fill<<<g, 256, 0, s>>>(t.pnear.off, t.pnear.np, nl, t.pnear.list);
-    k_piece_fill<<<g, 256, 0, s>>>(t.pfar.off, t.pfar.np, nl, t.pfar.list);
+    if (far)
+        k_piece_fill<<<g, 256, 0, s>>>(t.pfar.off, t.pfar.np, nl, t.pfar.list);
     return hipGetLastError();
 }
 

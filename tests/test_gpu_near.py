@@ -45,3 +45,59 @@ def test_coincident_particles(orc):
     say("[gpu near] 40 coincident pairs")
     a, _, _ = gpu_run(x, m, h, export=False)
     assert force_err(a, orc.fmm(x, m, h).a) <= 1e-12
+
+
+@pytest.mark.parametrize("precision", [F.FMM_FP64, F.FMM_FP32])
+@pytest.mark.parametrize("piece", [1, 7, None])
+def test_mutual_near_lists_in_pieces(orc, monkeypatch, piece, precision):
+    # two stars and one particle more: the leaf that holds particles of both
+    # has every leaf in its near list (longer than a piece of 512 blocks).
+    # Forces against the oracle, total force zero to rounding, the reverse pass
+    # as with whole lists; forces on kept lists as after the walk
+    import torch
+
+    from tests.gpu_util import to_dev
+
+    n = 1501 if piece else 9001
+    x, m, h = W.polytrope_binary(n, 8, cache=False)
+    x, m, h = x[:-1], m[:-1], h[:-1]
+    say(f"[gpu near] mutual binary {len(m)}, pieces of {piece}, precision {precision}")
+    dt = torch.float32 if precision == F.FMM_FP32 else torch.float64
+    X, Mt, H = to_dev(x, m, h)
+    AB = torch.from_numpy(W.cotangent(len(m), 5)).cuda().to(dt)
+
+    def run(hook):
+        if hook:
+            monkeypatch.setenv("FMM_MI355_PIECE", str(hook))
+        t = F.fmm_build_tree(X, F.default_params(walk=F.FMM_WALK_MUTUAL, precision=precision))
+        monkeypatch.delenv("FMM_MI355_PIECE", raising=False)
+        try:
+            F.fmm_moments(t, X, Mt, H)
+            out = []
+            for flags in (0, 0, F.FMM_REWALK):
+                A = torch.empty((len(m), 3), dtype=dt, device="cuda")
+                F.fmm_forces(t, A, flags)
+                out.append(A)
+            XB, MB = torch.empty_like(A), torch.empty(len(m), dtype=dt, device="cuda")
+            F.fmm_forces_vjp(t, AB, XB, MB)
+            torch.cuda.synchronize()
+            st = F.fmm_momentum_stats(X, None, Mt, out[0])
+        finally:
+            F.fmm_tree_free(t)
+        return [a.cpu().numpy() for a in out], XB.cpu().numpy(), MB.cpu().numpy(), st
+
+    a, xb, mb, st = run(piece)
+    np.testing.assert_array_equal(a[0], a[1])
+    np.testing.assert_array_equal(a[0], a[2])
+    ref = orc.fmm(x, m, h, policy=1).a
+    if precision == F.FMM_FP64:
+        assert force_err(a[0], ref) <= 1e-12
+        assert st["ratio"] <= 1e-13
+    else:
+        d = a[0].astype(np.float64) - ref
+        assert np.sqrt((d * d).sum() / (ref ** 2).sum()) <= 1e-5
+    # pieces of a million blocks: whole lists
+    _, xw, mw, _ = run(1000000)
+    tol = 1e-12 if precision == F.FMM_FP64 else 1e-5
+    assert np.abs(xb - xw).max() <= tol * np.abs(xw).max()
+    assert np.abs(mb - mw).max() <= tol * np.abs(mw).max()
