@@ -153,6 +153,103 @@ __device__ __forceinline__ void m2l_acc(T rx, T ry, T rz, T M, const T *Q, T *L)
              b3 * (T(3) * rz * Qzz);
 }
 
+// FP64 sums of eq. (6)'s form over the sources of one lane, in another
+// grouping of the same terms: with v_n = r^-(2n+1), t = 35/2 v4 q + a2/6 r,
+// P_ij = r_i t_j + t_i r_j + b3 Q_ij and s = a1/2 r + b3 q,
+//   L2_ij  = r_i s_j + s_i r_j + b2 Q_ij + a0 d_ij,
+//   L3_ijk = r_i P_jk + r_j P_ik + r_k P_ij + d_ij w_k + d_ik w_j + d_jk w_i,
+//   w = s + a1/2 r,
+// and the terms with d_ij (a0 and w) are summed apart and added at the end:
+// 120 FP64 instructions per source instead of 190.  The leaf M2L is bound by
+// its record loads as much as by these (five 16-byte loads per lane and
+// source, each of its own cache line), so a third fewer instructions give
+// 218 -> 205 us (binary, 2^19 particles) and 2.09 -> 2.00 ms (clumpy cube,
+// 2^22).  Reading the records by neighbouring lanes together and passing them
+// on through LDS spills here and took 388 us (2^19).
+struct M2lSum64 {
+    double l1[3], l2[6], l3[10], a0, w[3];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            l1[k] = w[k] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            l2[k] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 10; ++k)
+            l3[k] = 0.0;
+        a0 = 0.0;
+    }
+    __device__ __forceinline__ void add(double x, double y, double z, double M, const double *Q)
+    {
+        const double u = rsqrt_pos(x * x + y * y + z * z);  // r > 0: far cells are apart
+        const double u2 = u * u;
+        const double v1 = u * u2, v2 = v1 * u2, v3 = v2 * u2, v4 = v3 * u2, v5 = v4 * u2;
+        const double qx = Q[0] * x + Q[1] * y + Q[2] * z;
+        const double qy = Q[1] * x + Q[3] * y + Q[4] * z;
+        const double qz = Q[2] * x + Q[4] * y + Q[5] * z;
+        const double qq = 2.5 * (qx * x + qy * y + qz * z);
+        const double m0 = M * v1 + qq * v3;                             // -a0
+        const double h1 = (1.5 * M) * v2 + (3.5 * qq) * v4;             // a1 / 2
+        const double c2 = -((2.5 * M) * v3 + (10.5 * qq) * v5);         // a2 / 6
+        const double b3 = -5.0 * v3, c4 = 17.5 * v4;
+        const double tx = c4 * qx + c2 * x, ty = c4 * qy + c2 * y, tz = c4 * qz + c2 * z;
+        const double sx = b3 * qx + h1 * x, sy = b3 * qy + h1 * y, sz = b3 * qz + h1 * z;
+        const double x2 = x + x, y2 = y + y, z2 = z + z;
+        l1[0] += v2 * qx - m0 * x;
+        l1[1] += v2 * qy - m0 * y;
+        l1[2] += v2 * qz - m0 * z;
+        a0 -= m0;
+        l2[0] = fma(v2, Q[0], fma(x2, sx, l2[0]));
+        l2[1] = fma(v2, Q[1], fma(y, sx, fma(x, sy, l2[1])));
+        l2[2] = fma(v2, Q[2], fma(z, sx, fma(x, sz, l2[2])));
+        l2[3] = fma(v2, Q[3], fma(y2, sy, l2[3]));
+        l2[4] = fma(v2, Q[4], fma(z, sy, fma(y, sz, l2[4])));
+        l2[5] = fma(v2, Q[5], fma(z2, sz, l2[5]));
+        w[0] = fma(h1, x, w[0] + sx);
+        w[1] = fma(h1, y, w[1] + sy);
+        w[2] = fma(h1, z, w[2] + sz);
+        const double pxx = fma(x2, tx, b3 * Q[0]), pyy = fma(y2, ty, b3 * Q[3]),
+                     pzz = fma(z2, tz, b3 * Q[5]);
+        const double pxy = fma(x, ty, fma(y, tx, b3 * Q[1])),
+                     pxz = fma(x, tz, fma(z, tx, b3 * Q[2])),
+                     pyz = fma(y, tz, fma(z, ty, b3 * Q[4]));
+        l3[0] = fma(x, pxx, l3[0]);
+        l3[1] = fma(x2, pxy, fma(y, pxx, l3[1]));
+        l3[2] = fma(x2, pxz, fma(z, pxx, l3[2]));
+        l3[3] = fma(y2, pxy, fma(x, pyy, l3[3]));
+        l3[4] = fma(x, pyz, fma(y, pxz, fma(z, pxy, l3[4])));
+        l3[5] = fma(z2, pxz, fma(x, pzz, l3[5]));
+        l3[6] = fma(y, pyy, l3[6]);
+        l3[7] = fma(y2, pyz, fma(z, pyy, l3[7]));
+        l3[8] = fma(z2, pyz, fma(y, pzz, l3[8]));
+        l3[9] = fma(z, pzz, l3[9]);
+    }
+    __device__ __forceinline__ void total(double *L) const
+    {
+        L[0] = l1[0];
+        L[1] = l1[1];
+        L[2] = l1[2];
+        L[3] = l2[0] + a0;
+        L[4] = l2[1];
+        L[5] = l2[2];
+        L[6] = l2[3] + a0;
+        L[7] = l2[4];
+        L[8] = l2[5] + a0;
+        L[9] = 3.0 * (l3[0] + w[0]);
+        L[10] = l3[1] + w[1];
+        L[11] = l3[2] + w[2];
+        L[12] = l3[3] + w[0];
+        L[13] = l3[4];
+        L[14] = l3[5] + w[0];
+        L[15] = 3.0 * (l3[6] + w[1]);
+        L[16] = l3[7] + w[2];
+        L[17] = l3[8] + w[1];
+        L[18] = 3.0 * (l3[9] + w[2]);
+    }
+};
+
 // ---------------------------------------------------------------- list pieces
 // Pieces per leaf for a list of min(cnt, cap) entries of `mult` work units
 // each: ceil(work / per), at least one.
@@ -208,33 +305,6 @@ __global__ __launch_bounds__(256) void k_m2l_fold(const int32_t *__restrict__ le
 }
 
 // ---------------------------------------------------------------- M2L at the leaves
-// One source of the leaf M2L: FP64 records, or the FP32 form (r formed in
-// FP64 and rounded, M and Q from the FP32 mirror of the records, FP32
-// accumulation).
-template <int FORM>
-__device__ __forceinline__ void m2l_leaf_src(const double *__restrict__ recA,
-                                             const double *__restrict__ recQ, const float *,
-                                             int b, double c0, double c1, double c2, double *L)
-{
-    const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
-    const double *qb = recQ + (int64_t)NREC * b;
-    const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
-                  q45 = *(const double2 *)(qb + 4);
-    const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
-    m2l_acc<double, FORM>(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q, L);
-}
-template <int FORM>
-__device__ __forceinline__ void m2l_leaf_src(const double *__restrict__ recA, const double *,
-                                             const float *__restrict__ recF, int b, double c0,
-                                             double c1, double c2, float *L)
-{
-    const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
-    const float4 f0 = *(const float4 *)(recF + (int64_t)NREC * b);
-    const float4 f1 = *(const float4 *)(recF + (int64_t)NREC * b + 4);
-    const float Q[6] = {f0.y, f0.z, f0.w, f1.x, f1.y, f1.z};
-    m2l_acc<float, FORM>((float)(c0 - cb.x), (float)(c1 - cb.y), (float)(c2 - cb.z), f0.x, Q, L);
-}
-
 // The FP32 form with the load of the source record apart from the
 // arithmetic, so that the next source's record can be in flight while the
 // current one is evaluated.
@@ -324,13 +394,26 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
             }
         } else {
             // the next source's index is loaded one interaction ahead
+            [[maybe_unused]] M2lSum64 S;
+            if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+                S.clear();
             int bn = p0 + sub < p1 ? fl[p0 + sub] : 0;
             for (int k = p0 + sub; k < p1; k += M2L_LANES) {
                 const int b = bn;
                 if (k + M2L_LANES < p1)
                     bn = fl[k + M2L_LANES];
-                m2l_leaf_src<FORM>(recA, recQ, recF, b, c0, c1, c2, L);
+                const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
+                const double *qb = recQ + (int64_t)NREC * b;
+                const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
+                              q45 = *(const double2 *)(qb + 4);
+                const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+                if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+                    S.add(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q);
+                else
+                    m2l_acc<double, FORM>(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q, L);
             }
+            if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+                S.total(L);
         }
 #pragma unroll
         for (int off = M2L_LANES / 2; off >= 1; off >>= 1)
