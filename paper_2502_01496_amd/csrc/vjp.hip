@@ -11,7 +11,11 @@
 //   2. M2L^T, sink side per leaf over its far list (cbar_a += rbar) and source
 //      side per cell over the transposed far list (Mbar_b, Qbar_b, cbar_b -= rbar);
 //      the adjoint of one M2L term is the reverse-mode derivative of the
-//      forward factorisation (a0, a1, a2, b2, b3, b4, q) and needs g_1..g_6;
+//      forward factorisation (a0, a1, a2, b2, b3, b4, q) and needs g_1..g_6.
+//      In eq. (6) L2 = dL1/dr and L3 = dL2/dr, so on the sink side the first
+//      two orders' share of rbar, summed over the list, is a contraction of
+//      the forward sums (step 1 adds it) and only the third order's is summed
+//      over the list;
 //   3. P2P^T: per pair dbar = -m_j [G_ij abar'_i + (G'_ij / r)(d . abar'_i) d],
 //      xbar_i += dbar (sink side, near lists), xbar_j -= dbar and
 //      mbar_j -= G_ij (d . abar'_i) (source side, transposed near lists);
@@ -52,9 +56,18 @@ __device__ __forceinline__ constexpr int sym3(int i, int j, int k)
     return a == 0 ? (b == 0 ? c : (b == 1 ? 2 + c : 5)) : (a == 1 ? (b == 1 ? 5 + c : 8) : 9);
 }
 
-__device__ __forceinline__ constexpr double mult3(int i, int j, int k)
+// Stored cotangent of a local expansion -> the form that the M2L adjoint
+// reads: the full symmetric tensors' distinct entries (a stored off-diagonal
+// entry stands for 2, 3 or 6 equal ones), the third order times 3.
+__device__ __forceinline__ void lbar_full(double *Lb)
 {
-    return (i == j && j == k) ? 1.0 : ((i == j || j == k || i == k) ? 3.0 : 6.0);
+    Lb[4] *= 0.5;
+    Lb[5] *= 0.5;
+    Lb[7] *= 0.5;
+    Lb[9] *= 3.0;
+    Lb[13] *= 0.5;
+    Lb[15] *= 3.0;
+    Lb[18] *= 3.0;
 }
 
 // ---------------------------------------------------------------- M2L adjoint
@@ -89,7 +102,7 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            B[i][j] = Lb[3 + sym2(i, j)] * (i == j ? 1.0 : 0.5);
+            B[i][j] = Lb[3 + sym2(i, j)];
     double T[3][3][3];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -97,7 +110,7 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 3; ++k)
-                T[i][j][k] = Lb[9 + sym3(i, j, k)] * (1.0 / mult3(i, j, k));
+                T[i][j][k] = Lb[9 + sym3(i, j, k)] * k3;
     double Br[3], tr1[3], Trr[3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
@@ -142,139 +155,145 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
             Qb[sym2(i, j)] += i == j ? qb[i] * r[i] : qb[i] * r[j] + qb[j] * r[i];
 }
 
-// Given the stored cotangent Lb[19] of one M2L term K(r; M, Q), accumulate
-// d<Lb, K>/dr into rb, d/dM into Mb and d/dQ (stored entries) into Qb.
+// Given the cotangent Lb[19] (lbar_full) of one M2L term K(r; M, Q),
+// accumulate d<Lb, K>/dr into rb, d/dM into Mb and d/dQ (stored entries) into
+// Qb.  With A, B, T the three orders of Lb, E = <Lb, K> is
+//   g1 M e0 + g2 (M e1 + f2 / 3) + g3 (M e2 + qq/6 e0 + f3 / 3) + g4 (qq/6 e1 + f4 / 3)
+//   + g5 qq/6 e2,
+//   e0 = A.r + tr B, e1 = B:rr + t1.r, e2 = T:rrr / 3, f2 = A.q + B:Q,
+//   f3 = 2 B:rq + t1.q + (T:Q).r, f4 = T:rrq,
+// t1 the trace of T, and its derivative takes two products with the matrices
+// B and T r (w1 and w2 below): 250 instructions.
 // FORM = FMM_EXPANSION_DEHNEN: K's second and third orders come from the
 // monopole alone (A0 = M g1, A1 = M g2, A2 = M g3 in place of a0, a1, a2 and
 // no b3, b4 terms), so the quadrupole is reached through L1 only.
 template <int FORM>
-__device__ __forceinline__ void m2l_vjp(const double r[3], double M, const double *Qs,
+__device__ __forceinline__ void m2l_vjp(const double r[3], double M, const double *Q,
                                         const double *Lb, double rb[3], double &Mb, double Qb[6])
 {
     if constexpr (FORM == FMM_EXPANSION_DEHNEN) {
-        m2l_vjp_dehnen(r, M, Qs, Lb, rb, Mb, Qb);
+        m2l_vjp_dehnen(r, M, Q, Lb, rb, Mb, Qb);
         return;
     }
-    const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const double u = rsqrt_pos(r2);  // r2 > 0: far pairs are separated
+    const double x = r[0], y = r[1], z = r[2];
+    const double *A = Lb, *B = Lb + 3, *T = Lb + 9;
+    const double u = rsqrt_pos(x * x + y * y + z * z);  // r > 0: far pairs are separated
     const double u2 = u * u;
-    const double g1 = -u * u2, g2 = -3.0 * g1 * u2, g3 = -5.0 * g2 * u2, g4 = -7.0 * g3 * u2,
-                 g5 = -9.0 * g4 * u2, g6 = -11.0 * g5 * u2;
-    double Qf[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            Qf[i][j] = Qs[sym2(i, j)];
-    double q[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        q[i] = Qf[i][0] * r[0] + Qf[i][1] * r[1] + Qf[i][2] * r[2];
-    const double qq = q[0] * r[0] + q[1] * r[1] + q[2] * r[2];
-    // divisions by the constants 3 and 6 are taken as products with their
-    // rounded reciprocals (no FP64 divide in the loop)
-    constexpr double k3 = 1.0 / 3.0, k6 = 1.0 / 6.0;
-    const double qq6 = qq * k6;
-    const double a0 = M * g1 + g3 * qq6, a1 = M * g2 + g4 * qq6, a2 = M * g3 + g5 * qq6;
-    const double b2 = g2 * k3, b3 = g3 * k3, b4 = g4 * k3;
-    // full symmetric cotangent tensors
-    const double A[3] = {Lb[0], Lb[1], Lb[2]};
-    double B[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            B[i][j] = Lb[3 + sym2(i, j)] * (i == j ? 1.0 : 0.5);
-    double T[3][3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                T[i][j][k] = Lb[9 + sym3(i, j, k)] * (1.0 / mult3(i, j, k));
-    // contractions
-    double Br[3], Bq[3], tr1[3], Trr[3], Trq[3], TQ[3], Tr[3][3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        Br[m] = B[m][0] * r[0] + B[m][1] * r[1] + B[m][2] * r[2];
-        Bq[m] = B[m][0] * q[0] + B[m][1] * q[1] + B[m][2] * q[2];
-        tr1[m] = T[0][0][m] + T[1][1][m] + T[2][2][m];
-        double s_rr = 0.0, s_rq = 0.0, s_Q = 0.0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                s_rr += T[i][j][m] * r[i] * r[j];
-                s_rq += T[i][j][m] * r[i] * q[j];
-                s_Q += T[m][i][j] * Qf[i][j];
-            }
-        Trr[m] = s_rr;
-        Trq[m] = s_rq;
-        TQ[m] = s_Q;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            Tr[m][k] = T[0][m][k] * r[0] + T[1][m][k] * r[1] + T[2][m][k] * r[2];
-    }
-    const double Ar = A[0] * r[0] + A[1] * r[1] + A[2] * r[2];
-    const double Aq = A[0] * q[0] + A[1] * q[1] + A[2] * q[2];
-    const double trB = B[0][0] + B[1][1] + B[2][2];
-    const double Brr = Br[0] * r[0] + Br[1] * r[1] + Br[2] * r[2];
-    const double Brq = Bq[0] * r[0] + Bq[1] * r[1] + Bq[2] * r[2];
-    double BQ = 0.0, TrQ = 0.0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            BQ += B[i][j] * Qf[i][j];
-            TrQ += Tr[i][j] * Qf[i][j];
-        }
-    const double tr1r = tr1[0] * r[0] + tr1[1] * r[1] + tr1[2] * r[2];
-    const double tr1q = tr1[0] * q[0] + tr1[1] * q[1] + tr1[2] * q[2];
-    const double Trrr = Trr[0] * r[0] + Trr[1] * r[1] + Trr[2] * r[2];
-    const double Trrq = Trr[0] * q[0] + Trr[1] * q[1] + Trr[2] * q[2];
-    // cotangents of the scalar coefficients
-    const double a0b = Ar + trB;
-    const double a1b = Brr + 3.0 * tr1r;
-    const double a2b = Trrr;
-    const double b2b = Aq + BQ;
-    const double b3b = 2.0 * Brq + 3.0 * tr1q + 3.0 * TrQ;
-    const double b4b = 3.0 * Trrq;
-    // explicit dependence on r, q, Q
-    double rbl[3], qb[3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        rbl[m] = a0 * A[m] + 2.0 * a1 * Br[m] + 2.0 * b3 * Bq[m] + 3.0 * a2 * Trr[m] +
-                 3.0 * a1 * tr1[m] + 6.0 * b4 * Trq[m] + 3.0 * b3 * TQ[m];
-        qb[m] = b2 * A[m] + 2.0 * b3 * Br[m] + 3.0 * b4 * Trr[m] + 3.0 * b3 * tr1[m];
-    }
-    // through the coefficients
-    Mb += a0b * g1 + a1b * g2 + a2b * g3;
-    const double qqb = (a0b * g3 + a1b * g4 + a2b * g5) * k6;
-    const double gb1 = a0b * M;
-    const double gb2 = a1b * M + b2b * k3;
-    const double gb3 = a2b * M + a0b * qq6 + b3b * k3;
-    const double gb4 = a1b * qq6 + b4b * k3;
-    const double gb5 = a2b * qq6;
-    const double sg = gb1 * g2 + gb2 * g3 + gb3 * g4 + gb4 * g5 + gb5 * g6;
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-        qb[m] += qqb * r[m];
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-        rb[m] += rbl[m] + qqb * q[m] + (qb[0] * Qf[0][m] + qb[1] * Qf[1][m] + qb[2] * Qf[2][m]) +
-                 sg * r[m];
-    // stored quadrupole entries: explicit symmetric part + q = Qf r
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = i; j < 3; ++j) {
-            const double ex = b2 * B[i][j] + 3.0 * b3 * Tr[i][j];
-            if (i == j)
-                Qb[sym2(i, j)] += ex + qb[i] * r[i];
-            else
-                Qb[sym2(i, j)] += 2.0 * ex + qb[i] * r[j] + qb[j] * r[i];
-        }
+    const double v1 = u2 * u, v2 = v1 * u2, v3 = v2 * u2, v4 = v3 * u2, v5 = v4 * u2,
+                 v6 = v5 * u2;
+    const double qx = Q[0] * x + Q[1] * y + Q[2] * z;
+    const double qy = Q[1] * x + Q[3] * y + Q[4] * z;
+    const double qz = Q[2] * x + Q[4] * y + Q[5] * z;
+    const double q6 = (1.0 / 6.0) * (qx * x + qy * y + qz * z);
+    // B r, T r, T r r, T : Q and the trace of T
+    const double Bx = B[0] * x + B[1] * y + B[2] * z, By = B[1] * x + B[3] * y + B[4] * z,
+                 Bz = B[2] * x + B[4] * y + B[5] * z;
+    const double T0 = T[0] * x + T[1] * y + T[2] * z;  // xx, xy, xz, yy, yz, zz
+    const double T1 = T[1] * x + T[3] * y + T[4] * z;
+    const double T2 = T[2] * x + T[4] * y + T[5] * z;
+    const double T3 = T[3] * x + T[6] * y + T[7] * z;
+    const double T4 = T[4] * x + T[7] * y + T[8] * z;
+    const double T5 = T[5] * x + T[8] * y + T[9] * z;
+    const double rx = T0 * x + T1 * y + T2 * z, ry = T1 * x + T3 * y + T4 * z,
+                 rz = T2 * x + T4 * y + T5 * z;
+    const double d1 = Q[1] + Q[1], d2 = Q[2] + Q[2], d4 = Q[4] + Q[4];
+    const double wx = T[0] * Q[0] + T[1] * d1 + T[2] * d2 + T[3] * Q[3] + T[4] * d4 + T[5] * Q[5];
+    const double wy = T[1] * Q[0] + T[3] * d1 + T[4] * d2 + T[6] * Q[3] + T[7] * d4 + T[8] * Q[5];
+    const double wz = T[2] * Q[0] + T[4] * d1 + T[5] * d2 + T[7] * Q[3] + T[8] * d4 + T[9] * Q[5];
+    const double tx = T[0] + T[3] + T[5], ty = T[1] + T[6] + T[8], tz = T[2] + T[7] + T[9];
+    const double e0 = A[0] * x + A[1] * y + A[2] * z + (B[0] + B[3] + B[5]);
+    const double e1 = Bx * x + By * y + Bz * z + (tx * x + ty * y + tz * z);
+    const double rrr = rx * x + ry * y + rz * z;       // 3 e2
+    const double f2 = A[0] * qx + A[1] * qy + A[2] * qz +
+                      (B[0] * Q[0] + B[1] * d1 + B[2] * d2 + B[3] * Q[3] + B[4] * d4 + B[5] * Q[5]);
+    const double f3 = 2.0 * (Bx * qx + By * qy + Bz * qz) + (tx * qx + ty * qy + tz * qz) +
+                      (wx * x + wy * y + wz * z);
+    const double f4 = rx * qx + ry * qy + rz * qz;
+    // g_n = -1, 3, -15, 105, -945, 10395 times v_n
+    const double h3 = 35.0 * v4, h4 = -315.0 * v5, h5 = 3465.0 * v6;  // g_n / 3, n = 4..6
+    const double g4 = 3.0 * h3, g5 = 3.0 * h4, g2 = 3.0 * v2, g3 = -15.0 * v3;
+    const double b3 = -5.0 * v3;
+    const double a0 = fma(g3, q6, -(M * v1)), a1 = fma(g4, q6, g2 * M), a2 = fma(g5, q6, g3 * M);
+    Mb += fma(b3, rrr, fma(g2, e1, -(v1 * e0)));
+    // the sum of g_{n+1} times the bracket of g_n, and twice qq's cotangent
+    const double sg = a1 * e0 + a2 * e1 + fma(h5, q6, h3 * M) * rrr + b3 * f2 + h3 * f3 + h4 * f4;
+    const double qb2 = fma(b3, e0, fma(h3, e1, (1.0 / 3.0) * (h4 * rrr)));
+    const double qb1 = 0.5 * qb2;
+    // cotangent of q apart from qq's
+    const double bb = b3 + b3;
+    const double px = fma(v2, A[0], fma(bb, Bx, fma(h3, rx, b3 * tx)));
+    const double py = fma(v2, A[1], fma(bb, By, fma(h3, ry, b3 * ty)));
+    const double pz = fma(v2, A[2], fma(bb, Bz, fma(h3, rz, b3 * tz)));
+    const double a12 = a1 + a1, h32 = h3 + h3;
+    const double w1x = fma(a12, x, bb * qx), w1y = fma(a12, y, bb * qy), w1z = fma(a12, z, bb * qz);
+    const double w2x = fma(a2, x, h32 * qx), w2y = fma(a2, y, h32 * qy), w2z = fma(a2, z, h32 * qz);
+    rb[0] += a0 * A[0] + a1 * tx + b3 * wx + qb2 * qx + sg * x + B[0] * w1x + B[1] * w1y +
+             B[2] * w1z + T0 * w2x + T1 * w2y + T2 * w2z + Q[0] * px + Q[1] * py + Q[2] * pz;
+    rb[1] += a0 * A[1] + a1 * ty + b3 * wy + qb2 * qy + sg * y + B[1] * w1x + B[3] * w1y +
+             B[4] * w1z + T1 * w2x + T3 * w2y + T4 * w2z + Q[1] * px + Q[3] * py + Q[4] * pz;
+    rb[2] += a0 * A[2] + a1 * tz + b3 * wz + qb2 * qz + sg * z + B[2] * w1x + B[4] * w1y +
+             B[5] * w1z + T2 * w2x + T4 * w2y + T5 * w2z + Q[2] * px + Q[4] * py + Q[5] * pz;
+    // stored quadrupole entries: explicit symmetric part + q = Q r
+    const double sx = fma(qb1, x, px), sy = fma(qb1, y, py), sz = fma(qb1, z, pz);
+    const double v22 = v2 + v2;
+    Qb[0] = fma(sx, x, fma(b3, T0, fma(v2, B[0], Qb[0])));
+    Qb[1] = fma(sx, y, fma(sy, x, fma(bb, T1, fma(v22, B[1], Qb[1]))));
+    Qb[2] = fma(sx, z, fma(sz, x, fma(bb, T2, fma(v22, B[2], Qb[2]))));
+    Qb[3] = fma(sy, y, fma(b3, T3, fma(v2, B[3], Qb[3])));
+    Qb[4] = fma(sy, z, fma(sz, y, fma(bb, T4, fma(v22, B[4], Qb[4]))));
+    Qb[5] = fma(sz, z, fma(b3, T5, fma(v2, B[5], Qb[5])));
+}
+
+// Sink side of eq. (6)'s form: d<L3b, K's third order>/dr of one M2L term,
+// added to rb.  T is three times the full symmetric cotangent of L3 (its ten
+// distinct entries), t1 its trace.
+__device__ __forceinline__ void m2l_vjp_third(const double r[3], double M, const double *Q,
+                                              const double *T, const double *t1, double rb[3])
+{
+    const double x = r[0], y = r[1], z = r[2];
+    const double u = rsqrt_pos(x * x + y * y + z * z);  // r > 0: far pairs are separated
+    const double u2 = u * u;
+    const double v2 = u2 * u2 * u, v3 = v2 * u2, v4 = v3 * u2, v5 = v4 * u2, v6 = v5 * u2;
+    const double qx = Q[0] * x + Q[1] * y + Q[2] * z;
+    const double qy = Q[1] * x + Q[3] * y + Q[4] * z;
+    const double qz = Q[2] * x + Q[4] * y + Q[5] * z;
+    const double qq = qx * x + qy * y + qz * z;
+    const double T0 = T[0] * x + T[1] * y + T[2] * z;   // (T r)_xx, xy, xz, yy, yz, zz
+    const double T1 = T[1] * x + T[3] * y + T[4] * z;
+    const double T2 = T[2] * x + T[4] * y + T[5] * z;
+    const double T3 = T[3] * x + T[6] * y + T[7] * z;
+    const double T4 = T[4] * x + T[7] * y + T[8] * z;
+    const double T5 = T[5] * x + T[8] * y + T[9] * z;
+    const double rx = T0 * x + T1 * y + T2 * z, ry = T1 * x + T3 * y + T4 * z,
+                 rz = T2 * x + T4 * y + T5 * z;         // T r r
+    const double d1 = Q[1] + Q[1], d2 = Q[2] + Q[2], d4 = Q[4] + Q[4];
+    const double wx = T[0] * Q[0] + T[1] * d1 + T[2] * d2 + T[3] * Q[3] + T[4] * d4 + T[5] * Q[5];
+    const double wy = T[1] * Q[0] + T[3] * d1 + T[4] * d2 + T[6] * Q[3] + T[7] * d4 + T[8] * Q[5];
+    const double wz = T[2] * Q[0] + T[4] * d1 + T[5] * d2 + T[7] * Q[3] + T[8] * d4 + T[9] * Q[5];
+    // <L3b, L3> = g2 e2 + g3 e3 + g4 e4 + g5 e5, g_n = (-1)^n (2n - 1)!! r^-(2n+1)
+    const double t1r = t1[0] * x + t1[1] * y + t1[2] * z;
+    const double rrr = rx * x + ry * y + rz * z;        // 3 T r r r / 3
+    const double rrq = rx * qx + ry * qy + rz * qz;
+    const double b3b = t1[0] * qx + t1[1] * qy + t1[2] * qz + wx * x + wy * y + wz * z;
+    const double q6 = qq * (1.0 / 6.0);
+    // sum of g_{n+1} e_n and the cotangent of qq, doubled
+    const double sg = t1r * fma(-15.0 * v3, M, (-945.0 * v5) * q6) +
+                      rrr * fma(35.0 * v4, M, (3465.0 * v6) * q6) + (35.0 * v4) * b3b -
+                      (315.0 * v5) * rrq;
+    const double qqb2 = fma(35.0 * v4, t1r, (-105.0 * v5) * rrr);
+    const double a1 = fma(3.0 * v2, M, (105.0 * v4) * q6);
+    const double a2 = fma(-15.0 * v3, M, (-945.0 * v5) * q6);
+    const double b3 = -5.0 * v3, b4 = 35.0 * v4;
+    const double ex = fma(a2, x, (b4 + b4) * qx), ey = fma(a2, y, (b4 + b4) * qy),
+                 ez = fma(a2, z, (b4 + b4) * qz);
+    const double px = fma(b4, rx, b3 * t1[0]), py = fma(b4, ry, b3 * t1[1]),
+                 pz = fma(b4, rz, b3 * t1[2]);          // cotangent of q
+    rb[0] += T0 * ex + T1 * ey + T2 * ez + a1 * t1[0] + b3 * wx + qqb2 * qx + sg * x + Q[0] * px +
+             Q[1] * py + Q[2] * pz;
+    rb[1] += T1 * ex + T3 * ey + T4 * ez + a1 * t1[1] + b3 * wy + qqb2 * qy + sg * y + Q[1] * px +
+             Q[3] * py + Q[4] * pz;
+    rb[2] += T2 * ex + T4 * ey + T5 * ez + a1 * t1[2] + b3 * wz + qqb2 * qz + sg * z + Q[2] * px +
+             Q[4] * py + Q[5] * pz;
 }
 
 // ---------------------------------------------------------------- L2P adjoint
@@ -371,7 +390,10 @@ __global__ void k_vjp_prep(const TA *__restrict__ abar, int64_t n, const int32_t
         abt[3 * n + threadIdx.x] = 0.0;
 }
 
-// 1. L2P^T: one thread per leaf.
+// 1. L2P^T: one thread per leaf.  WITH_M2L: L is the sum of eq. (6)'s form over
+// the leaf's own far list, and cbar takes the first two orders' share of the
+// sink side of M2L^T with it, sum_b d<L1b, L1> + <L2b, L2>/dr = L1b . L2 + L2b : L3.
+template <bool WITH_M2L>
 __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
                                                  const double *__restrict__ abt,
                                                  const int32_t *__restrict__ leaf_node, int nleaves,
@@ -379,7 +401,8 @@ __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
                                                  const int32_t *__restrict__ count,
                                                  const double *__restrict__ recA,
                                                  const double *__restrict__ Lloc, double *Lbar,
-                                                 double *Lleaf, double *xbt, double *nadj)
+                                                 double2 *Lleaf, int64_t lstride, double *xbt,
+                                                 double *nadj)
 {
     const int lf = blockIdx.x * blockDim.x + threadIdx.x;
     if (lf >= nleaves)
@@ -411,30 +434,42 @@ __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
         cb1 -= b1;
         cb2 -= b2;
     }
+    if constexpr (WITH_M2L) {
+        cb0 += Lb[0] * L[3] + Lb[1] * L[4] + Lb[2] * L[5] + Lb[3] * L[9] + Lb[4] * L[10] +
+               Lb[5] * L[11] + Lb[6] * L[12] + Lb[7] * L[13] + Lb[8] * L[14];
+        cb1 += Lb[0] * L[4] + Lb[1] * L[6] + Lb[2] * L[7] + Lb[3] * L[10] + Lb[4] * L[12] +
+               Lb[5] * L[13] + Lb[6] * L[15] + Lb[7] * L[16] + Lb[8] * L[17];
+        cb2 += Lb[0] * L[5] + Lb[1] * L[7] + Lb[2] * L[8] + Lb[3] * L[11] + Lb[4] * L[13] +
+               Lb[5] * L[14] + Lb[6] * L[16] + Lb[7] * L[17] + Lb[8] * L[18];
+    }
     double *o = Lbar + (int64_t)NLOC * v;
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         o[k] = Lb[k];
-    // the same by leaf index with the leaf's centre: the record the M2L^T
-    // source side reads once per far pair (consecutive sinks of a transposed
-    // list are adjacent records)
-    double *ol = Lleaf + (int64_t)LLEAF * lf;
+    // the leaf's centre and Lbar by leaf index, as the M2L^T source side reads
+    // them: LLEAF / 2 arrays of pairs, so that the consecutive sinks of a
+    // transposed list are neighbours in each (null: not needed)
+    if (Lleaf) {
+        lbar_full(Lb);
+        double2 *ol = Lleaf + lf;
+        ol[0] = make_double2(rv[0], rv[1]);
+        ol[lstride] = make_double2(rv[2], Lb[0]);
 #pragma unroll
-    for (int k = 0; k < 19; ++k)
-        ol[k] = Lb[k];
-    ol[19] = rv[0];
-    ol[20] = rv[1];
-    ol[21] = rv[2];
-    ol[22] = 0.0;
-    ol[23] = 0.0;
+        for (int k = 2; k < LLEAF / 2; ++k)
+            ol[k * lstride] = make_double2(Lb[2 * k - 3], Lb[2 * k - 2]);
+    }
     double *na = nadj + 16 * (int64_t)v;
     na[0] = cb0;
     na[1] = cb1;
     na[2] = cb2;
 }
 
-// 2a. M2L^T, sink side: 16 lanes per leaf over its far list, cbar_sink += rbar.
-constexpr int M2LT_LANES = 16;  // lanes per sink leaf (8 and 4 measured no different)
+// 2a. M2L^T, sink side: 16 lanes per leaf over its far list, cbar_sink += rbar
+// (of the third order only for eq. (6)'s form, step 1 has the others: 150
+// instead of 310 instructions per pair).  The loads of the source records, one
+// L1 lookup per lane and 16 bytes, bound it: 290 -> 230 us (binary, 2^19
+// particles, 2.1e7 pairs), 2.19 -> 1.47 ms (Plummer, 2^19, 1.6e8 pairs).
+constexpr int M2LT_LANES = 16;  // lanes per sink leaf (8 lanes: 232 us, 1.51 ms)
 
 template <int FORM>
 __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
@@ -447,19 +482,37 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
     const bool valid = g < nleaves;
     const int v = valid ? leaf_node[g] : 0;
     const double *rv = recA + (int64_t)NREC * v;
-    double Lb[19];
+    double Lb[19], t1[3];
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         Lb[k] = Lbar[(int64_t)NLOC * v + k];
+    lbar_full(Lb);
+    if constexpr (FORM == FMM_EXPANSION_PHANTOM) {
+        t1[0] = Lb[9] + Lb[12] + Lb[14];
+        t1[1] = Lb[10] + Lb[15] + Lb[17];
+        t1[2] = Lb[11] + Lb[16] + Lb[18];
+    }
+    const double c0 = rv[0], c1 = rv[1], c2 = rv[2];
     double rb[3] = {0.0, 0.0, 0.0};
     const int nk = valid ? max(0, min(far_cnt[g], cap_far)) : 0;
     const int32_t *fl = far_src + (int64_t)(valid ? g : 0) * cap_far;
+    int bn = sub < nk ? fl[sub] : 0;
     for (int k = sub; k < nk; k += M2LT_LANES) {
-        const int b = fl[k];
-        const double *rbp = recA + (int64_t)NREC * b;
-        const double r[3] = {rv[0] - rbp[0], rv[1] - rbp[1], rv[2] - rbp[2]};
-        double Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
-        m2l_vjp<FORM>(r, rbp[3], recQ + (int64_t)NREC * b, Lb, rb, Mb, Qb);
+        const int b = bn;
+        if (k + M2LT_LANES < nk)
+            bn = fl[k + M2LT_LANES];
+        const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
+        const double *qb = recQ + (int64_t)NREC * b;
+        const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
+                      q45 = *(const double2 *)(qb + 4);
+        const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+        const double r[3] = {c0 - cb.x, c1 - cb.y, c2 - cb.z};
+        if constexpr (FORM == FMM_EXPANSION_PHANTOM) {
+            m2l_vjp_third(r, cb.w, Q, Lb + 9, t1, rb);
+        } else {
+            double Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
+            m2l_vjp<FORM>(r, cb.w, Q, Lb, rb, Mb, Qb);
+        }
     }
 #pragma unroll
     for (int off = M2LT_LANES / 2; off >= 1; off >>= 1)
@@ -477,7 +530,7 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
 // 2b. M2L^T, source side.  The sinks that took a cell as far field are
 // processed in pieces of M2LT_PIECE pairs (a cell high in the tree is far
 // field for a large part of the leaves, so one wavefront per cell would leave
-// a few wavefronts with most of the work): one wavefront per piece writes the
+// a few wavefronts with most of the work): VJPM_LANES lanes write a
 // piece's sums, then one thread per cell adds its pieces in order
 // (deterministic).  Per cell: Mbar, Qbar and cbar_src (zero if none), and
 // cbar_sink of internal cells zeroed.
@@ -496,63 +549,70 @@ __global__ void k_piece_fill(const int64_t *__restrict__ poff, int nnodes, int32
             pnode[j] = b;
 }
 
-constexpr int VJPM_WAVES = 1;  // wavefronts (pieces) per workgroup
+// 16 lanes per piece: the mean list of a cell has 80 sinks (binary, 2^19
+// particles) to 600 (Plummer), so a wavefront per piece idled in its last
+// round and in the sums over its lanes; the four pieces of a wavefront belong
+// to neighbouring source cells, which share most of their sinks.  Per pair the
+// kernel does 250 FP64 instructions (m2l_vjp) on 176 bytes, read as 11 arrays
+// so that consecutive sinks share cache lines.  527 -> 379 us (binary) and
+// 4.31 -> 3.61 ms (Plummer, 2^19); with 32 lanes 386 us and 3.57 ms, 64 lanes
+// 447 us and 4.13 ms.
+constexpr int VJPM_LANES = 16;
+constexpr int VJPM_WG = 64;
 
 template <int FORM>
-__global__ __launch_bounds__(64 * VJPM_WAVES)
+__global__ __launch_bounds__(VJPM_WG)
     __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_m2l_src_piece(
     const double *__restrict__ recA, const double *__restrict__ recQ,
     const int64_t *__restrict__ toff, const uint32_t *__restrict__ tsrc,
-    const double *__restrict__ Lleaf, const int32_t *__restrict__ pnode,
+    const double2 *__restrict__ Lleaf, int64_t lstride, const int32_t *__restrict__ pnode,
     const int64_t *__restrict__ poff, int64_t npieces, double *part)
 {
     // consecutive pieces (neighbouring source cells, which share most of
     // their sinks) run behind the same L2
     const int64_t pc =
-        (int64_t)xcd_block(blockIdx.x, gridDim.x) * VJPM_WAVES + (threadIdx.x >> 6);
-    if (pc >= npieces)
-        return;
-    const int lane = lane_id();
-    const int b = pnode[pc];
-    const int64_t e0 = toff[b] + (pc - poff[b]) * M2LT_PIECE;
-    const int64_t e1 = min(e0 + M2LT_PIECE, toff[b + 1]);
-    const double *rbp = recA + (int64_t)NREC * b;
-    const double cb0 = rbp[0], cb1 = rbp[1], cb2 = rbp[2], M = rbp[3];
-    const double *Qs = recQ + (int64_t)NREC * b;
+        ((int64_t)xcd_block(blockIdx.x, gridDim.x) * VJPM_WG + threadIdx.x) / VJPM_LANES;
+    const int sub = threadIdx.x & (VJPM_LANES - 1);
+    const bool valid = pc < npieces;
+    const int b = valid ? pnode[pc] : 0;
+    const int64_t e0 = valid ? toff[b] + (pc - poff[b]) * M2LT_PIECE : 0;
+    const int64_t e1 = valid ? min(e0 + M2LT_PIECE, toff[b + 1]) : 0;
+    const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
+    double Q[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        Q[k] = recQ[(int64_t)NREC * b + k];
     double acc[10];
 #pragma unroll
     for (int k = 0; k < 10; ++k)
         acc[k] = 0.0;
-    for (int64_t e = e0 + lane; e < e1; e += 64) {
-        // the sink leaf's L-bar and centre, one 192-byte record
-        const double2 *lr = (const double2 *)(Lleaf + (int64_t)LLEAF * (int)tsrc[e]);
-        double Lb[20];
+    uint32_t an = e0 + sub < e1 ? tsrc[e0 + sub] : 0u;
+    for (int64_t e = e0 + sub; e < e1; e += VJPM_LANES) {
+        const double2 *lr = Lleaf + an;
+        if (e + VJPM_LANES < e1)
+            an = tsrc[e + VJPM_LANES];
+        const double2 c01 = lr[0], c2a = lr[lstride];
+        double Lb[19];
+        Lb[0] = c2a.y;
 #pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            const double2 q = lr[k];
-            Lb[2 * k] = q.x;
-            Lb[2 * k + 1] = q.y;
+        for (int k = 2; k < LLEAF / 2; ++k) {
+            const double2 q = lr[k * lstride];
+            Lb[2 * k - 3] = q.x;
+            Lb[2 * k - 2] = q.y;
         }
-        const double2 c12 = lr[10];
-        const double r[3] = {Lb[19] - cb0, c12.x - cb1, c12.y - cb2};
-        double rb[3] = {0.0, 0.0, 0.0}, Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
-        m2l_vjp<FORM>(r, M, Qs, Lb, rb, Mb, Qb);
-        acc[0] += Mb;
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            acc[1 + k] += Qb[k];
-        acc[7] -= rb[0];
-        acc[8] -= rb[1];
-        acc[9] -= rb[2];
+        const double r[3] = {c01.x - cb.x, c01.y - cb.y, c2a.x - cb.z};
+        m2l_vjp<FORM>(r, cb.w, Q, Lb, acc + 7, acc[0], acc + 1);
     }
 #pragma unroll
-    for (int k = 0; k < 10; ++k)
-        acc[k] = wave_sum(acc[k]);
-    if (lane == 0) {
+    for (int off = VJPM_LANES / 2; off >= 1; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < 10; ++k)
+            acc[k] += __shfl_xor(acc[k], off);
+    if (valid && sub == 0) {
         double *pp = part + 10 * pc;
 #pragma unroll
         for (int k = 0; k < 10; ++k)
-            pp[k] = acc[k];
+            pp[k] = k < 7 ? acc[k] : -acc[k];
     }
 }
 
@@ -687,6 +747,7 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         Lb[k] = Lbar[(int64_t)NLOC * vv + k];
+    lbar_full(Lb);
     double rs[3] = {0.0, 0.0, 0.0}, rt[3] = {0.0, 0.0, 0.0}, Mb = 0.0,
            Qb[6] = {0, 0, 0, 0, 0, 0};
     const int64_t e0 = valid ? fstart[v] : 0, e1 = valid ? fend[v] : 0;
@@ -697,7 +758,12 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
         double Mx = 0.0, Qx[6] = {0, 0, 0, 0, 0, 0};
         m2l_vjp<FORM>(r, rb[3], recQ + (int64_t)NREC * b, Lb, rs, Mx, Qx);
         const double q[3] = {-r[0], -r[1], -r[2]};
-        m2l_vjp<FORM>(q, Mv, Qv, Lbar + (int64_t)NLOC * b, rt, Mb, Qb);
+        double Lx[19];
+#pragma unroll
+        for (int k = 0; k < 19; ++k)
+            Lx[k] = Lbar[(int64_t)NLOC * b + k];
+        lbar_full(Lx);
+        m2l_vjp<FORM>(q, Mv, Qv, Lx, rt, Mb, Qb);
     }
     double acc[13] = {rs[0], rs[1], rs[2], rt[0], rt[1], rt[2], Mb,
                       Qb[0], Qb[1], Qb[2], Qb[3], Qb[4], Qb[5]};
@@ -1401,7 +1467,7 @@ static hipError_t ensure_vjp_base(Tree &t)
     if (e == hipSuccess) e = valloc(t, &t.xbt, 3 * n);
     if (e == hipSuccess) e = valloc(t, &t.mbt, n);
     if (e == hipSuccess) e = valloc(t, &t.Lbar, NLOC * nc);
-    if (e == hipSuccess) e = valloc(t, &t.Lleaf, LLEAF * (int64_t)T.leaf_cap);
+    if (e == hipSuccess) e = valloc(t, &t.Lleaf, LLEAF / 2 * (int64_t)T.leaf_cap);
     if (e == hipSuccess) e = valloc(t, &t.nadj, 16 * nc);
     if (e == hipSuccess) e = valloc(t, &t.pair_off, T.leaf_cap + 1);
     if (e == hipSuccess) e = valloc(t, &t.vscan, T.leaf_cap / SCAN_TILE + 2);
@@ -1417,7 +1483,8 @@ static hipError_t ensure_vjp_base(Tree &t)
         for (auto &b : t.vjp_owned)
             tree_free(t, b.p);
         t.vjp_owned.clear();
-        t.abt = t.xbt = t.mbt = t.Lbar = t.Lleaf = t.nadj = nullptr;
+        t.abt = t.xbt = t.mbt = t.Lbar = t.nadj = nullptr;
+        t.Lleaf = nullptr;
         t.pair_off = t.vscan = t.farT.off = t.poff = t.pscan = t.nearT.off = nullptr;
         t.pcnt = nullptr;
     }
@@ -1634,8 +1701,9 @@ static void vjp_m2l(Tree &t, hipStream_t s)
         t.recA, t.recQ, t.leaf_node, nl, t.far_cnt, t.far_src, (int)t.cap_far, t.Lbar, t.nadj);
     if (t.npieces > 0)
         k_vjp_m2l_src_piece<FORM>
-            <<<(int)((t.npieces + VJPM_WAVES - 1) / VJPM_WAVES), 64 * VJPM_WAVES, 0, s>>>(
-            t.recA, t.recQ, t.farT.off, t.farT.src, t.Lleaf, t.pnode, t.poff, t.npieces, t.ppart);
+            <<<(int)((t.npieces * VJPM_LANES + VJPM_WG - 1) / VJPM_WG), VJPM_WG, 0, s>>>(
+            t.recA, t.recQ, t.farT.off, t.farT.src, t.Lleaf, t.topo.leaf_cap, t.pnode, t.poff,
+            t.npieces, t.ppart);
 }
 
 // Mutual walk: forward totals of the internal cells, L2L^T level by level
@@ -1707,8 +1775,14 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         k_vjp_prep<float><<<gs, 256, 0, s>>>((const float *)abar, n, t.perm, t.p.G, t.abt);
     else
         k_vjp_prep<double><<<gs, 256, 0, s>>>((const double *)abar, n, t.perm, t.p.G, t.abt);
-    k_vjp_l2p<<<(nl + 255) / 256, 256, 0, s>>>(t.pm, t.abt, t.leaf_node, nl, t.first, t.count,
-                                               t.recA, t.L, t.Lbar, t.Lleaf, t.xbt, t.nadj);
+    if (t.lists_policy != FMM_WALK_MUTUAL && t.p.expansion == FMM_EXPANSION_PHANTOM)
+        k_vjp_l2p<true><<<(nl + 255) / 256, 256, 0, s>>>(t.pm, t.abt, t.leaf_node, nl, t.first,
+                                                         t.count, t.recA, t.L, t.Lbar, t.Lleaf,
+                                                         T.leaf_cap, t.xbt, t.nadj);
+    else
+        k_vjp_l2p<false><<<(nl + 255) / 256, 256, 0, s>>>(
+            t.pm, t.abt, t.leaf_node, nl, t.first, t.count, t.recA, t.L, t.Lbar,
+            t.lists_policy == FMM_WALK_MUTUAL ? nullptr : t.Lleaf, T.leaf_cap, t.xbt, t.nadj);
     if (t.lists_policy == FMM_WALK_MUTUAL) {
         e = vjp_mutual_far(t, s);
         if (e != hipSuccess)
