@@ -325,6 +325,10 @@ struct Tree {
     int32_t *pnode = nullptr;      // cell of each piece
     double *ppart = nullptr;       // 10 sums per piece
     int64_t npieces = 0, piece_cap = 0;
+    // the pieces in the order of their sinks (m2lt_sorted): sort buffers, result
+    uint32_t *pkey = nullptr, *pkey1 = nullptr, *pid = nullptr, *porder = nullptr,
+             *phist = nullptr;
+    int64_t porder_cap = 0;
 
     MutualLists mw;
     int64_t mw_init_cap = 0;        // test hook: FMM_MI355_MW_CAP sets small first capacities

@@ -339,7 +339,10 @@ __device__ __forceinline__ void m2l_src_eval(const M2lSrc32 &S, double c0, doubl
 // by k_m2l_fold), with bit-identical totals either way.
 constexpr int M2L_LANES = 8;  // lanes per unit
 
-template <typename T, int FORM>
+// REGROUP: FP64 sums in the grouping of M2lSum64 (eq. (6)'s form).  The FP64
+// expansions that the reverse pass of FP32 trees forms keep the plain order:
+// its results, rounded to FP32, stay the same to the bit.
+template <typename T, int FORM, bool REGROUP>
 __global__ __launch_bounds__(256) void k_m2l_leaf(
     const double *__restrict__ recA, const double *__restrict__ recQ,
     const float *__restrict__ recF, const int32_t *__restrict__ leaf_node, int nunits,
@@ -395,7 +398,7 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
         } else {
             // the next source's index is loaded one interaction ahead
             [[maybe_unused]] M2lSum64 S;
-            if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+            if constexpr (REGROUP)
                 S.clear();
             int bn = p0 + sub < p1 ? fl[p0 + sub] : 0;
             for (int k = p0 + sub; k < p1; k += M2L_LANES) {
@@ -407,12 +410,12 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
                 const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
                               q45 = *(const double2 *)(qb + 4);
                 const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
-                if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+                if constexpr (REGROUP)
                     S.add(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q);
                 else
                     m2l_acc<double, FORM>(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q, L);
             }
-            if constexpr (FORM == FMM_EXPANSION_PHANTOM)
+            if constexpr (REGROUP)
                 S.total(L);
         }
 #pragma unroll
@@ -1463,16 +1466,21 @@ static void far_leaf(Tree &t, bool fp64, hipStream_t s)
     const int per = (int)t.far_piece_entries;
     const int extra = pc ? nu - nl : 0;
     if (fp64) {
-        k_m2l_leaf<double, FORM><<<g, 256, 0, s>>>(t.recA, t.recQ, t.recF, t.leaf_node, nu,
-                                                   t.far_cnt, t.far_src, (int)t.cap_far, t.L, pl,
-                                                   per, (double *)t.pfar.part);
+        auto run = [&](auto kernel) {
+            kernel<<<g, 256, 0, s>>>(t.recA, t.recQ, t.recF, t.leaf_node, nu, t.far_cnt, t.far_src,
+                                     (int)t.cap_far, t.L, pl, per, (double *)t.pfar.part);
+        };
+        if (FORM == FMM_EXPANSION_PHANTOM && t.p.precision != FMM_FP32)
+            run(k_m2l_leaf<double, FORM, FORM == FMM_EXPANSION_PHANTOM>);
+        else
+            run(k_m2l_leaf<double, FORM, false>);
         if (extra > 0)
             k_m2l_fold<double><<<(extra + 255) / 256, 256, 0, s>>>(
                 t.leaf_node, t.pfar.off, t.pfar.list, extra, (const double *)t.pfar.part, t.L);
     } else {
-        k_m2l_leaf<float, FORM><<<g, 256, 0, s>>>(t.recA, t.recQ, t.recF, t.leaf_node, nu,
-                                                  t.far_cnt, t.far_src, (int)t.cap_far, t.Lf, pl,
-                                                  per, (float *)t.pfar.part);
+        k_m2l_leaf<float, FORM, false><<<g, 256, 0, s>>>(
+            t.recA, t.recQ, t.recF, t.leaf_node, nu, t.far_cnt, t.far_src, (int)t.cap_far, t.Lf,
+            pl, per, (float *)t.pfar.part);
         if (extra > 0)
             k_m2l_fold<float><<<(extra + 255) / 256, 256, 0, s>>>(
                 t.leaf_node, t.pfar.off, t.pfar.list, extra, (const float *)t.pfar.part, t.Lf);

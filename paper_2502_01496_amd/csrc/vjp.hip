@@ -33,6 +33,10 @@
 // of every cell in one pass over its own pairs (section 2c below).
 // Every accumulator has exactly one owning thread (no floating-point
 // atomics), so the result is bitwise reproducible.  The arithmetic is FP64.
+// The results of FP32 trees are these sums rounded to FP32, where any other
+// order of additions shows as a unit in the last place here and there; they
+// are kept to the bit, so the far field's kernels have the plain sums for FP32
+// trees (F32 = true) beside the regrouped ones, and both share the layout.
 #include "fmm_internal.h"
 
 namespace fmm {
@@ -54,6 +58,11 @@ __device__ __forceinline__ constexpr int sym3(int i, int j, int k)
     const int c = hi > k ? hi : k;
     const int b = i + j + k - a - c;
     return a == 0 ? (b == 0 ? c : (b == 1 ? 2 + c : 5)) : (a == 1 ? (b == 1 ? 5 + c : 8) : 9);
+}
+
+__device__ __forceinline__ constexpr double mult3(int i, int j, int k)
+{
+    return (i == j && j == k) ? 1.0 : ((i == j || j == k || i == k) ? 3.0 : 6.0);
 }
 
 // Stored cotangent of a local expansion -> the form that the M2L adjoint
@@ -102,7 +111,7 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            B[i][j] = Lb[3 + sym2(i, j)];
+            B[i][j] = Lb[3 + sym2(i, j)] * (i == j ? 1.0 : 0.5);
     double T[3][3][3];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -110,7 +119,7 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 3; ++k)
-                T[i][j][k] = Lb[9 + sym3(i, j, k)] * k3;
+                T[i][j][k] = Lb[9 + sym3(i, j, k)] * (1.0 / mult3(i, j, k));
     double Br[3], tr1[3], Trr[3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
@@ -155,26 +164,148 @@ __device__ __forceinline__ void m2l_vjp_dehnen(const double r[3], double M, cons
             Qb[sym2(i, j)] += i == j ? qb[i] * r[i] : qb[i] * r[j] + qb[j] * r[i];
 }
 
-// Given the cotangent Lb[19] (lbar_full) of one M2L term K(r; M, Q),
-// accumulate d<Lb, K>/dr into rb, d/dM into Mb and d/dQ (stored entries) into
+// Given the stored cotangent Lb[19] of one M2L term K(r; M, Q), accumulate
+// d<Lb, K>/dr into rb, d/dM into Mb and d/dQ (stored entries) into Qb.
+// Eq. (6)'s form, in the plain order of its terms.
+__device__ __forceinline__ void m2l_vjp_plain(const double r[3], double M, const double *Qs,
+                                              const double *Lb, double rb[3], double &Mb,
+                                              double Qb[6])
+{
+    const double r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+    const double u = rsqrt_pos(r2);  // r2 > 0: far pairs are separated
+    const double u2 = u * u;
+    const double g1 = -u * u2, g2 = -3.0 * g1 * u2, g3 = -5.0 * g2 * u2, g4 = -7.0 * g3 * u2,
+                 g5 = -9.0 * g4 * u2, g6 = -11.0 * g5 * u2;
+    double Qf[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            Qf[i][j] = Qs[sym2(i, j)];
+    double q[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        q[i] = Qf[i][0] * r[0] + Qf[i][1] * r[1] + Qf[i][2] * r[2];
+    const double qq = q[0] * r[0] + q[1] * r[1] + q[2] * r[2];
+    // divisions by the constants 3 and 6 are taken as products with their
+    // rounded reciprocals (no FP64 divide in the loop)
+    constexpr double k3 = 1.0 / 3.0, k6 = 1.0 / 6.0;
+    const double qq6 = qq * k6;
+    const double a0 = M * g1 + g3 * qq6, a1 = M * g2 + g4 * qq6, a2 = M * g3 + g5 * qq6;
+    const double b2 = g2 * k3, b3 = g3 * k3, b4 = g4 * k3;
+    // full symmetric cotangent tensors
+    const double A[3] = {Lb[0], Lb[1], Lb[2]};
+    double B[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            B[i][j] = Lb[3 + sym2(i, j)] * (i == j ? 1.0 : 0.5);
+    double T[3][3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                T[i][j][k] = Lb[9 + sym3(i, j, k)] * (1.0 / mult3(i, j, k));
+    // contractions
+    double Br[3], Bq[3], tr1[3], Trr[3], Trq[3], TQ[3], Tr[3][3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        Br[m] = B[m][0] * r[0] + B[m][1] * r[1] + B[m][2] * r[2];
+        Bq[m] = B[m][0] * q[0] + B[m][1] * q[1] + B[m][2] * q[2];
+        tr1[m] = T[0][0][m] + T[1][1][m] + T[2][2][m];
+        double s_rr = 0.0, s_rq = 0.0, s_Q = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                s_rr += T[i][j][m] * r[i] * r[j];
+                s_rq += T[i][j][m] * r[i] * q[j];
+                s_Q += T[m][i][j] * Qf[i][j];
+            }
+        Trr[m] = s_rr;
+        Trq[m] = s_rq;
+        TQ[m] = s_Q;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            Tr[m][k] = T[0][m][k] * r[0] + T[1][m][k] * r[1] + T[2][m][k] * r[2];
+    }
+    const double Ar = A[0] * r[0] + A[1] * r[1] + A[2] * r[2];
+    const double Aq = A[0] * q[0] + A[1] * q[1] + A[2] * q[2];
+    const double trB = B[0][0] + B[1][1] + B[2][2];
+    const double Brr = Br[0] * r[0] + Br[1] * r[1] + Br[2] * r[2];
+    const double Brq = Bq[0] * r[0] + Bq[1] * r[1] + Bq[2] * r[2];
+    double BQ = 0.0, TrQ = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            BQ += B[i][j] * Qf[i][j];
+            TrQ += Tr[i][j] * Qf[i][j];
+        }
+    const double tr1r = tr1[0] * r[0] + tr1[1] * r[1] + tr1[2] * r[2];
+    const double tr1q = tr1[0] * q[0] + tr1[1] * q[1] + tr1[2] * q[2];
+    const double Trrr = Trr[0] * r[0] + Trr[1] * r[1] + Trr[2] * r[2];
+    const double Trrq = Trr[0] * q[0] + Trr[1] * q[1] + Trr[2] * q[2];
+    // cotangents of the scalar coefficients
+    const double a0b = Ar + trB;
+    const double a1b = Brr + 3.0 * tr1r;
+    const double a2b = Trrr;
+    const double b2b = Aq + BQ;
+    const double b3b = 2.0 * Brq + 3.0 * tr1q + 3.0 * TrQ;
+    const double b4b = 3.0 * Trrq;
+    // explicit dependence on r, q, Q
+    double rbl[3], qb[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        rbl[m] = a0 * A[m] + 2.0 * a1 * Br[m] + 2.0 * b3 * Bq[m] + 3.0 * a2 * Trr[m] +
+                 3.0 * a1 * tr1[m] + 6.0 * b4 * Trq[m] + 3.0 * b3 * TQ[m];
+        qb[m] = b2 * A[m] + 2.0 * b3 * Br[m] + 3.0 * b4 * Trr[m] + 3.0 * b3 * tr1[m];
+    }
+    // through the coefficients
+    Mb += a0b * g1 + a1b * g2 + a2b * g3;
+    const double qqb = (a0b * g3 + a1b * g4 + a2b * g5) * k6;
+    const double gb1 = a0b * M;
+    const double gb2 = a1b * M + b2b * k3;
+    const double gb3 = a2b * M + a0b * qq6 + b3b * k3;
+    const double gb4 = a1b * qq6 + b4b * k3;
+    const double gb5 = a2b * qq6;
+    const double sg = gb1 * g2 + gb2 * g3 + gb3 * g4 + gb4 * g5 + gb5 * g6;
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        qb[m] += qqb * r[m];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        rb[m] += rbl[m] + qqb * q[m] + (qb[0] * Qf[0][m] + qb[1] * Qf[1][m] + qb[2] * Qf[2][m]) +
+                 sg * r[m];
+    // stored quadrupole entries: explicit symmetric part + q = Qf r
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) {
+            const double ex = b2 * B[i][j] + 3.0 * b3 * Tr[i][j];
+            if (i == j)
+                Qb[sym2(i, j)] += ex + qb[i] * r[i];
+            else
+                Qb[sym2(i, j)] += 2.0 * ex + qb[i] * r[j] + qb[j] * r[i];
+        }
+}
+
+// The same regrouped.  Given the cotangent Lb[19] (lbar_full) of one M2L term
+// K(r; M, Q), accumulate d<Lb, K>/dr into rb, d/dM into Mb and d/dQ (stored entries) into
 // Qb.  With A, B, T the three orders of Lb, E = <Lb, K> is
 //   g1 M e0 + g2 (M e1 + f2 / 3) + g3 (M e2 + qq/6 e0 + f3 / 3) + g4 (qq/6 e1 + f4 / 3)
 //   + g5 qq/6 e2,
 //   e0 = A.r + tr B, e1 = B:rr + t1.r, e2 = T:rrr / 3, f2 = A.q + B:Q,
 //   f3 = 2 B:rq + t1.q + (T:Q).r, f4 = T:rrq,
 // t1 the trace of T, and its derivative takes two products with the matrices
-// B and T r (w1 and w2 below): 250 instructions.
-// FORM = FMM_EXPANSION_DEHNEN: K's second and third orders come from the
-// monopole alone (A0 = M g1, A1 = M g2, A2 = M g3 in place of a0, a1, a2 and
-// no b3, b4 terms), so the quadrupole is reached through L1 only.
-template <int FORM>
-__device__ __forceinline__ void m2l_vjp(const double r[3], double M, const double *Q,
-                                        const double *Lb, double rb[3], double &Mb, double Qb[6])
+// B and T r (w1 and w2 below): 250 instructions instead of 400.
+__device__ __forceinline__ void m2l_vjp_regrouped(const double r[3], double M, const double *Q,
+                                                  const double *Lb, double rb[3], double &Mb,
+                                                  double Qb[6])
 {
-    if constexpr (FORM == FMM_EXPANSION_DEHNEN) {
-        m2l_vjp_dehnen(r, M, Q, Lb, rb, Mb, Qb);
-        return;
-    }
     const double x = r[0], y = r[1], z = r[2];
     const double *A = Lb, *B = Lb + 3, *T = Lb + 9;
     const double u = rsqrt_pos(x * x + y * y + z * z);  // r > 0: far pairs are separated
@@ -242,6 +373,27 @@ __device__ __forceinline__ void m2l_vjp(const double r[3], double M, const doubl
     Qb[3] = fma(sy, y, fma(b3, T3, fma(v2, B[3], Qb[3])));
     Qb[4] = fma(sy, z, fma(sz, y, fma(bb, T4, fma(v22, B[4], Qb[4]))));
     Qb[5] = fma(sz, z, fma(b3, T5, fma(v2, B[5], Qb[5])));
+}
+
+// Whether the kernels of an expansion and a precision read Lb as lbar_full
+// gives it and sum the terms regrouped.
+template <int FORM, bool F32>
+constexpr bool vjp_regrouped = FORM == FMM_EXPANSION_PHANTOM && !F32;
+
+// One M2L term's adjoint.  FORM = FMM_EXPANSION_DEHNEN: K's second and third
+// orders come from the monopole alone (A0 = M g1, A1 = M g2, A2 = M g3 in
+// place of a0, a1, a2 and no b3, b4 terms), so the quadrupole is reached
+// through L1 only.
+template <int FORM, bool F32>
+__device__ __forceinline__ void m2l_vjp(const double r[3], double M, const double *Q,
+                                        const double *Lb, double rb[3], double &Mb, double Qb[6])
+{
+    if constexpr (FORM == FMM_EXPANSION_DEHNEN)
+        m2l_vjp_dehnen(r, M, Q, Lb, rb, Mb, Qb);
+    else if constexpr (F32)
+        m2l_vjp_plain(r, M, Q, Lb, rb, Mb, Qb);
+    else
+        m2l_vjp_regrouped(r, M, Q, Lb, rb, Mb, Qb);
 }
 
 // Sink side of eq. (6)'s form: d<L3b, K's third order>/dr of one M2L term,
@@ -390,8 +542,8 @@ __global__ void k_vjp_prep(const TA *__restrict__ abar, int64_t n, const int32_t
         abt[3 * n + threadIdx.x] = 0.0;
 }
 
-// 1. L2P^T: one thread per leaf.  WITH_M2L: L is the sum of eq. (6)'s form over
-// the leaf's own far list, and cbar takes the first two orders' share of the
+// 1. L2P^T: one thread per leaf.  WITH_M2L (regrouped sums, leaf <- cell lists):
+// L is the sum of eq. (6)'s form over the leaf's own far list, and cbar takes the first two orders' share of the
 // sink side of M2L^T with it, sum_b d<L1b, L1> + <L2b, L2>/dr = L1b . L2 + L2b : L3.
 template <bool WITH_M2L>
 __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
@@ -450,7 +602,8 @@ __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
     // them: LLEAF / 2 arrays of pairs, so that the consecutive sinks of a
     // transposed list are neighbours in each (null: not needed)
     if (Lleaf) {
-        lbar_full(Lb);
+        if constexpr (WITH_M2L)
+            lbar_full(Lb);
         double2 *ol = Lleaf + lf;
         ol[0] = make_double2(rv[0], rv[1]);
         ol[lstride] = make_double2(rv[2], Lb[0]);
@@ -471,7 +624,7 @@ __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
 // particles, 2.1e7 pairs), 2.19 -> 1.47 ms (Plummer, 2^19, 1.6e8 pairs).
 constexpr int M2LT_LANES = 16;  // lanes per sink leaf (8 lanes: 232 us, 1.51 ms)
 
-template <int FORM>
+template <int FORM, bool F32>
 __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
     const double *__restrict__ recA, const double *__restrict__ recQ,
     const int32_t *__restrict__ leaf_node, int nleaves, const int32_t *__restrict__ far_cnt,
@@ -482,12 +635,13 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
     const bool valid = g < nleaves;
     const int v = valid ? leaf_node[g] : 0;
     const double *rv = recA + (int64_t)NREC * v;
-    double Lb[19], t1[3];
+    double Lb[19];
+    [[maybe_unused]] double t1[3];
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         Lb[k] = Lbar[(int64_t)NLOC * v + k];
-    lbar_full(Lb);
-    if constexpr (FORM == FMM_EXPANSION_PHANTOM) {
+    if constexpr (vjp_regrouped<FORM, F32>) {
+        lbar_full(Lb);
         t1[0] = Lb[9] + Lb[12] + Lb[14];
         t1[1] = Lb[10] + Lb[15] + Lb[17];
         t1[2] = Lb[11] + Lb[16] + Lb[18];
@@ -507,11 +661,11 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
                       q45 = *(const double2 *)(qb + 4);
         const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
         const double r[3] = {c0 - cb.x, c1 - cb.y, c2 - cb.z};
-        if constexpr (FORM == FMM_EXPANSION_PHANTOM) {
+        if constexpr (vjp_regrouped<FORM, F32>) {
             m2l_vjp_third(r, cb.w, Q, Lb + 9, t1, rb);
         } else {
             double Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
-            m2l_vjp<FORM>(r, cb.w, Q, Lb, rb, Mb, Qb);
+            m2l_vjp<FORM, F32>(r, cb.w, Q, Lb, rb, Mb, Qb);
         }
     }
 #pragma unroll
@@ -530,7 +684,7 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
 // 2b. M2L^T, source side.  The sinks that took a cell as far field are
 // processed in pieces of M2LT_PIECE pairs (a cell high in the tree is far
 // field for a large part of the leaves, so one wavefront per cell would leave
-// a few wavefronts with most of the work): VJPM_LANES lanes write a
+// a few wavefronts with most of the work): vjpm_lanes lanes write a
 // piece's sums, then one thread per cell adds its pieces in order
 // (deterministic).  Per cell: Mbar, Qbar and cbar_src (zero if none), and
 // cbar_sink of internal cells zeroed.
@@ -549,32 +703,54 @@ __global__ void k_piece_fill(const int64_t *__restrict__ poff, int nnodes, int32
             pnode[j] = b;
 }
 
-// 16 lanes per piece: the mean list of a cell has 80 sinks (binary, 2^19
-// particles) to 600 (Plummer), so a wavefront per piece idled in its last
-// round and in the sums over its lanes; the four pieces of a wavefront belong
-// to neighbouring source cells, which share most of their sinks.  Per pair the
-// kernel does 250 FP64 instructions (m2l_vjp) on 176 bytes, read as 11 arrays
-// so that consecutive sinks share cache lines.  527 -> 379 us (binary) and
-// 4.31 -> 3.61 ms (Plummer, 2^19); with 32 lanes 386 us and 3.57 ms, 64 lanes
-// 447 us and 4.13 ms.
-constexpr int VJPM_LANES = 16;
-constexpr int VJPM_WG = 64;
+// Sort keys of the pieces: the first sink leaf >> kshift, and the piece's number.
+__global__ void k_piece_keys(const int32_t *__restrict__ pnode, const int64_t *__restrict__ poff,
+                             int64_t npieces, const int64_t *__restrict__ toff,
+                             const uint32_t *__restrict__ tsrc, int kshift, uint32_t *pkey,
+                             uint32_t *pid)
+{
+    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (j >= npieces)
+        return;
+    const int b = pnode[j];
+    pkey[j] = tsrc[toff[b] + (j - poff[b]) * M2LT_PIECE] >> kshift;
+    pid[j] = (uint32_t)j;
+}
 
-template <int FORM>
-__global__ __launch_bounds__(VJPM_WG)
+// Lanes per piece.  The mean list of a cell has 80 sinks (binary, 2^19
+// particles) to 600 (Plummer), so a wavefront per piece idles in its last
+// round and in the sums over its lanes; 16 lanes give four pieces to a
+// wavefront, of neighbouring cells, which share most of their sinks (FP32
+// trees: 64 lanes, the order of the sums).  A pair costs 250 FP64 instructions
+// (regrouped) on 176 bytes, read as 11 arrays so that consecutive sinks share
+// cache lines.  Records of 192 bytes, 64 lanes and the plain sums took 527 us
+// (binary) and 4.31 ms (Plummer, 2^19), this 371 us and 3.61 ms (1.99 ms in
+// the order of the sinks, below; for FP32 trees, with the plain sums, 3.22 ms);
+// 32 lanes 386 us and 3.57 ms.
+constexpr int vjpm_lanes(bool f32) { return f32 ? 64 : 16; }
+
+template <int FORM, bool F32>
+__global__ __launch_bounds__(64)
     __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_m2l_src_piece(
     const double *__restrict__ recA, const double *__restrict__ recQ,
     const int64_t *__restrict__ toff, const uint32_t *__restrict__ tsrc,
     const double2 *__restrict__ Lleaf, int64_t lstride, const int32_t *__restrict__ pnode,
-    const int64_t *__restrict__ poff, int64_t npieces, double *part)
+    const int64_t *__restrict__ poff, const uint32_t *__restrict__ order, int64_t npieces,
+    double *part)
 {
-    // consecutive pieces (neighbouring source cells, which share most of
-    // their sinks) run behind the same L2
-    const int64_t pc =
-        ((int64_t)xcd_block(blockIdx.x, gridDim.x) * VJPM_WG + threadIdx.x) / VJPM_LANES;
-    const int sub = threadIdx.x & (VJPM_LANES - 1);
-    const bool valid = pc < npieces;
-    const int b = valid ? pnode[pc] : 0;
+    constexpr int LANES = vjpm_lanes(F32);
+    // consecutive pieces (neighbouring source cells, or neighbouring sinks
+    // with order != null) run behind the same L2
+    const int64_t pi =
+        (int64_t)xcd_block(blockIdx.x, gridDim.x) * (64 / LANES) + threadIdx.x / LANES;
+    const int sub = threadIdx.x & (LANES - 1);
+    const bool valid = pi < npieces;
+    int pc = valid && order ? (int)order[pi] : (int)pi;
+    if constexpr (LANES == 64)
+        pc = __builtin_amdgcn_readfirstlane(pc);  // the cell's data in scalar registers
+    int b = valid ? pnode[pc] : 0;
+    if constexpr (LANES == 64)
+        b = __builtin_amdgcn_readfirstlane(b);
     const int64_t e0 = valid ? toff[b] + (pc - poff[b]) * M2LT_PIECE : 0;
     const int64_t e1 = valid ? min(e0 + M2LT_PIECE, toff[b + 1]) : 0;
     const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
@@ -586,11 +762,8 @@ __global__ __launch_bounds__(VJPM_WG)
 #pragma unroll
     for (int k = 0; k < 10; ++k)
         acc[k] = 0.0;
-    uint32_t an = e0 + sub < e1 ? tsrc[e0 + sub] : 0u;
-    for (int64_t e = e0 + sub; e < e1; e += VJPM_LANES) {
-        const double2 *lr = Lleaf + an;
-        if (e + VJPM_LANES < e1)
-            an = tsrc[e + VJPM_LANES];
+    for (int64_t e = e0 + sub; e < e1; e += LANES) {
+        const double2 *lr = Lleaf + tsrc[e];
         const double2 c01 = lr[0], c2a = lr[lstride];
         double Lb[19];
         Lb[0] = c2a.y;
@@ -601,15 +774,27 @@ __global__ __launch_bounds__(VJPM_WG)
             Lb[2 * k - 2] = q.y;
         }
         const double r[3] = {c01.x - cb.x, c01.y - cb.y, c2a.x - cb.z};
-        m2l_vjp<FORM>(r, cb.w, Q, Lb, acc + 7, acc[0], acc + 1);
+        if constexpr (vjp_regrouped<FORM, F32>) {
+            m2l_vjp<FORM, F32>(r, cb.w, Q, Lb, acc + 7, acc[0], acc + 1);
+        } else {
+            double rb[3] = {0.0, 0.0, 0.0}, Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
+            m2l_vjp<FORM, F32>(r, cb.w, Q, Lb, rb, Mb, Qb);
+            acc[0] += Mb;
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                acc[1 + k] += Qb[k];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                acc[7 + k] += rb[k];
+        }
     }
 #pragma unroll
-    for (int off = VJPM_LANES / 2; off >= 1; off >>= 1)
+    for (int off = LANES / 2; off >= 1; off >>= 1)
 #pragma unroll
         for (int k = 0; k < 10; ++k)
             acc[k] += __shfl_xor(acc[k], off);
     if (valid && sub == 0) {
-        double *pp = part + 10 * pc;
+        double *pp = part + 10 * (int64_t)pc;
 #pragma unroll
         for (int k = 0; k < 10; ++k)
             pp[k] = k < 7 ? acc[k] : -acc[k];
@@ -729,7 +914,7 @@ __global__ __launch_bounds__(256) void k_vjp_l2l_level(const int32_t *__restrict
 // pass over the CSR range of v does both sides: cbar_v += rbar of (v <- b)
 // with Lbar_v, and Mbar_v, Qbar_v, cbar_v -= rbar of (b <- v) with Lbar_b.
 // 16 lanes per cell, all cells.
-template <int FORM>
+template <int FORM, bool F32>
 __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
     const double *__restrict__ recA, const double *__restrict__ recQ, int nnodes,
     const int64_t *__restrict__ fstart, const int64_t *__restrict__ fend,
@@ -747,7 +932,8 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         Lb[k] = Lbar[(int64_t)NLOC * vv + k];
-    lbar_full(Lb);
+    if constexpr (vjp_regrouped<FORM, F32>)
+        lbar_full(Lb);
     double rs[3] = {0.0, 0.0, 0.0}, rt[3] = {0.0, 0.0, 0.0}, Mb = 0.0,
            Qb[6] = {0, 0, 0, 0, 0, 0};
     const int64_t e0 = valid ? fstart[v] : 0, e1 = valid ? fend[v] : 0;
@@ -756,14 +942,15 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
         const double *rb = recA + (int64_t)NREC * b;
         const double r[3] = {rv[0] - rb[0], rv[1] - rb[1], rv[2] - rb[2]};
         double Mx = 0.0, Qx[6] = {0, 0, 0, 0, 0, 0};
-        m2l_vjp<FORM>(r, rb[3], recQ + (int64_t)NREC * b, Lb, rs, Mx, Qx);
+        m2l_vjp<FORM, F32>(r, rb[3], recQ + (int64_t)NREC * b, Lb, rs, Mx, Qx);
         const double q[3] = {-r[0], -r[1], -r[2]};
         double Lx[19];
 #pragma unroll
         for (int k = 0; k < 19; ++k)
             Lx[k] = Lbar[(int64_t)NLOC * b + k];
-        lbar_full(Lx);
-        m2l_vjp<FORM>(q, Mv, Qv, Lx, rt, Mb, Qb);
+        if constexpr (vjp_regrouped<FORM, F32>)
+            lbar_full(Lx);
+        m2l_vjp<FORM, F32>(q, Mv, Qv, Lx, rt, Mb, Qb);
     }
     double acc[13] = {rs[0], rs[1], rs[2], rt[0], rt[1], rt[2], Mb,
                       Qb[0], Qb[1], Qb[2], Qb[3], Qb[4], Qb[5]};
@@ -1456,6 +1643,13 @@ static void vfree(Tree &t, std::initializer_list<void **> ptrs)
     }
 }
 
+static void vfree_pieces(Tree &t)
+{
+    vfree(t, {(void **)&t.pnode, (void **)&t.ppart, (void **)&t.pkey, (void **)&t.pkey1,
+              (void **)&t.pid, (void **)&t.porder, (void **)&t.phist});
+    t.piece_cap = t.porder_cap = 0;
+}
+
 static hipError_t ensure_vjp_base(Tree &t)
 {
     if (t.abt)
@@ -1592,10 +1786,26 @@ static hipError_t transpose_lists(Tree &t, const int32_t *cnt, const int32_t *sl
     return e;
 }
 
+// Whether the pieces are evaluated in the order of their sinks: where the
+// arrays of the leaves' cotangents exceed the 4 MiB L2 of an XCD.  In the order
+// of the sources each cell high in the tree sweeps all the arrays (26 GB from
+// beyond the L2 for Plummer, 2^19 particles, 11.5 MB of arrays); in ranges of
+// sinks, one contiguous part of the order per XCD, the part that an XCD reads
+// stays in its L2.  The kernel alone, Plummer 2^19: 3.48 -> 1.99 ms.  The
+// reverse pass, sorted against not: Plummer 2^18 6.69 against 6.78 ms, 2^17
+// (2.9 MB) 3.02 either way, 2^16 1.45 against 1.44; clumpy cube 2^20 (theta
+// 0.4) 7.40 against 7.67.
+constexpr int64_t M2LT_SORT_BYTES = 4 << 20;
+static bool m2lt_sorted(const Tree &t)
+{
+    return (int64_t)t.topo.nleaves * LLEAF * (int64_t)sizeof(double) > M2LT_SORT_BYTES;
+}
+
 // Pieces of the transposed far lists for the source side of M2L^T.
 static hipError_t build_m2lt_pieces(Tree &t, hipStream_t s)
 {
-    const int nn = t.topo.nnodes;
+    const Topology &T = t.topo;
+    const int nn = T.nnodes;
     const int ntiles = (nn + SCAN_TILE - 1) / SCAN_TILE;
     int64_t *total = t.pscan + ntiles;
     const int g = (nn + 255) / 256;
@@ -1609,24 +1819,43 @@ static hipError_t build_m2lt_pieces(Tree &t, hipStream_t s)
     if (e != hipSuccess)
         return e;
     const int64_t np = t.h_pairs[1];
-    if (np > t.piece_cap) {
+    const bool sorted = m2lt_sorted(t);
+    if (np > t.piece_cap || (sorted && np > t.porder_cap)) {
         e = hipStreamSynchronize(s);
         if (e != hipSuccess)
             return e;
-        vfree(t, {(void **)&t.pnode, (void **)&t.ppart});
-        t.piece_cap = 0;
+        vfree_pieces(t);
         const int64_t cp = np + np / 4 + 256;
+        const int64_t nblk = (cp + RS_TILE - 1) / RS_TILE;
         e = tree_malloc(t, (void **)&t.pnode, cp * sizeof(int32_t));
         if (e == hipSuccess)
             e = tree_malloc(t, (void **)&t.ppart, 10 * cp * sizeof(double));
+        for (uint32_t **b : {&t.pkey, &t.pkey1, &t.pid, &t.porder})
+            if (e == hipSuccess && sorted)
+                e = tree_malloc(t, (void **)b, cp * sizeof(uint32_t));
+        if (e == hipSuccess && sorted)
+            e = tree_malloc(t, (void **)&t.phist, RS_MAX_DIGITS * (nblk + 1) * sizeof(uint32_t));
         if (e != hipSuccess) {
-            vfree(t, {(void **)&t.pnode, (void **)&t.ppart});
+            vfree_pieces(t);
             return e;
         }
         t.piece_cap = cp;
+        t.porder_cap = sorted ? cp : 0;
     }
     t.npieces = np;
     k_piece_fill<<<g, 256, 0, s>>>(t.poff, nn, t.pnode);
+    if (sorted) {
+        // one pass of the radix sort: at most 1024 ranges of sinks
+        int kshift = 0;
+        while ((T.nleaves - 1) >> kshift >= RS_MAX_DIGITS)
+            ++kshift;
+        k_piece_keys<<<(int)((np + 255) / 256), 256, 0, s>>>(t.pnode, t.poff, np, t.farT.off,
+                                                             t.farT.src, kshift, t.pkey, t.pid);
+        e = radix_sort_u32(t.pkey, t.pid, t.pkey1, t.porder, np, 1, 1,
+                           t.phist + RS_MAX_DIGITS, t.phist, s, 10);
+        if (e != hipSuccess)
+            return e;
+    }
     return hipGetLastError();
 }
 
@@ -1693,17 +1922,17 @@ static hipError_t build_p2pt_pieces(Tree &t, hipStream_t s)
 }
 
 // M2L^T, sink side per leaf and source side in pieces.
-template <int FORM>
+template <int FORM, bool F32>
 static void vjp_m2l(Tree &t, hipStream_t s)
 {
     const int nl = t.topo.nleaves;
-    k_vjp_m2l_sink<FORM><<<(int)(((int64_t)nl * M2LT_LANES + 255) / 256), 256, 0, s>>>(
+    k_vjp_m2l_sink<FORM, F32><<<(int)(((int64_t)nl * M2LT_LANES + 255) / 256), 256, 0, s>>>(
         t.recA, t.recQ, t.leaf_node, nl, t.far_cnt, t.far_src, (int)t.cap_far, t.Lbar, t.nadj);
     if (t.npieces > 0)
-        k_vjp_m2l_src_piece<FORM>
-            <<<(int)((t.npieces * VJPM_LANES + VJPM_WG - 1) / VJPM_WG), VJPM_WG, 0, s>>>(
+        k_vjp_m2l_src_piece<FORM, F32>
+            <<<(int)((t.npieces * vjpm_lanes(F32) + 63) / 64), 64, 0, s>>>(
             t.recA, t.recQ, t.farT.off, t.farT.src, t.Lleaf, t.topo.leaf_cap, t.pnode, t.poff,
-            t.npieces, t.ppart);
+            m2lt_sorted(t) ? t.porder : nullptr, t.npieces, t.ppart);
 }
 
 // Mutual walk: forward totals of the internal cells, L2L^T level by level
@@ -1724,12 +1953,17 @@ static hipError_t vjp_mutual_far(Tree &t, hipStream_t s)
     const MutualLists &M = t.mw;
     const uint64_t mask = (1ull << mutual_key_bits(t)) - 1ull;
     const int g = (int)(((int64_t)T.nnodes * 16 + 255) / 256);
+    auto run = [&](auto kernel) {
+        kernel<<<g, 256, 0, s>>>(t.recA, t.recQ, T.nnodes, M.fstart, M.fend, M.far_sorted, mask,
+                                 t.Lbar, t.nadj);
+    };
+    const bool fp32 = t.p.precision == FMM_FP32;
     if (t.p.expansion == FMM_EXPANSION_DEHNEN)
-        k_vjp_m2l_mutual<FMM_EXPANSION_DEHNEN><<<g, 256, 0, s>>>(
-            t.recA, t.recQ, T.nnodes, M.fstart, M.fend, M.far_sorted, mask, t.Lbar, t.nadj);
+        run(k_vjp_m2l_mutual<FMM_EXPANSION_DEHNEN, false>);
+    else if (fp32)
+        run(k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM, true>);
     else
-        k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM><<<g, 256, 0, s>>>(
-            t.recA, t.recQ, T.nnodes, M.fstart, M.fend, M.far_sorted, mask, t.Lbar, t.nadj);
+        run(k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM, false>);
     return hipGetLastError();
 }
 
@@ -1775,7 +2009,7 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         k_vjp_prep<float><<<gs, 256, 0, s>>>((const float *)abar, n, t.perm, t.p.G, t.abt);
     else
         k_vjp_prep<double><<<gs, 256, 0, s>>>((const double *)abar, n, t.perm, t.p.G, t.abt);
-    if (t.lists_policy != FMM_WALK_MUTUAL && t.p.expansion == FMM_EXPANSION_PHANTOM)
+    if (t.lists_policy != FMM_WALK_MUTUAL && t.p.expansion == FMM_EXPANSION_PHANTOM && !fp32)
         k_vjp_l2p<true><<<(nl + 255) / 256, 256, 0, s>>>(t.pm, t.abt, t.leaf_node, nl, t.first,
                                                          t.count, t.recA, t.L, t.Lbar, t.Lleaf,
                                                          T.leaf_cap, t.xbt, t.nadj);
@@ -1788,10 +2022,14 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         if (e != hipSuccess)
             return e;
     } else {
-        if (t.p.expansion == FMM_EXPANSION_DEHNEN)
-            vjp_m2l<FMM_EXPANSION_DEHNEN>(t, s);
+        if (t.p.expansion == FMM_EXPANSION_DEHNEN && fp32)
+            vjp_m2l<FMM_EXPANSION_DEHNEN, true>(t, s);
+        else if (t.p.expansion == FMM_EXPANSION_DEHNEN)
+            vjp_m2l<FMM_EXPANSION_DEHNEN, false>(t, s);
+        else if (fp32)
+            vjp_m2l<FMM_EXPANSION_PHANTOM, true>(t, s);
         else
-            vjp_m2l<FMM_EXPANSION_PHANTOM>(t, s);
+            vjp_m2l<FMM_EXPANSION_PHANTOM, false>(t, s);
         k_vjp_m2l_src_fold<<<(T.nnodes + 255) / 256, 256, 0, s>>>(t.left, T.nnodes, t.poff,
                                                                   t.ppart, t.nadj);
     }
@@ -1845,8 +2083,9 @@ void release_vjp(Tree &t)
     t.vjp_owned.clear();
     vfree(t, {(void **)&t.vk0, (void **)&t.vk1, (void **)&t.vv0, (void **)&t.vv1,
               (void **)&t.vhist, (void **)&t.vtot, (void **)&t.farT.src, (void **)&t.nearT.src,
-              (void **)&t.pnode, (void **)&t.ppart, (void **)&t.pnearT.np, (void **)&t.pnearT.off,
+              (void **)&t.pnearT.np, (void **)&t.pnearT.off,
               (void **)&t.pnearT.tsum, (void **)&t.pnearT.list, &t.pnearT.part});
+    vfree_pieces(t);
     t.pnearT.cap = t.pnearT.n = 0;
     t.vjp_pair_cap = t.farT.src_cap = t.nearT.src_cap = 0;
     if (t.h_pairs)
