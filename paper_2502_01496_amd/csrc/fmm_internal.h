@@ -15,7 +15,6 @@ namespace fmm {
 // Nodes with at most SUBTREE_MAX particles are split entirely inside one
 // workgroup's LDS (all their descendants in one launch).
 constexpr int SUBTREE_MAX = 2048;
-constexpr int SUBTREE_MAXSEG = SUBTREE_MAX / 2;
 constexpr int SUBTREE_THREADS = 1024;
 constexpr int SM_MAXNODES = 1024;  // nodes of a subtree whose moments are combined in LDS
 constexpr int SM_MAXL = 16;        // internal levels of such a subtree
