@@ -26,7 +26,7 @@ COMMON = [
 NO_CONTRACT = {"build.hip", "moments.hip", "walk.hip", "mutual.hip", "stats.hip",
                "integrate.hip", "asym.hip", "build_com.hip"}
 SOURCES = ["api.cpp", "build.hip", "moments.hip", "walk.hip", "mutual.hip", "forces.hip",
-           "stats.hip", "vjp.hip", "integrate.hip", "asym.hip", "build_com.hip"]
+           "stats.hip", "vjp.hip", "integrate.hip", "asym.hip", "build_com.hip", "transpose.hip"]
 
 
 def _compile(src: str) -> str:

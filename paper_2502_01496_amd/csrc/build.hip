@@ -392,17 +392,10 @@ __global__ __launch_bounds__(RS_SCAN_THREADS) void k_rs_scan(uint32_t *hist, uin
         tot[b * nb + d] = run;
 }
 
-template <int BITS>
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
+hipError_t launch_rs_scan(uint32_t *hist, uint32_t *tot, int digits, int nblk, hipStream_t s)
 {
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < BITS; ++bit) {
-        bool on = (d >> bit) & 1u;
-        uint64_t bb = __ballot(valid && on);
-        m &= on ? bb : ~bb;
-    }
-    return m;
+    k_rs_scan<<<dim3(digits, 1), RS_SCAN_THREADS, 0, s>>>(hist, tot, nblk);
+    return hipGetLastError();
 }
 
 // Stable scatter of one tile: rank the keys by digit (per wave, ballot

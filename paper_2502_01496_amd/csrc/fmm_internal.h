@@ -307,8 +307,13 @@ struct Tree {
     int64_t vjp_pair_cap = 0;
     uint32_t *vk0 = nullptr, *vk1 = nullptr;
     uint32_t *vv0 = nullptr, *vv1 = nullptr, *vhist = nullptr, *vtot = nullptr;
-    int64_t *pair_off = nullptr;   // nleaves + 1 offsets of the compacted pairs
-    int64_t *vscan = nullptr;
+    // transposition: leaves of pairs, pairs between the passes, digit counts
+    int64_t tp_cap = 0;
+    int32_t *tp_seg = nullptr;
+    uint32_t *tp_tmp = nullptr, *tp_hist = nullptr, *tp_tot = nullptr;
+    // far and near: nleaves + 1 offsets of the pairs in the order of the lists
+    int64_t *pair_off[2] = {nullptr, nullptr};
+    int64_t *vscan[2] = {nullptr, nullptr};
     double *abt = nullptr;         // G * abar, tree order, 3 per particle
     double *xbt = nullptr;         // xbar accumulator, tree order, 3 per particle
     double *mbt = nullptr;         // mbar accumulator, tree order
@@ -407,7 +412,42 @@ hipError_t radix_sort_u32(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1
                           int B, int passes, uint32_t *hist, uint32_t *tot, hipStream_t s,
                           int digit_bits);
 void radix_plan(int bits, int &passes, int &digit_bits);
+// Exclusive scans of digit rows over the tiles; the row totals go to tot.
+hipError_t launch_rs_scan(uint32_t *hist, uint32_t *tot, int digits, int nblk, hipStream_t s);
 
+// Lanes of the wavefront with the same digit of BITS bits.
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
+{
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < BITS; ++bit) {
+        bool on = (d >> bit) & 1u;
+        uint64_t bb = __ballot(valid && on);
+        m &= on ? bb : ~bb;
+    }
+    return m;
+}
+
+// The pairs of interaction lists: list k of leaf lf is slots[lf * cap + k], its
+// first pair off[lf]; seg: leaf of every 64th pair.
+struct PairLists {
+    const int64_t *off;
+    const int32_t *slots;
+    int64_t cap;
+    const int32_t *seg;
+    int nl, leaf_bits;
+    int64_t np;
+};
+// Transposition (np > 0): off[0 .. nnodes] and out, the sinks of each target;
+// map: what the leaf indices are written as (null: themselves).  Work space:
+// seg of tp_seg_entries, tmp of np, hist of tp_hist_words, tot of 2048.
+int tp_digit_bits(int key_bits, int leaf_bits);
+int64_t tp_seg_entries(int64_t np);
+int64_t tp_hist_words(int64_t np);
+hipError_t launch_transpose(const PairLists &P, int key_bits, const int32_t *map, int nnodes,
+                            int32_t *seg, uint32_t *tmp, uint32_t *hist, uint32_t *tot,
+                            int64_t *off, uint32_t *out, hipStream_t s);
 
 // launchers (return hipError_t of the last launch / runtime call)
 hipError_t launch_build(Tree &t, const double *x, hipStream_t s);

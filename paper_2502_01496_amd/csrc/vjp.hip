@@ -1650,6 +1650,12 @@ static void vfree_pieces(Tree &t)
     t.piece_cap = t.porder_cap = 0;
 }
 
+static void vfree_transpose(Tree &t)
+{
+    vfree(t, {(void **)&t.tp_seg, (void **)&t.tp_tmp, (void **)&t.tp_hist, (void **)&t.tp_tot});
+    t.tp_cap = 0;
+}
+
 static hipError_t ensure_vjp_base(Tree &t)
 {
     if (t.abt)
@@ -1663,8 +1669,10 @@ static hipError_t ensure_vjp_base(Tree &t)
     if (e == hipSuccess) e = valloc(t, &t.Lbar, NLOC * nc);
     if (e == hipSuccess) e = valloc(t, &t.Lleaf, LLEAF / 2 * (int64_t)T.leaf_cap);
     if (e == hipSuccess) e = valloc(t, &t.nadj, 16 * nc);
-    if (e == hipSuccess) e = valloc(t, &t.pair_off, T.leaf_cap + 1);
-    if (e == hipSuccess) e = valloc(t, &t.vscan, T.leaf_cap / SCAN_TILE + 2);
+    for (int k = 0; k < 2; ++k) {
+        if (e == hipSuccess) e = valloc(t, &t.pair_off[k], T.leaf_cap + 1);
+        if (e == hipSuccess) e = valloc(t, &t.vscan[k], T.leaf_cap / SCAN_TILE + 2);
+    }
     if (e == hipSuccess) e = valloc(t, &t.farT.off, nc + 1);
     if (e == hipSuccess) e = valloc(t, &t.pcnt, nc);
     if (e == hipSuccess) e = valloc(t, &t.poff, nc + 1);
@@ -1679,7 +1687,9 @@ static hipError_t ensure_vjp_base(Tree &t)
         t.vjp_owned.clear();
         t.abt = t.xbt = t.mbt = t.Lbar = t.nadj = nullptr;
         t.Lleaf = nullptr;
-        t.pair_off = t.vscan = t.farT.off = t.poff = t.pscan = t.nearT.off = nullptr;
+        t.farT.off = t.poff = t.pscan = t.nearT.off = nullptr;
+        for (int k = 0; k < 2; ++k)
+            t.pair_off[k] = t.vscan[k] = nullptr;
         t.pcnt = nullptr;
     }
     return e;
@@ -1694,23 +1704,15 @@ static int key_bits(int nnodes)
     return bits;
 }
 
-// Build one transposed list (sink-major pairs -> target-major CSR, stable).
-static hipError_t transpose_lists(Tree &t, const int32_t *cnt, const int32_t *slots, int64_t cap,
-                                  bool node_values, Tree::Transposed &out, hipStream_t s)
+// The same where the targets take more than two digits (trees of more than
+// 2^20 cells): the pairs as (key, value), sorted as such.
+static hipError_t sort_pairs(Tree &t, int k, const int32_t *cnt, const int32_t *slots, int64_t cap,
+                             bool node_values, Tree::Transposed &out, hipStream_t s)
 {
     const Topology &T = t.topo;
     const int nl = T.nleaves;
-    const int ntiles = (nl + SCAN_TILE - 1) / SCAN_TILE;
-    int64_t *total = t.vscan + ntiles;
-    k_cnt_tiles<<<ntiles, 256, 0, s>>>(cnt, (int)cap, nl, t.vscan);
-    k_cnt_tile_scan<<<1, 1024, 0, s>>>(t.vscan, ntiles, total);
-    k_cnt_write<<<ntiles, 256, 0, s>>>(cnt, (int)cap, nl, t.vscan, total, t.pair_off);
-    hipError_t e = hipMemcpyAsync(t.h_pairs, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
-        return e;
-    const int64_t np = t.h_pairs[0];
+    const int64_t np = t.h_pairs[k];
+    hipError_t e = hipSuccess;
     if (np > t.vjp_pair_cap || !t.vv0) {
         // (re)allocate the pair sort buffers
         e = hipStreamSynchronize(s);
@@ -1738,7 +1740,7 @@ static hipError_t transpose_lists(Tree &t, const int32_t *cnt, const int32_t *sl
     }
     if (nl > 0)
         k_pairs_write<<<nl, 64, 0, s>>>(cnt, slots, (int)cap, nl, t.leaf_node, node_values ? 1 : 0,
-                                        t.pair_off, t.vk0, t.vv0);
+                                        t.pair_off[k], t.vk0, t.vv0);
     int passes, dbits;
     radix_plan(key_bits(T.nnodes), passes, dbits);
     e = radix_sort_u32(t.vk0, t.vv0, t.vk1, t.vv1, np, 1, passes, t.vhist, t.vtot, s, dbits);
@@ -1786,6 +1788,68 @@ static hipError_t transpose_lists(Tree &t, const int32_t *cnt, const int32_t *sl
     return e;
 }
 
+// Offsets of the pairs of the far (k = 0) or near lists, and the readback of
+// their number to h_pairs[k].
+static hipError_t count_pairs_async(Tree &t, int k, const int32_t *cnt, int64_t cap, hipStream_t s)
+{
+    const int nl = t.topo.nleaves;
+    const int ntiles = (nl + SCAN_TILE - 1) / SCAN_TILE;
+    int64_t *total = t.vscan[k] + ntiles;
+    k_cnt_tiles<<<ntiles, 256, 0, s>>>(cnt, (int)cap, nl, t.vscan[k]);
+    k_cnt_tile_scan<<<1, 1024, 0, s>>>(t.vscan[k], ntiles, total);
+    k_cnt_write<<<ntiles, 256, 0, s>>>(cnt, (int)cap, nl, t.vscan[k], total, t.pair_off[k]);
+    return hipMemcpyAsync(t.h_pairs + k, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+}
+
+// Build one transposed list (sink-major pairs -> target-major CSR, stable).
+static hipError_t transpose_lists(Tree &t, int k, const int32_t *cnt, const int32_t *slots,
+                                  int64_t cap, bool node_values, Tree::Transposed &out,
+                                  hipStream_t s)
+{
+    const Topology &T = t.topo;
+    const int kb = key_bits(T.nnodes), lb = key_bits(T.nleaves);
+    const int64_t np = t.h_pairs[k];
+    if (np == 0) {
+        k_lower_bound<<<(T.nnodes + 256) / 256, 256, 0, s>>>(nullptr, 0, T.nnodes, out.off);
+        out.npairs = 0;
+        return hipGetLastError();
+    }
+    if (!tp_digit_bits(kb, lb))
+        return sort_pairs(t, k, cnt, slots, cap, node_values, out, s);
+    hipError_t e = hipSuccess;
+    if (np > t.tp_cap || np > out.src_cap) {
+        if ((e = hipStreamSynchronize(s)) != hipSuccess)
+            return e;
+        const int64_t cp = np + np / 4 + 1024;
+        if (np > t.tp_cap) {
+            vfree_transpose(t);
+            e = tree_malloc(t, (void **)&t.tp_seg, tp_seg_entries(cp) * sizeof(int32_t));
+            if (e == hipSuccess)
+                e = tree_malloc(t, (void **)&t.tp_tmp, cp * sizeof(uint32_t));
+            if (e == hipSuccess)
+                e = tree_malloc(t, (void **)&t.tp_hist, tp_hist_words(cp) * sizeof(uint32_t));
+            if (e == hipSuccess)
+                e = tree_malloc(t, (void **)&t.tp_tot, 2 * RS_MAX_DIGITS * sizeof(uint32_t));
+            if (e != hipSuccess) {
+                vfree_transpose(t);
+                return e;
+            }
+            t.tp_cap = cp;
+        }
+        if (np > out.src_cap) {
+            vfree(t, {(void **)&out.src});
+            out.src_cap = 0;
+            if ((e = tree_malloc(t, (void **)&out.src, cp * sizeof(uint32_t))) != hipSuccess)
+                return e;
+            out.src_cap = cp;
+        }
+    }
+    out.npairs = np;
+    const PairLists P = {t.pair_off[k], slots, cap, t.tp_seg, T.nleaves, lb, np};
+    return launch_transpose(P, kb, node_values ? t.leaf_node : nullptr, T.nnodes, t.tp_seg,
+                            t.tp_tmp, t.tp_hist, t.tp_tot, out.off, out.src, s);
+}
+
 // Whether the pieces are evaluated in the order of their sinks: where the
 // arrays of the leaves' cotangents exceed the 4 MiB L2 of an XCD.  In the order
 // of the sources each cell high in the tree sweeps all the arrays (26 GB from
@@ -1801,24 +1865,28 @@ static bool m2lt_sorted(const Tree &t)
     return (int64_t)t.topo.nleaves * LLEAF * (int64_t)sizeof(double) > M2LT_SORT_BYTES;
 }
 
-// Pieces of the transposed far lists for the source side of M2L^T.
-static hipError_t build_m2lt_pieces(Tree &t, hipStream_t s)
+// Pieces of the transposed far lists for the source side of M2L^T: their
+// number, to h_pairs[2].
+static hipError_t count_m2lt_pieces_async(Tree &t, hipStream_t s)
 {
-    const Topology &T = t.topo;
-    const int nn = T.nnodes;
+    const int nn = t.topo.nnodes;
     const int ntiles = (nn + SCAN_TILE - 1) / SCAN_TILE;
     int64_t *total = t.pscan + ntiles;
-    const int g = (nn + 255) / 256;
-    k_piece_count<<<g, 256, 0, s>>>(t.farT.off, nn, t.pcnt);
+    k_piece_count<<<(nn + 255) / 256, 256, 0, s>>>(t.farT.off, nn, t.pcnt);
     k_cnt_tiles<<<ntiles, 256, 0, s>>>(t.pcnt, INT32_MAX, nn, t.pscan);
     k_cnt_tile_scan<<<1, 1024, 0, s>>>(t.pscan, ntiles, total);
     k_cnt_write<<<ntiles, 256, 0, s>>>(t.pcnt, INT32_MAX, nn, t.pscan, total, t.poff);
-    hipError_t e = hipMemcpyAsync(t.h_pairs + 1, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
-        return e;
-    const int64_t np = t.h_pairs[1];
+    return hipMemcpyAsync(t.h_pairs + 2, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+}
+
+// The table of those pieces, once their number is known.
+static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
+{
+    const Topology &T = t.topo;
+    const int nn = T.nnodes;
+    const int g = (nn + 255) / 256;
+    hipError_t e = hipSuccess;
+    const int64_t np = t.h_pairs[2];
     const bool sorted = m2lt_sorted(t);
     if (np > t.piece_cap || (sorted && np > t.porder_cap)) {
         e = hipStreamSynchronize(s);
@@ -1873,7 +1941,7 @@ __global__ void k_tpiece_count(const int32_t *__restrict__ leaf_node, int nleave
     np[lf] = (int32_t)max<int64_t>(1, (wk + per - 1) / per);
 }
 
-static hipError_t build_p2pt_pieces(Tree &t, hipStream_t s)
+static hipError_t count_p2pt_pieces_async(Tree &t, hipStream_t s)
 {
     Tree::Pieces &P = t.pnearT;
     const Topology &T = t.topo;
@@ -1897,12 +1965,17 @@ static hipError_t build_p2pt_pieces(Tree &t, hipStream_t s)
                                                      t.vjp_src_piece_blocks, P.np);
     e = launch_count_scan(P.np, INT32_MAX, nl, P.tsum, P.off, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(t.h_pairs + 2, P.off + nl, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
-        return e;
-    const int64_t np = t.h_pairs[2];
+        e = hipMemcpyAsync(t.h_pairs + 3, P.off + nl, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+    return e;
+}
+
+static hipError_t fill_p2pt_pieces(Tree &t, hipStream_t s)
+{
+    Tree::Pieces &P = t.pnearT;
+    const Topology &T = t.topo;
+    const int nl = T.nleaves;
+    hipError_t e = hipSuccess;
+    const int64_t np = t.h_pairs[3];
     if (np > nl && np > P.cap) {
         vfree(t, {(void **)&P.list, &P.part});
         P.cap = 0;
@@ -1975,15 +2048,28 @@ hipError_t ensure_transposed(Tree &t, hipStream_t s)
     hipError_t e = ensure_vjp_base(t);
     if (e != hipSuccess || t.has_transposed)
         return e;
-    if (t.lists_policy != FMM_WALK_MUTUAL) {
-        e = transpose_lists(t, t.far_cnt, t.far_src, t.cap_far, false, t.farT, s);
-        if (e == hipSuccess)
-            e = build_m2lt_pieces(t, s);
-    }
+    // two readbacks: the numbers of pairs, the numbers of pieces
+    const bool far = t.lists_policy != FMM_WALK_MUTUAL;
+    if (far)
+        e = count_pairs_async(t, 0, t.far_cnt, t.cap_far, s);
     if (e == hipSuccess)
-        e = transpose_lists(t, t.near_cnt, t.near_src, t.cap_near, true, t.nearT, s);
+        e = count_pairs_async(t, 1, t.near_cnt, t.cap_near, s);
     if (e == hipSuccess)
-        e = build_p2pt_pieces(t, s);
+        e = hipStreamSynchronize(s);
+    if (e == hipSuccess && far)
+        e = transpose_lists(t, 0, t.far_cnt, t.far_src, t.cap_far, false, t.farT, s);
+    if (e == hipSuccess)
+        e = transpose_lists(t, 1, t.near_cnt, t.near_src, t.cap_near, true, t.nearT, s);
+    if (e == hipSuccess && far)
+        e = count_m2lt_pieces_async(t, s);
+    if (e == hipSuccess)
+        e = count_p2pt_pieces_async(t, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e == hipSuccess && far)
+        e = fill_m2lt_pieces(t, s);
+    if (e == hipSuccess)
+        e = fill_p2pt_pieces(t, s);
     if (e == hipSuccess)
         t.has_transposed = true;
     return e;
@@ -2086,6 +2172,7 @@ void release_vjp(Tree &t)
               (void **)&t.pnearT.np, (void **)&t.pnearT.off,
               (void **)&t.pnearT.tsum, (void **)&t.pnearT.list, &t.pnearT.part});
     vfree_pieces(t);
+    vfree_transpose(t);
     t.pnearT.cap = t.pnearT.n = 0;
     t.vjp_pair_cap = t.farT.src_cap = t.nearT.src_cap = 0;
     if (t.h_pairs)
