@@ -346,13 +346,14 @@ static fmm_status create_tree(int64_t n, const fmm_params &p, Tree **out)
         A(dalloc(*t, &t->int_nodes, nc));
         A(dalloc(*t, &t->big_nodes, nc));
         Tree::ComWork &W = t->cw;
-        W.cap_a = n / (p.leaf_size + 1) + 2;
+        W.cap_a = com_max_active(n) + 1;
         W.cap_c = (n + COM_CHUNK - 1) / COM_CHUNK + W.cap_a + 2;
         A(dalloc(*t, &W.q, 4 * n));
         A(dalloc(*t, &W.q_tmp, 4 * n));
-        A(dalloc(*t, &W.perm_tmp, n));
+        A(dalloc(*t, &W.perm_tmp, 2 * n));
         A(dalloc(*t, &W.node, 8 * nc));
         A(dalloc(*t, &W.ren, 4 * nc));
+        A(dalloc(*t, &W.rec, 2 * n));
         for (int k = 0; k < 2; ++k) {
             A(dalloc(*t, &W.act[k], W.cap_a));
             A(dalloc(*t, &W.act_choff[k], W.cap_a + 1));
@@ -360,13 +361,10 @@ static fmm_status create_tree(int64_t n, const fmm_params &p, Tree **out)
         }
         A(dalloc(*t, &W.cpart, 16 * W.cap_c));
         A(dalloc(*t, &W.cleft, W.cap_c));
-        A(dalloc(*t, &W.cbase, W.cap_c));
         A(dalloc(*t, &W.split, 4 * W.cap_a));
-        A(dalloc(*t, &W.nl, W.cap_a));
-        A(dalloc(*t, &W.big, nc));
-        A(dalloc(*t, &W.ctl, 8));
+        A(dalloc(*t, &W.ctl, COM_CTL));
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&W.h_ctl, 8 * sizeof(int64_t), hipHostMallocDefault);
+            e = hipHostMalloc((void **)&W.h_ctl, COM_CTL * sizeof(int64_t), hipHostMallocDefault);
     } else {
         build_topology(n, p.leaf_size, t->topo);
         const Topology &T = t->topo;

@@ -11,28 +11,42 @@
 // particles share one grid point is halved in tree order.
 //
 // The shape depends on the data, so the build is level-synchronous over the
-// cells still to be cut ("active"), each cut in chunks of COM_CHUNK
-// particles:
-//   stats (per chunk: quantised box, sum w, sum w q) -> split (per cell:
-//   fold its chunks, axis and cut) -> count (per chunk: particles going
-//   left) -> offsets (per cell: exclusive bases of its chunks) -> scatter
-//   (per chunk: stable partition into a copy) -> copy back -> children (per
-//   cell: two new cells) -> next (one workgroup: the next level's active
-//   cells and chunks).
-// One readback per level gives the host the next launch sizes.  Cells are
-// numbered breadth-first while building and renumbered to DFS pre-order
-// (subtree sizes bottom-up, ids top-down), the numbering every later stage
-// expects.
+// cells of more than COM_SUB particles ("active"), each cut in chunks of
+// COM_CHUNK particles:
+//   stats (per chunk: quantised box, sum w, sum w q) -> count (per chunk: its
+//   cell's stats folded, axis and cut, particles going left) -> scatter (per
+//   chunk: stable partition into the other buffer; the two new cells) -> next
+//   (one workgroup: the next level's active cells and chunks).
+// The sizes of a level stay on the device; the host launches the levels that a
+// balanced tree has and reads back once, then one by one while cells are left.
+// Every cell of at most COM_SUB particles is finished by one workgroup in LDS
+// (all levels below it).  Cells are numbered as they appear and renumbered to
+// DFS pre-order: a finished cell's nodes among themselves in LDS, the cells
+// above by one workgroup.  The internal cells by level follow from one pass of
+// the radix sort.
+// Launches bound the build at a few 10^5 particles: 200003 (leaf 10) took 1.57
+// ms as 18 levels of 8 launches and a readback each, this 0.54; 2^20 particles
+// 3.68 and 1.12 ms.
 #include "fmm_internal.h"
 
 namespace fmm {
 
-constexpr int CB = 256;  // threads per chunk workgroup
+constexpr int CB = 1024;  // threads per chunk workgroup
+constexpr int COM_SUB = 2048;  // largest cell finished in LDS
 
-// BFS node table rows
-enum { NF = 0, NC = 1, NP = 2, NLV = 3, NAX = 4, NL = 5, NR = 6, NIR = 7 };
-// renumbering rows
-enum { RSUB = 0, RLEAF = 1, RPRE = 2, RLOFS = 3 };
+// control words: active cells and chunks of the level, finished cells, m_max
+// bits, cells so far, levels above the finished cells, cells and leaves in
+// all, depth, large cells (written, counted), then internal cells per level
+enum { CA = 0, CC = 1, CS = 2, CMM = 3, CNN = 4, CLEV = 5, CTOT = 6, CLEAF = 7, CDEP = 8, CBIG = 9,
+       CNBIG = 10, CLVL = 16 };
+static_assert(CLVL + COM_MAX_DEPTH <= COM_CTL, "control words");
+
+// node table rows of the cells above the finished ones, and of those: first,
+// count, parent, level, axis, children, pre-order id
+enum { NF = 0, NC = 1, NP = 2, NLV = 3, NAX = 4, NL = 5, NR = 6, NPRE = 7 };
+// renumbering rows: nodes of the subtree, leaves before it, first cell of each
+// level, finished cells
+enum { RSUB = 0, RLOFS = 1, RLEV = 2, RFIN = 3 };
 
 __device__ __forceinline__ void add128(uint64_t &lo, uint64_t &hi, uint64_t blo, uint64_t bhi)
 {
@@ -51,15 +65,16 @@ __device__ __forceinline__ bool left_of_cut(uint32_t qd, uint64_t sw, uint64_t l
 
 __global__ void k_com_zero(int64_t *ctl)
 {
-    if (threadIdx.x < 8)
+    if (threadIdx.x < COM_CTL)
         ctl[threadIdx.x] = 0;
 }
 
 // Largest positive mass (NaN and non-positive masses ignored), as ordered
-// bits in ctl[3].
+// bits in ctl[CMM]; one atomic per workgroup.
 __global__ __launch_bounds__(256) void k_com_mmax(const double *__restrict__ m, int64_t n,
                                                   int64_t *ctl)
 {
+    __shared__ uint64_t sh[4];
     uint64_t best = 0ull;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -74,8 +89,15 @@ __global__ __launch_bounds__(256) void k_com_mmax(const double *__restrict__ m, 
         const uint64_t o = __shfl_xor((unsigned long long)best, off);
         best = o > best ? o : best;
     }
-    if (lane_id() == 0 && best)
-        atomicMax((unsigned long long *)&ctl[3], (unsigned long long)best);
+    if (lane_id() == 0)
+        sh[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w)
+            best = sh[w] > best ? sh[w] : best;
+        if (best)
+            atomicMax((unsigned long long *)&ctl[CMM], (unsigned long long)best);
+    }
 }
 
 // Tree order = Morton order; quantised coordinates and weights.
@@ -97,7 +119,7 @@ __global__ __launch_bounds__(256) void k_com_init(const double *__restrict__ x,
     if (ext == 0.0)
         ext = 1.0;
     const double scale = 4294967296.0 / ext;
-    const uint64_t mb = (uint64_t)ctl[3];
+    const uint64_t mb = (uint64_t)ctl[CMM];
     const double mmax = mb ? from_ordbits(mb) : 0.0;
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
          p += (int64_t)gridDim.x * blockDim.x) {
@@ -117,14 +139,13 @@ __global__ __launch_bounds__(256) void k_com_init(const double *__restrict__ x,
     }
 }
 
-// The root cell and, when it is to be cut, its chunks.
-__global__ __launch_bounds__(256) void k_com_root(int64_t n, int leaf_size, int32_t *node,
-                                                  int64_t cap, int32_t *act, int64_t *choff,
-                                                  int32_t *chk, int64_t cap_c, int32_t *big,
-                                                  int64_t *ctl)
+// The root cell and, when it is active, its chunks.
+__global__ __launch_bounds__(256) void k_com_root(int64_t n, int32_t *node, int64_t cap,
+                                                  int32_t *act, int64_t *choff, int32_t *chk,
+                                                  int64_t cap_c, int32_t *ren, int64_t *ctl)
 {
     const int t = threadIdx.x;
-    const bool cut = n > leaf_size;
+    const bool cut = n > COM_SUB;
     const int64_t nch = cut ? (n + COM_CHUNK - 1) / COM_CHUNK : 0;
     if (t == 0) {
         node[NF * cap] = 0;
@@ -134,17 +155,16 @@ __global__ __launch_bounds__(256) void k_com_root(int64_t n, int leaf_size, int3
         node[NAX * cap] = -1;
         node[NL * cap] = -1;
         node[NR * cap] = -1;
-        node[NIR * cap] = -1;
-        if (cut) {
-            act[0] = 0;
-            choff[0] = 0;
-            choff[1] = nch;
-        }
-        ctl[0] = cut ? 1 : 0;
-        ctl[1] = nch;
-        ctl[2] = n >= 64 ? 1 : 0;
-        if (n >= 64)
-            big[0] = 0;
+        act[0] = 0;
+        choff[0] = 0;
+        choff[1] = nch;
+        ren[RLEV * cap] = 0;
+        ren[RFIN * cap] = 0;
+        ctl[CA] = cut ? 1 : 0;
+        ctl[CC] = nch;
+        ctl[CS] = cut ? 0 : 1;
+        ctl[CNN] = 1;
+        ctl[CLEV] = 1;
     }
     for (int64_t c = t; c < nch; c += blockDim.x) {
         chk[c] = 0;
@@ -156,10 +176,13 @@ __global__ __launch_bounds__(256) void k_com_root(int64_t n, int leaf_size, int3
 // Per chunk: quantised box, sum w and sum w q_d (d = 0..2, 128-bit).
 __global__ __launch_bounds__(CB) void k_com_stats(const uint32_t *__restrict__ q, int64_t n,
                                                   const int32_t *__restrict__ chk, int64_t cap_c,
-                                                  uint64_t *cpart)
+                                                  uint64_t *cpart,
+                                                  const int64_t *__restrict__ ctl)
 {
     __shared__ uint64_t sh[CB / 64][13];
     const int c = blockIdx.x;
+    if (c >= ctl[CC])
+        return;
     const int start = chk[cap_c + c], end = chk[2 * cap_c + c];
     uint32_t mn[3] = {~0u, ~0u, ~0u}, mx[3] = {0u, 0u, 0u};
     uint64_t sw = 0ull, lo[3] = {0ull, 0ull, 0ull}, hi[3] = {0ull, 0ull, 0ull};
@@ -217,37 +240,6 @@ __global__ __launch_bounds__(CB) void k_com_stats(const uint32_t *__restrict__ q
     }
 }
 
-// Per active cell: fold its chunks; axis, degenerate flag and the cut.
-// split[4a] = axis | degenerate << 8, then sum w, sum w q_axis (lo, hi).
-__global__ __launch_bounds__(256) void k_com_split(int64_t A, const int64_t *__restrict__ choff,
-                                                  const uint64_t *__restrict__ cpart,
-                                                  uint64_t *split)
-{
-    const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (a >= A)
-        return;
-    uint64_t mn[3] = {~0ull, ~0ull, ~0ull}, mx[3] = {0ull, 0ull, 0ull};
-    uint64_t sw = 0ull, lo[3] = {0ull, 0ull, 0ull}, hi[3] = {0ull, 0ull, 0ull};
-    for (int64_t c = choff[a]; c < choff[a + 1]; ++c) {
-        const uint64_t *r = cpart + 16 * c;
-        for (int d = 0; d < 3; ++d) {
-            mn[d] = r[d] < mn[d] ? r[d] : mn[d];
-            mx[d] = r[3 + d] > mx[d] ? r[3 + d] : mx[d];
-            add128(lo[d], hi[d], r[7 + 2 * d], r[8 + 2 * d]);
-        }
-        sw += r[6];
-    }
-    int ax = 0;
-    for (int d = 1; d < 3; ++d)
-        if (mx[d] - mn[d] > mx[ax] - mn[ax])
-            ax = d;
-    const uint64_t degenerate = mx[ax] == mn[ax] ? 1ull : 0ull;
-    split[4 * a] = (uint64_t)ax | (degenerate << 8);
-    split[4 * a + 1] = sw;
-    split[4 * a + 2] = lo[ax];
-    split[4 * a + 3] = hi[ax];
-}
-
 __device__ __forceinline__ bool goes_left(const uint32_t *__restrict__ q, int64_t n, int p,
                                           int first, int count, const uint64_t *sp)
 {
@@ -257,20 +249,74 @@ __device__ __forceinline__ bool goes_left(const uint32_t *__restrict__ q, int64_
     return left_of_cut(q[ax * n + p], sp[1], sp[2], sp[3]);
 }
 
-// Per chunk: particles going left.
+// Per chunk: the cell's chunks folded; axis, degenerate flag and cut (split[4a]
+// = axis | degenerate << 8, then sum w, sum w q_axis (lo, hi), written by the
+// cell's first chunk); particles going left.
 __global__ __launch_bounds__(CB) void k_com_count(const uint32_t *__restrict__ q, int64_t n,
                                                   const int32_t *__restrict__ chk, int64_t cap_c,
                                                   const int32_t *__restrict__ act,
+                                                  const int64_t *__restrict__ choff,
                                                   const int32_t *__restrict__ node, int64_t cap,
-                                                  const uint64_t *__restrict__ split,
-                                                  int32_t *cleft)
+                                                  const uint64_t *__restrict__ cpart,
+                                                  uint64_t *split, int32_t *cleft,
+                                                  const int64_t *__restrict__ ctl)
 {
+    __shared__ uint64_t sp[4];
     __shared__ int sh[CB / 64];
     const int c = blockIdx.x;
+    if (c >= ctl[CC])
+        return;
     const int a = chk[c], start = chk[cap_c + c], end = chk[2 * cap_c + c];
     const int v = act[a];
     const int f = node[NF * cap + v], cnt = node[NC * cap + v];
-    const uint64_t *sp = split + 4 * (int64_t)a;
+    if (threadIdx.x < 64) {
+        uint64_t mn[3] = {~0ull, ~0ull, ~0ull}, mx[3] = {0ull, 0ull, 0ull};
+        uint64_t sw = 0ull, lo[3] = {0ull, 0ull, 0ull}, hi[3] = {0ull, 0ull, 0ull};
+        for (int64_t j = choff[a] + threadIdx.x; j < choff[a + 1]; j += 64) {
+            const uint64_t *r = cpart + 16 * j;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mn[d] = r[d] < mn[d] ? r[d] : mn[d];
+                mx[d] = r[3 + d] > mx[d] ? r[3 + d] : mx[d];
+                add128(lo[d], hi[d], r[7 + 2 * d], r[8 + 2 * d]);
+            }
+            sw += r[6];
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            sw += __shfl_xor((unsigned long long)sw, off);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const uint64_t x = __shfl_xor((unsigned long long)mn[d], off);
+                const uint64_t y = __shfl_xor((unsigned long long)mx[d], off);
+                mn[d] = x < mn[d] ? x : mn[d];
+                mx[d] = y > mx[d] ? y : mx[d];
+                const uint64_t ol = __shfl_xor((unsigned long long)lo[d], off);
+                const uint64_t oh = __shfl_xor((unsigned long long)hi[d], off);
+                add128(lo[d], hi[d], ol, oh);
+            }
+        }
+        if (threadIdx.x == 0) {
+            int ax = 0;
+            uint64_t ext = mx[0] - mn[0], slo = lo[0], shi = hi[0];
+#pragma unroll
+            for (int d = 1; d < 3; ++d)
+                if (mx[d] - mn[d] > ext) {
+                    ax = d;
+                    ext = mx[d] - mn[d];
+                    slo = lo[d];
+                    shi = hi[d];
+                }
+            sp[0] = (uint64_t)ax | (ext == 0ull ? 1ull << 8 : 0ull);
+            sp[1] = sw;
+            sp[2] = slo;
+            sp[3] = shi;
+            if (c == choff[a])
+                for (int k = 0; k < 4; ++k)
+                    split[4 * (int64_t)a + k] = sp[k];
+        }
+    }
+    __syncthreads();
     int k = 0;
     for (int p = start + threadIdx.x; p < end; p += CB)
         k += goes_left(q, n, p, f, cnt, sp) ? 1 : 0;
@@ -288,45 +334,62 @@ __global__ __launch_bounds__(CB) void k_com_count(const uint32_t *__restrict__ q
     }
 }
 
-// Per active cell, over its chunks in order: cleft becomes the exclusive base
-// of the chunk's left particles, cbase that of its right particles; nl = the
-// cell's left count.
-__global__ __launch_bounds__(256) void k_com_offsets(int64_t A, const int64_t *__restrict__ choff,
-                                                    const int32_t *__restrict__ chk,
-                                                    int64_t cap_c, int32_t *cleft,
-                                                    int32_t *cbase, int32_t *nl)
-{
-    const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (a >= A)
-        return;
-    int rl = 0, rr = 0;
-    for (int64_t c = choff[a]; c < choff[a + 1]; ++c) {
-        const int len = chk[2 * cap_c + c] - chk[cap_c + c];
-        const int l = cleft[c];
-        cleft[c] = rl;
-        cbase[c] = rr;
-        rl += l;
-        rr += len - l;
-    }
-    nl[a] = rl;
-}
-
-// Per chunk: stable partition into the copy, 256 particles per round in
-// order (a round's lanes hold consecutive particles).
+// Per chunk: stable partition into the other buffer, CB particles per round in
+// order (a round's lanes hold consecutive particles).  The cell's first chunk
+// writes its children: cells NN + 2a (left) and NN + 2a + 1 (right).
 __global__ __launch_bounds__(CB) void k_com_scatter(
     const uint32_t *__restrict__ q, const int32_t *__restrict__ perm, int64_t n,
     const int32_t *__restrict__ chk, int64_t cap_c, const int32_t *__restrict__ act,
-    const int32_t *__restrict__ node, int64_t cap, const uint64_t *__restrict__ split,
-    const int32_t *__restrict__ cleft, const int32_t *__restrict__ cbase,
-    const int32_t *__restrict__ nl, uint32_t *q_tmp, int32_t *perm_tmp)
+    const int64_t *__restrict__ choff, int32_t *node, int64_t cap,
+    const uint64_t *__restrict__ split, const int32_t *__restrict__ cleft, uint32_t *q_out,
+    int32_t *perm_out, const int64_t *__restrict__ ctl)
 {
     __shared__ int wl[CB / 64];
+    __shared__ int sbase[2];
     const int c = blockIdx.x;
+    if (c >= ctl[CC])
+        return;
     const int a = chk[c], start = chk[cap_c + c], end = chk[2 * cap_c + c];
     const int v = act[a];
     const int f = node[NF * cap + v], cnt = node[NC * cap + v];
     const uint64_t *sp = split + 4 * (int64_t)a;
-    int bl = f + cleft[c], br = f + nl[a] + cbase[c];
+    if (threadIdx.x < 64) {
+        // left particles of the cell's earlier chunks, and of all
+        int before = 0, all = 0;
+        for (int64_t j = choff[a] + threadIdx.x; j < choff[a + 1]; j += 64) {
+            const int l = cleft[j];
+            all += l;
+            before += j < c ? l : 0;
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            before += __shfl_xor(before, off);
+            all += __shfl_xor(all, off);
+        }
+        if (threadIdx.x == 0) {
+            sbase[0] = before;
+            sbase[1] = all;
+            if (c == choff[a]) {
+                const int l = (int)ctl[CNN] + 2 * a, r = l + 1, lv = node[NLV * cap + v] + 1;
+                node[NF * cap + l] = f;
+                node[NF * cap + r] = f + all;
+                node[NC * cap + l] = all;
+                node[NC * cap + r] = cnt - all;
+                for (int u = l; u <= r; ++u) {
+                    node[NP * cap + u] = v;
+                    node[NLV * cap + u] = lv;
+                    node[NAX * cap + u] = -1;
+                    node[NL * cap + u] = -1;
+                    node[NR * cap + u] = -1;
+                }
+                node[NL * cap + v] = l;
+                node[NR * cap + v] = r;
+                node[NAX * cap + v] = (int)(sp[0] & 0xffull);
+            }
+        }
+    }
+    __syncthreads();
+    int bl = f + sbase[0], br = f + sbase[1] + (start - f - sbase[0]);
     const int wv = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
     for (int r0 = start; r0 < end; r0 += CB) {
@@ -344,11 +407,11 @@ __global__ __launch_bounds__(CB) void k_com_scatter(
         }
         const int rank_l = before + __popcll(bal & lt);
         if (valid) {
-            const int dst = left ? bl + rank_l : br + (threadIdx.x - rank_l);
+            const int dst = left ? bl + rank_l : br + ((int)threadIdx.x - rank_l);
 #pragma unroll
             for (int d = 0; d < 4; ++d)
-                q_tmp[d * n + dst] = q[d * n + p];
-            perm_tmp[dst] = perm[p];
+                q_out[d * n + dst] = q[d * n + p];
+            perm_out[dst] = perm[p];
         }
         const int nvalid = min(CB, end - r0);
         bl += total;
@@ -357,58 +420,9 @@ __global__ __launch_bounds__(CB) void k_com_scatter(
     }
 }
 
-__global__ __launch_bounds__(CB) void k_com_copyback(const int32_t *__restrict__ chk,
-                                                     int64_t cap_c,
-                                                     const uint32_t *__restrict__ q_tmp,
-                                                     const int32_t *__restrict__ perm_tmp,
-                                                     int64_t n, uint32_t *q, int32_t *perm)
-{
-    const int c = blockIdx.x;
-    const int start = chk[cap_c + c], end = chk[2 * cap_c + c];
-    for (int p = start + threadIdx.x; p < end; p += CB) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            q[d * n + p] = q_tmp[d * n + p];
-        perm[p] = perm_tmp[p];
-    }
-}
-
-// Per active cell a: children NN + 2a (left) and NN + 2a + 1 (right).
-__global__ __launch_bounds__(256) void k_com_children(int64_t A, const int32_t *__restrict__ act,
-                                                     const int32_t *__restrict__ nl,
-                                                     const uint64_t *__restrict__ split,
-                                                     int32_t *node, int64_t cap, int NN,
-                                                     int level, int int_off)
-{
-    const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (a >= A)
-        return;
-    const int v = act[a];
-    const int f = node[NF * cap + v], c = node[NC * cap + v];
-    const int l = NN + 2 * (int)a, r = l + 1;
-    const int nleft = nl[a];
-    const int fs[2] = {f, f + nleft}, cs[2] = {nleft, c - nleft}, ids[2] = {l, r};
-    for (int k = 0; k < 2; ++k) {
-        const int u = ids[k];
-        node[NF * cap + u] = fs[k];
-        node[NC * cap + u] = cs[k];
-        node[NP * cap + u] = v;
-        node[NLV * cap + u] = level + 1;
-        node[NAX * cap + u] = -1;
-        node[NL * cap + u] = -1;
-        node[NR * cap + u] = -1;
-        node[NIR * cap + u] = -1;
-    }
-    node[NL * cap + v] = l;
-    node[NR * cap + v] = r;
-    node[NAX * cap + v] = (int)(split[4 * a] & 0xffull);
-    node[NIR * cap + v] = int_off + (int)a;
-}
-
-// One workgroup: over the children [NN, NN + m), the next level's active cells
-// (count > leaf_size) with their chunks, and the children of >= 64 particles
-// appended to the list of large cells.  ctl[0], ctl[1] = next A, C;
-// ctl[2] += large cells.
+// One workgroup: over the children of the level's active cells, the next
+// level's active cells with their chunks, and the others appended to the cells
+// to be finished.
 constexpr int NEXT_T = 1024;
 
 __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total)
@@ -441,25 +455,26 @@ __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total)
     return ex;
 }
 
-__global__ __launch_bounds__(NEXT_T) void k_com_next(int NN, int m, int leaf_size,
-                                                    const int32_t *__restrict__ node, int64_t cap,
-                                                    int32_t *act, int64_t *choff, int32_t *chk,
-                                                    int64_t cap_c, int32_t *big, int64_t *ctl)
+__global__ __launch_bounds__(NEXT_T) void k_com_next(int level, const int32_t *__restrict__ node,
+                                                    int64_t cap, int32_t *act, int64_t *choff,
+                                                    int32_t *chk, int64_t cap_c, int32_t *ren,
+                                                    int64_t *ctl)
 {
     __shared__ int sh[NEXT_T / 64 + 1];
-    int base_a = 0, base_b = (int)ctl[2];
+    const int NN = (int)ctl[CNN], m = 2 * (int)ctl[CA];
+    int base_a = 0, base_s = (int)ctl[CS];
     int64_t base_c = 0;
     for (int k0 = 0; k0 < m; k0 += NEXT_T) {
         const int k = k0 + threadIdx.x;
         const int u = NN + k;
         const int cnt = k < m ? node[NC * cap + u] : 0;
-        const int isact = k < m && cnt > leaf_size ? 1 : 0;
+        const int isact = cnt > COM_SUB ? 1 : 0;
         const int nch = isact ? (cnt + COM_CHUNK - 1) / COM_CHUNK : 0;
-        const int isbig = k < m && cnt >= 64 ? 1 : 0;
-        int ta, tc, tb;
+        const int isfin = k < m && !isact ? 1 : 0;
+        int ta, tc, ts;
         const int pa = block_excl_scan(isact, sh, ta);
         const int pc = block_excl_scan(nch, sh, tc);
-        const int pb = block_excl_scan(isbig, sh, tb);
+        const int ps = block_excl_scan(isfin, sh, ts);
         if (isact) {
             const int ai = base_a + pa;
             const int64_t c0 = base_c + pc;
@@ -472,106 +487,346 @@ __global__ __launch_bounds__(NEXT_T) void k_com_next(int NN, int m, int leaf_siz
                 chk[2 * cap_c + c0 + j] = f + min(cnt, (j + 1) * COM_CHUNK);
             }
         }
-        if (isbig)
-            big[base_b + pb] = u;
+        if (isfin)
+            ren[RFIN * cap + base_s + ps] = u;
         base_a += ta;
         base_c += tc;
-        base_b += tb;
+        base_s += ts;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
         choff[base_a] = base_c;
-        ctl[0] = base_a;
-        ctl[1] = base_c;
-        ctl[2] = base_b;
+        if (m > 0) {
+            ren[RLEV * cap + level + 1] = NN;
+            ctl[CLEV] = level + 2;
+        }
+        ctl[CA] = base_a;
+        ctl[CC] = base_c;
+        ctl[CS] = base_s;
+        ctl[CNN] = NN + m;
     }
 }
 
-// Renumbering.  Bottom-up, one level at a time: subtree node and leaf counts.
-__global__ __launch_bounds__(256) void k_com_sizes(int b, int e, const int32_t *__restrict__ node,
-                                                  int64_t cap, int32_t *ren)
+// A node of a finished cell, in pre-order within it: first position and count,
+// distance to the right child (0: a leaf) and to the parent, axis, level, all
+// relative to the cell.
+__device__ __forceinline__ uint64_t fin_pack(int f, int c, int right, int parent, int ax, int lv)
 {
-    const int v = b + blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= e)
-        return;
-    const int l = node[NL * cap + v], r = node[NR * cap + v];
-    if (l < 0) {
-        ren[RSUB * cap + v] = 1;
-        ren[RLEAF * cap + v] = 1;
-    } else {
-        ren[RSUB * cap + v] = 1 + ren[RSUB * cap + l] + ren[RSUB * cap + r];
-        ren[RLEAF * cap + v] = ren[RLEAF * cap + l] + ren[RLEAF * cap + r];
+    return (uint64_t)f | ((uint64_t)c << 12) | ((uint64_t)right << 24) | ((uint64_t)parent << 36) |
+           ((uint64_t)ax << 48) | ((uint64_t)lv << 50);
+}
+
+// All levels below a cell of at most COM_SUB particles, one workgroup per cell.
+// A wavefront cuts one cell at a time: extents, then the sums of the chosen
+// axis, then the partition, 64 particles per round; particles move as local
+// ids, between two buffers by level.  Nodes are numbered as they appear (in an
+// order that may differ from run to run) and then in pre-order.
+constexpr int FIN_T = 1024, FIN_W = FIN_T / 64, FIN_NODES = 2 * COM_SUB;
+
+__global__ __launch_bounds__(FIN_T) void k_com_finish(
+    const uint32_t *__restrict__ q0, const int32_t *__restrict__ perm0,
+    const uint32_t *__restrict__ q1, const int32_t *__restrict__ perm1, int64_t n,
+    const int32_t *__restrict__ node, int64_t cap, int leaf_size, int32_t *ren, uint64_t *rec,
+    int32_t *perm_out, int64_t *ctl)
+{
+    __shared__ uint32_t q[4][COM_SUB];     // coordinates and weight by local id
+    __shared__ int32_t pm[COM_SUB];        // caller index by local id
+    __shared__ uint16_t idx[2][COM_SUB];   // local ids in tree order
+    __shared__ uint16_t nf[FIN_NODES], nc[FIN_NODES], nl[FIN_NODES], np[FIN_NODES];
+    __shared__ uint16_t nsub[FIN_NODES], npre[FIN_NODES];
+    __shared__ uint8_t nax[FIN_NODES];
+    __shared__ uint16_t lev[COM_SUB + 2];  // first node of each level
+    __shared__ int nn, nbig;
+    __shared__ int lcnt[COM_MAX_DEPTH];    // internal nodes per (absolute) level
+    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const uint64_t lt = lanemask_lt();
+    const int v0 = ren[RFIN * cap + blockIdx.x];
+    const int f0 = node[NF * cap + v0], c0 = node[NC * cap + v0], lv0 = node[NLV * cap + v0];
+    const uint32_t *qg = lv0 & 1 ? q1 : q0;
+    const int32_t *pg = lv0 & 1 ? perm1 : perm0;
+    for (int p = t; p < c0; p += FIN_T) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            q[d][p] = qg[d * n + f0 + p];
+        pm[p] = pg[f0 + p];
+        idx[0][p] = (uint16_t)p;
     }
-    if (v == 0) {  // the root opens the top-down pass
-        ren[RPRE * cap] = 0;
+    for (int i = t; i < COM_MAX_DEPTH; i += FIN_T)
+        lcnt[i] = 0;
+    if (t == 0) {
+        nf[0] = 0;
+        nc[0] = (uint16_t)c0;
+        np[0] = 0;
+        nn = 1;
+        nbig = 0;
+        lev[0] = 0;
+    }
+    __syncthreads();
+    int lo = 0, hi = 1, depth = 0;
+    while (lo < hi) {
+        const int par = depth & 1;
+        for (int v = lo + w; v < hi; v += FIN_W) {
+            const int f = nf[v], c = nc[v];
+            if (c <= leaf_size) {
+                for (int i = lane; i < c; i += 64)
+                    perm_out[f0 + f + i] = pm[idx[par][f + i]];
+                if (lane == 0) {
+                    nl[v] = 0;
+                    nax[v] = 0;
+                    if (c >= 64)
+                        atomicAdd(&nbig, 1);
+                }
+                continue;
+            }
+            uint32_t mn[3] = {~0u, ~0u, ~0u}, mx[3] = {0u, 0u, 0u};
+            for (int i = lane; i < c; i += 64) {
+                const int id = idx[par][f + i];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const uint32_t x = q[d][id];
+                    mn[d] = x < mn[d] ? x : mn[d];
+                    mx[d] = x > mx[d] ? x : mx[d];
+                }
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const uint32_t x = (uint32_t)__shfl_xor((int)mn[d], off);
+                    const uint32_t y = (uint32_t)__shfl_xor((int)mx[d], off);
+                    mn[d] = x < mn[d] ? x : mn[d];
+                    mx[d] = y > mx[d] ? y : mx[d];
+                }
+            int ax = 0;
+            uint32_t ext = mx[0] - mn[0];
+#pragma unroll
+            for (int d = 1; d < 3; ++d)
+                if (mx[d] - mn[d] > ext) {
+                    ax = d;
+                    ext = mx[d] - mn[d];
+                }
+            // sum w and sum w q of the axis: w q < 2^56, 2^11 terms, summed in
+            // two halves
+            uint64_t sw = 0, sl = 0, sh = 0;
+            for (int i = lane; i < c; i += 64) {
+                const int id = idx[par][f + i];
+                const uint64_t wt = q[3][id], p = wt * (uint64_t)q[ax][id];
+                sw += wt;
+                sl += p & 0xffffffffull;
+                sh += p >> 32;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                sw += __shfl_xor((unsigned long long)sw, off);
+                sl += __shfl_xor((unsigned long long)sl, off);
+                sh += __shfl_xor((unsigned long long)sh, off);
+            }
+            uint64_t wql = sh << 32, wqh = sh >> 32;
+            add128(wql, wqh, sl, 0ull);
+            auto left_of = [&](int i, int id) {
+                return ext == 0u ? i < (c + 1) / 2 : left_of_cut(q[ax][id], sw, wql, wqh);
+            };
+            int left = 0;
+            for (int i0 = 0; i0 < c; i0 += 64) {
+                const int i = i0 + lane;
+                left += __popcll(__ballot(i < c && left_of(i, idx[par][f + min(i, c - 1)])));
+            }
+            int bl = 0;
+            for (int i0 = 0; i0 < c; i0 += 64) {
+                const int i = i0 + lane;
+                const int id = idx[par][f + min(i, c - 1)];
+                const uint64_t bal = __ballot(i < c && left_of(i, id));
+                const int rank = bl + __popcll(bal & lt);
+                if (i < c)
+                    idx[par ^ 1][f + ((bal >> lane) & 1ull ? rank : left + i - rank)] =
+                        (uint16_t)id;
+                bl += __popcll(bal);
+            }
+            if (lane == 0) {
+                const int u = atomicAdd(&nn, 2);
+                nl[v] = (uint16_t)u;
+                nax[v] = (uint8_t)ax;
+                nf[u] = (uint16_t)f;
+                nc[u] = (uint16_t)left;
+                nf[u + 1] = (uint16_t)(f + left);
+                nc[u + 1] = (uint16_t)(c - left);
+                np[u] = np[u + 1] = (uint16_t)v;
+                if (c >= 64)
+                    atomicAdd(&nbig, 1);
+                if (lv0 + depth < COM_MAX_DEPTH)
+                    atomicAdd(&lcnt[lv0 + depth], 1);
+            }
+        }
+        __syncthreads();
+        lo = hi;
+        hi = nn;
+        ++depth;
+        if (t == 0)
+            lev[depth] = (uint16_t)lo;
+        __syncthreads();
+    }
+    // subtree sizes from the deepest level up, pre-order ids from the root down
+    for (int l = depth - 1; l >= 0; --l) {
+        for (int v = lev[l] + t; v < lev[l + 1]; v += FIN_T)
+            nsub[v] = nl[v] ? (uint16_t)(1 + nsub[nl[v]] + nsub[nl[v] + 1]) : (uint16_t)1;
+        __syncthreads();
+    }
+    if (t == 0)
+        npre[0] = 0;
+    __syncthreads();
+    for (int l = 0; l < depth; ++l) {
+        for (int v = lev[l] + t; v < lev[l + 1]; v += FIN_T) {
+            const int u = nl[v], P = npre[v];
+            if (u) {
+                npre[u] = (uint16_t)(P + 1);
+                npre[u + 1] = (uint16_t)(P + 1 + nsub[u]);
+            }
+            rec[2 * (int64_t)f0 + P] =
+                fin_pack(nf[v], nc[v], u ? 1 + nsub[u] : 0, P - npre[np[v]], nax[v], l);
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        ren[RSUB * cap + v0] = nsub[0];
+        atomicMax((unsigned long long *)&ctl[CDEP], (unsigned long long)(lv0 + depth));
+        atomicAdd((unsigned long long *)&ctl[CNBIG], (unsigned long long)nbig);
+    }
+    for (int i = t; i < COM_MAX_DEPTH; i += FIN_T)
+        if (lcnt[i])
+            atomicAdd((unsigned long long *)&ctl[CLVL + i], (unsigned long long)lcnt[i]);
+}
+
+// One workgroup: subtree sizes of the cells above the finished ones from the
+// deepest level up, then pre-order ids and leaf offsets from the root down (a
+// subtree of k nodes has (k + 1) / 2 leaves).
+__global__ __launch_bounds__(1024) void k_com_number(int32_t *node, int64_t cap, int32_t *ren,
+                                                     int64_t *ctl)
+{
+    const int nlev = (int)ctl[CLEV], NN = (int)ctl[CNN], t = threadIdx.x;
+    auto first_of = [&](int l) { return l < nlev ? ren[RLEV * cap + l] : NN; };
+    for (int l = nlev - 1; l >= 0; --l) {
+        for (int v = first_of(l) + t; v < first_of(l + 1); v += 1024) {
+            const int a = node[NL * cap + v], b = node[NR * cap + v];
+            if (a >= 0) {
+                ren[RSUB * cap + v] = 1 + ren[RSUB * cap + a] + ren[RSUB * cap + b];
+                atomicAdd((unsigned long long *)&ctl[CNBIG], 1ull);
+                if (l < COM_MAX_DEPTH)
+                    atomicAdd((unsigned long long *)&ctl[CLVL + l], 1ull);
+            }
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        node[NPRE * cap] = 0;
         ren[RLOFS * cap] = 0;
+        ctl[CTOT] = ren[RSUB * cap];
+        ctl[CLEAF] = (ren[RSUB * cap] + 1) / 2;
+    }
+    __syncthreads();
+    for (int l = 0; l < nlev; ++l) {
+        for (int v = first_of(l) + t; v < first_of(l + 1); v += 1024) {
+            const int a = node[NL * cap + v], b = node[NR * cap + v];
+            if (a >= 0) {
+                const int P = node[NPRE * cap + v], o = ren[RLOFS * cap + v];
+                const int sa = ren[RSUB * cap + a];
+                node[NPRE * cap + a] = P + 1;
+                node[NPRE * cap + b] = P + 1 + sa;
+                ren[RLOFS * cap + a] = o;
+                ren[RLOFS * cap + b] = o + (sa + 1) / 2;
+            }
+        }
+        __syncthreads();
     }
 }
 
-// Top-down, one level at a time: pre-order ids and leaf offsets of the
-// children (left subtree first).
-__global__ __launch_bounds__(256) void k_com_pre(int b, int e, const int32_t *__restrict__ node,
-                                                int64_t cap, int32_t *ren)
+// The topology arrays at the pre-order ids, the list of large cells, and the
+// sort keys of the internal cells by level (leaves last).  Workgroups 0 ..
+// nfin - 1: the nodes of a finished cell, the others: the cells above.
+struct ComOut {
+    int32_t *first, *count, *left, *right, *parent, *level, *axis, *node_leaf, *leaf_node, *big;
+    uint32_t *key, *val;
+};
+
+__device__ __forceinline__ void com_emit(const ComOut &O, int P, int f, int c, int left, int right,
+                                         int parent, int lv, int ax, int leaf, int64_t *ctl)
 {
-    const int v = b + blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= e)
-        return;
-    const int l = node[NL * cap + v], r = node[NR * cap + v];
-    if (l < 0)
-        return;
-    const int pv = ren[RPRE * cap + v], ov = ren[RLOFS * cap + v];
-    ren[RPRE * cap + l] = pv + 1;
-    ren[RPRE * cap + r] = pv + 1 + ren[RSUB * cap + l];
-    ren[RLOFS * cap + l] = ov;
-    ren[RLOFS * cap + r] = ov + ren[RLEAF * cap + l];
+    O.first[P] = f;
+    O.count[P] = c;
+    O.left[P] = left;
+    O.right[P] = right;
+    O.parent[P] = parent;
+    O.level[P] = lv;
+    O.axis[P] = ax;
+    O.node_leaf[P] = leaf;
+    if (leaf >= 0)
+        O.leaf_node[leaf] = P;
+    O.key[P] = leaf >= 0 ? 255u : (uint32_t)min(lv, 254);
+    O.val[P] = (uint32_t)P;
+    if (c >= 64)
+        O.big[atomicAdd((unsigned long long *)&ctl[CBIG], 1ull)] = P;
 }
 
-// Per BFS node: the topology arrays at its pre-order id.
-__global__ __launch_bounds__(256) void k_com_emit(int NN, const int32_t *__restrict__ node,
+__global__ __launch_bounds__(256) void k_com_emit(int nfin, const int32_t *__restrict__ node,
                                                  int64_t cap, const int32_t *__restrict__ ren,
-                                                 int32_t *first, int32_t *count, int32_t *left,
-                                                 int32_t *right, int32_t *parent, int32_t *level,
-                                                 int32_t *axis, int32_t *node_leaf,
-                                                 int32_t *leaf_node, int32_t *int_nodes)
+                                                 const uint64_t *__restrict__ rec, ComOut O,
+                                                 int64_t *ctl)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= NN)
+    const int t = threadIdx.x;
+    if ((int)blockIdx.x >= nfin) {
+        const int NN = (int)ctl[CNN];
+        for (int v = ((int)blockIdx.x - nfin) * 256 + t; v < NN;
+             v += ((int)gridDim.x - nfin) * 256) {
+            const int a = node[NL * cap + v], b = node[NR * cap + v], pa = node[NP * cap + v];
+            if (a >= 0)
+                com_emit(O, node[NPRE * cap + v], node[NF * cap + v], node[NC * cap + v],
+                         node[NPRE * cap + a], node[NPRE * cap + b],
+                         pa >= 0 ? node[NPRE * cap + pa] : -1, node[NLV * cap + v],
+                         node[NAX * cap + v], -1, ctl);
+        }
         return;
-    const int P = ren[RPRE * cap + v];
-    const int l = node[NL * cap + v], r = node[NR * cap + v], pa = node[NP * cap + v];
-    first[P] = node[NF * cap + v];
-    count[P] = node[NC * cap + v];
-    left[P] = l >= 0 ? ren[RPRE * cap + l] : -1;
-    right[P] = r >= 0 ? ren[RPRE * cap + r] : -1;
-    parent[P] = pa >= 0 ? ren[RPRE * cap + pa] : -1;
-    level[P] = node[NLV * cap + v];
-    axis[P] = node[NAX * cap + v];
-    if (l < 0) {
-        const int lf = ren[RLOFS * cap + v];
-        node_leaf[P] = lf;
-        leaf_node[lf] = P;
-    } else {
-        node_leaf[P] = -1;
-        int_nodes[node[NIR * cap + v]] = P;
     }
-}
-
-__global__ __launch_bounds__(256) void k_com_bigmap(int nbig, const int32_t *__restrict__ bigbfs,
-                                                   const int32_t *__restrict__ ren, int64_t cap,
-                                                   int32_t *big_nodes)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nbig)
-        big_nodes[k] = ren[RPRE * cap + bigbfs[k]];
+    __shared__ int wl[4];
+    const int v = ren[RFIN * cap + blockIdx.x];
+    const int P0 = node[NPRE * cap + v], f0 = node[NF * cap + v], lv0 = node[NLV * cap + v];
+    const int pa = node[NP * cap + v], k = ren[RSUB * cap + v];
+    int lofs = ren[RLOFS * cap + v];
+    const uint64_t *r = rec + 2 * (int64_t)f0;
+    for (int i0 = 0; i0 < k; i0 += 256) {
+        const int i = i0 + t;
+        const uint64_t x = i < k ? r[i] : 0ull;
+        const int right = (int)(x >> 24) & 0xfff, up = (int)(x >> 36) & 0xfff;
+        const bool leaf = i < k && right == 0;
+        const uint64_t bal = __ballot(leaf);
+        if (lane_id() == 0)
+            wl[t >> 6] = __popcll(bal);
+        __syncthreads();
+        int before = 0, total = 0;
+        for (int w = 0; w < 4; ++w) {
+            before += w < (t >> 6) ? wl[w] : 0;
+            total += wl[w];
+        }
+        if (i < k) {
+            const int P = P0 + i;
+            com_emit(O, P, f0 + (int)(x & 0xfff), (int)(x >> 12) & 0xfff, leaf ? -1 : P + 1,
+                     leaf ? -1 : P + right, i ? P - up : (pa >= 0 ? node[NPRE * cap + pa] : -1),
+                     lv0 + (int)(x >> 50), leaf ? -1 : (int)(x >> 48) & 3,
+                     leaf ? lofs + before + __popcll(bal & lanemask_lt()) : -1, ctl);
+        }
+        lofs += total;
+        __syncthreads();
+    }
 }
 
 static hipError_t read_ctl(Tree &t, hipStream_t s)
 {
-    hipError_t e = hipMemcpyAsync(t.cw.h_ctl, t.cw.ctl, 8 * sizeof(int64_t),
+    hipError_t e = hipMemcpyAsync(t.cw.h_ctl, t.cw.ctl, COM_CTL * sizeof(int64_t),
                                   hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     return e;
 }
+
+int64_t com_max_active(int64_t n) { return n / (COM_SUB + 1) + 1; }
 
 hipError_t launch_build_com(Tree &t, const double *x, const double *m, hipStream_t s)
 {
@@ -582,70 +837,62 @@ hipError_t launch_build_com(Tree &t, const double *x, const double *m, hipStream
     if (e != hipSuccess)
         return e;
     const int gs = (int)std::min<int64_t>((n + 255) / 256, 2048);
-    k_com_zero<<<1, 64, 0, s>>>(W.ctl);
+    // cells of even levels lie in the first buffer, of odd levels in the second
+    uint32_t *Q[2] = {W.q, W.q_tmp};
+    int32_t *perm[2] = {W.perm_tmp, W.perm_tmp + n};
+    k_com_zero<<<1, COM_CTL, 0, s>>>(W.ctl);
     if (m)
-        k_com_mmax<<<gs, 256, 0, s>>>(m, n, W.ctl);
-    k_com_init<<<gs, 256, 0, s>>>(x, m, n, t.bbox, W.ctl, t.vals0, t.perm, W.q);
-    k_com_root<<<1, 256, 0, s>>>(n, T.leaf_size, W.node, cap, W.act[0], W.act_choff[0], W.chk[0],
-                                 cap_c, W.big, W.ctl);
-    if ((e = read_ctl(t, s)) != hipSuccess)
-        return e;
-    int64_t A = W.h_ctl[0], C = W.h_ctl[1];
-    int NN = 1, level = 0, int_off = 0, cur = 0;
-    W.lev_off.assign({0, 1});
-    T.lvl_int_off.assign(1, 0);
-    while (A > 0) {
-        if (A > W.cap_a || C > cap_c || NN + 2 * A > cap)
-            return hipErrorInvalidValue;  // impossible by the capacity bounds
-        const int ga = (int)((A + 255) / 256);
-        k_com_stats<<<(int)C, CB, 0, s>>>(W.q, n, W.chk[cur], cap_c, W.cpart);
-        k_com_split<<<ga, 256, 0, s>>>(A, W.act_choff[cur], W.cpart, W.split);
-        k_com_count<<<(int)C, CB, 0, s>>>(W.q, n, W.chk[cur], cap_c, W.act[cur], W.node, cap,
-                                          W.split, W.cleft);
-        k_com_offsets<<<ga, 256, 0, s>>>(A, W.act_choff[cur], W.chk[cur], cap_c, W.cleft,
-                                         W.cbase, W.nl);
-        k_com_scatter<<<(int)C, CB, 0, s>>>(W.q, t.perm, n, W.chk[cur], cap_c, W.act[cur],
-                                            W.node, cap, W.split, W.cleft, W.cbase, W.nl,
-                                            W.q_tmp, W.perm_tmp);
-        k_com_copyback<<<(int)C, CB, 0, s>>>(W.chk[cur], cap_c, W.q_tmp, W.perm_tmp, n, W.q,
-                                             t.perm);
-        k_com_children<<<ga, 256, 0, s>>>(A, W.act[cur], W.nl, W.split, W.node, cap, NN, level,
-                                          int_off);
-        k_com_next<<<1, NEXT_T, 0, s>>>(NN, (int)(2 * A), T.leaf_size, W.node, cap,
-                                        W.act[cur ^ 1], W.act_choff[cur ^ 1], W.chk[cur ^ 1],
-                                        cap_c, W.big, W.ctl);
+        k_com_mmax<<<std::min(gs, 256), 256, 0, s>>>(m, n, W.ctl);
+    k_com_init<<<gs, 256, 0, s>>>(x, m, n, t.bbox, W.ctl, t.vals0, perm[0], Q[0]);
+    k_com_root<<<1, 256, 0, s>>>(n, W.node, cap, W.act[0], W.act_choff[0], W.chk[0], cap_c, W.ren,
+                                 W.ctl);
+    // levels that a balanced tree has above the finished cells, and one more
+    int batch = n > COM_SUB ? 1 : 0;
+    while (batch && (n >> batch) > COM_SUB)
+        ++batch;
+    batch = batch ? batch + 1 : 0;
+    int level = 0;
+    do {
+        for (; batch > 0; --batch, ++level) {
+            const int cur = level & 1;
+            const int64_t acts =
+                std::min<int64_t>(level < 30 ? 1ll << level : W.cap_a, com_max_active(n));
+            const int C = (int)std::min<int64_t>(n / COM_CHUNK + acts, cap_c);
+            k_com_stats<<<C, CB, 0, s>>>(Q[cur], n, W.chk[cur], cap_c, W.cpart, W.ctl);
+            k_com_count<<<C, CB, 0, s>>>(Q[cur], n, W.chk[cur], cap_c, W.act[cur],
+                                         W.act_choff[cur], W.node, cap, W.cpart, W.split, W.cleft,
+                                         W.ctl);
+            k_com_scatter<<<C, CB, 0, s>>>(Q[cur], perm[cur], n, W.chk[cur], cap_c, W.act[cur],
+                                           W.act_choff[cur], W.node, cap, W.split, W.cleft,
+                                           Q[cur ^ 1], perm[cur ^ 1], W.ctl);
+            k_com_next<<<1, NEXT_T, 0, s>>>(level, W.node, cap, W.act[cur ^ 1],
+                                            W.act_choff[cur ^ 1], W.chk[cur ^ 1], cap_c, W.ren,
+                                            W.ctl);
+        }
         if ((e = read_ctl(t, s)) != hipSuccess)
             return e;
-        int_off += (int)A;
-        T.lvl_int_off.push_back(int_off);
-        NN += (int)(2 * A);
-        W.lev_off.push_back(NN);
-        ++level;
-        A = W.h_ctl[0];
-        C = W.h_ctl[1];
-        cur ^= 1;
-    }
-    const int depth = level + 1;
-    T.lvl_int_off.push_back(int_off);  // the deepest level holds leaves only
-    const int nbig = (int)W.h_ctl[2];
-    for (int l = depth - 1; l >= 0; --l) {
-        const int b = W.lev_off[l], en = W.lev_off[l + 1];
-        k_com_sizes<<<(en - b + 255) / 256, 256, 0, s>>>(b, en, W.node, cap, W.ren);
-    }
-    for (int l = 0; l + 1 < depth; ++l) {
-        const int b = W.lev_off[l], en = W.lev_off[l + 1];
-        k_com_pre<<<(en - b + 255) / 256, 256, 0, s>>>(b, en, W.node, cap, W.ren);
-    }
-    k_com_emit<<<(NN + 255) / 256, 256, 0, s>>>(NN, W.node, cap, W.ren, t.first, t.count, t.left,
-                                               t.right, t.parent, t.level, t.axis, t.node_leaf,
-                                               t.leaf_node, t.int_nodes);
-    if (nbig > 0)
-        k_com_bigmap<<<(nbig + 255) / 256, 256, 0, s>>>(nbig, W.big, W.ren, cap, t.big_nodes);
-    T.nnodes = NN;
-    T.nleaves = NN - int_off;
-    T.depth = depth;
-    T.nbig = nbig;
-    return hipGetLastError();
+        batch = 1;
+    } while (W.h_ctl[CA] > 0);
+    const int nfin = (int)W.h_ctl[CS], ntop = (int)W.h_ctl[CNN];
+    k_com_finish<<<nfin, FIN_T, 0, s>>>(Q[0], perm[0], Q[1], perm[1], n, W.node, cap, T.leaf_size,
+                                        W.ren, W.rec, t.perm, W.ctl);
+    k_com_number<<<1, 1024, 0, s>>>(W.node, cap, W.ren, W.ctl);
+    uint32_t *key = (uint32_t *)t.keys0, *val = (uint32_t *)t.keys1;
+    const ComOut O = {t.first, t.count, t.left, t.right, t.parent, t.level, t.axis, t.node_leaf,
+                      t.leaf_node, t.big_nodes, key, val};
+    const int top_blocks = std::min((ntop + 255) / 256, 256);
+    k_com_emit<<<nfin + top_blocks, 256, 0, s>>>(nfin, W.node, cap, W.ren, W.rec, O, W.ctl);
+    if ((e = read_ctl(t, s)) != hipSuccess)
+        return e;
+    T.nnodes = (int)W.h_ctl[CTOT];
+    T.nleaves = (int)W.h_ctl[CLEAF];
+    T.depth = (int)W.h_ctl[CDEP];
+    T.nbig = (int)W.h_ctl[CNBIG];
+    T.lvl_int_off.assign(1, 0);
+    for (int l = 0; l < T.depth && l < COM_MAX_DEPTH; ++l)
+        T.lvl_int_off.push_back(T.lvl_int_off.back() + (int)W.h_ctl[CLVL + l]);
+    return radix_sort_u32(key, val, key + cap, (uint32_t *)t.int_nodes, T.nnodes, 1, 1, t.rs_hist,
+                          t.rs_tot, s, 8);
 }
 
 }  // namespace fmm

@@ -31,6 +31,7 @@ constexpr int RS_PASSES = 8;
 constexpr int MAX_LEAF = 64;
 constexpr int COM_CHUNK = 4096;  // particles per chunk of the centre-of-mass build
 constexpr int COM_MAX_DEPTH = 64; // deepest centre-of-mass tree accepted (walk stacks)
+constexpr int COM_CTL = 128;      // control words of its build
 constexpr int NREC = 8;   // doubles per node record (geometry / quadrupole)
 // Geometry record (recA) of a node: centre of mass 0..2, mass 3, size s 4,
 // h_max 5; slot 6 holds the child ids (left in the low 32 bits, right in the
@@ -340,23 +341,21 @@ struct Tree {
 
     // centre-of-mass tree build (FMM_TREE_COM)
     struct ComWork {
-        uint32_t *q = nullptr, *q_tmp = nullptr;   // [4][n]: q0, q1, q2, w in tree order
+        // quantised particles [4][n] (q0, q1, q2, w) in tree order, two buffers;
+        // caller indices [2][n]
+        uint32_t *q = nullptr, *q_tmp = nullptr;
         int32_t *perm_tmp = nullptr;
-        int32_t *node = nullptr;   // [8][node_cap] BFS: first, count, parent, level, axis,
-                                   // left, right, internal rank
-        int32_t *ren = nullptr;    // [4][node_cap] subtree nodes, leaves, pre-order id, leaf offset
-        int32_t *act[2] = {nullptr, nullptr};     // active BFS ids per level
+        int32_t *node = nullptr;   // [8][node_cap] cells above the ones finished in LDS
+        int32_t *ren = nullptr;    // [4][node_cap] their renumbering
+        uint64_t *rec = nullptr;   // 2 n nodes of the finished cells, packed
+        int32_t *act[2] = {nullptr, nullptr};     // active cells per level
         int64_t *act_choff[2] = {nullptr, nullptr};
         int32_t *chk[2] = {nullptr, nullptr};     // [3][cap_c]: active index, start, end
         uint64_t *cpart = nullptr;                 // 16 per chunk
-        int32_t *cleft = nullptr;                  // left count per chunk, then its base
-        int32_t *cbase = nullptr;                  // right base per chunk
-        uint64_t *split = nullptr;                 // 4 per active node: axis|flag, sw, swq lo, hi
-        int32_t *nl = nullptr;                     // left count per active node
-        int32_t *big = nullptr;                    // BFS ids of nodes of >= 64 particles
-        int64_t *ctl = nullptr, *h_ctl = nullptr;  // next level's A, C; big count; m_max bits
+        int32_t *cleft = nullptr;                  // left count per chunk
+        uint64_t *split = nullptr;                 // 4 per active cell: axis|flag, sw, swq lo, hi
+        int64_t *ctl = nullptr, *h_ctl = nullptr;  // COM_CTL control words
         int64_t cap_a = 0, cap_c = 0;
-        std::vector<int32_t> lev_off;              // BFS id range per level
     } cw;
     int64_t s2part_depth = 0;       // levels the s^2 partial buffer holds
     int64_t slots_nl = 0;           // leaves the list slots were allocated for
@@ -488,6 +487,7 @@ hipError_t launch_far_mutual(Tree &t, hipStream_t s);
 hipError_t launch_l2l_internal(Tree &t, hipStream_t s);
 hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStream_t s);
 hipError_t ensure_transposed(Tree &t, hipStream_t s);
+int64_t com_max_active(int64_t n);  // active cells of a level of the centre-of-mass build
 void release_vjp(Tree &t);
 hipError_t launch_asym(Tree &t, double m_leaf, double *out, hipStream_t s);
 void release_asym(Tree &t);
