@@ -68,6 +68,62 @@ __device__ __forceinline__ double rsqrt_pos(double x)
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
+// Gather of 64-byte records by the four lanes of a quad.  A lane that reads its
+// own record part by part makes an L1 lookup of its own per 16 bytes; here the
+// quad reads one record together (one lookup), four times, and the parts change
+// lanes in registers (a 4 x 4 transposition over the quad).  All four lanes must
+// be active, with a valid record each.
+template <int CTRL>
+__device__ __forceinline__ int quad_perm(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+
+template <int CTRL>
+__device__ __forceinline__ int4 quad_perm4(const int4 &x)
+{
+    return make_int4(quad_perm<CTRL>(x.x), quad_perm<CTRL>(x.y), quad_perm<CTRL>(x.z),
+                     quad_perm<CTRL>(x.w));
+}
+
+__device__ __forceinline__ int4 sel4(bool c, const int4 &a, const int4 &b)
+{
+    return make_int4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
+}
+
+struct QuadRecord {
+    int4 v0, v1, v2, v3;
+    // the loads: part (lane & 3) of the quad's four records
+    __device__ __forceinline__ void fetch(const void *base, int rec)
+    {
+        const int4 *p = (const int4 *)base + (lane_id() & 3);
+        v0 = p[4 * (int64_t)quad_perm<0x00>(rec)];
+        v1 = p[4 * (int64_t)quad_perm<0x55>(rec)];
+        v2 = p[4 * (int64_t)quad_perm<0xaa>(rec)];
+        v3 = p[4 * (int64_t)quad_perm<0xff>(rec)];
+    }
+    // this lane's record
+    __device__ __forceinline__ void parts(int4 &o0, int4 &o1, int4 &o2, int4 &o3) const
+    {
+        const bool odd = lane_id() & 1, hi = lane_id() & 2;
+        // with the neighbour: both parts of a pair of parts
+        const int4 r = quad_perm4<0xb1>(sel4(odd, v0, v1)), s = quad_perm4<0xb1>(sel4(odd, v2, v3));
+        const int4 a0 = sel4(odd, r, v0), a1 = sel4(odd, v1, r);
+        const int4 b0 = sel4(odd, s, v2), b1 = sel4(odd, v3, s);
+        // with the lane two away: the other pair
+        const int4 p = quad_perm4<0x4e>(sel4(hi, a0, b0)), q = quad_perm4<0x4e>(sel4(hi, a1, b1));
+        o0 = sel4(hi, p, a0);
+        o1 = sel4(hi, q, a1);
+        o2 = sel4(hi, b0, p);
+        o3 = sel4(hi, b1, q);
+    }
+};
+
+__device__ __forceinline__ double2 as_double2(const int4 &x)
+{
+    return make_double2(__hiloint2double(x.y, x.x), __hiloint2double(x.w, x.z));
+}
+
 // L2P, eq. (8)
 template <typename T>
 __device__ __forceinline__ void l2p(const T *L, T y0, T y1, T y2, T &a0, T &a1, T &a2)
@@ -266,7 +322,7 @@ struct Tree {
 
     // nodes
     double *recA = nullptr;       // per node: cx, cy, cz, M, s, hmax, 0, 0
-    double *recQ = nullptr;       // per node: Qxx, Qxy, Qxz, Qyy, Qyz, Qzz, 0, 0
+    double *recQ = nullptr;       // per node: Qxx, Qxy, Qxz, Qyy, Qyz, Qzz, c_z, M
     float *recF = nullptr;        // per node FP32 mirror: M, Q[6], 0
     double *lbox = nullptr;       // LBOX per leaf: bounding box of its particles (centre,
                                   // half widths), their largest 4 h^2, 0

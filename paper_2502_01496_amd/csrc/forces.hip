@@ -160,12 +160,13 @@ __device__ __forceinline__ void m2l_acc(T rx, T ry, T rz, T M, const T *Q, T *L)
 //   L3_ijk = r_i P_jk + r_j P_ik + r_k P_ij + d_ij w_k + d_ik w_j + d_jk w_i,
 //   w = s + a1/2 r,
 // and the terms with d_ij (a0 and w) are summed apart and added at the end:
-// 120 FP64 instructions per source instead of 190.  The leaf M2L is bound by
-// its record loads as much as by these (five 16-byte loads per lane and
-// source, each of its own cache line), so a third fewer instructions give
-// 218 -> 205 us (binary, 2^19 particles) and 2.09 -> 2.00 ms (clumpy cube,
-// 2^22).  Reading the records by neighbouring lanes together and passing them
-// on through LDS spills here and took 388 us (2^19).
+// 120 FP64 instructions per source instead of 190.  With the source's record
+// read part by part (an L1 lookup per lane and 16 bytes, 5.2 per source, which
+// bounded the leaf M2L) they gave 218 -> 205 us (binary, 2^19 particles) and
+// 2.09 -> 2.00 ms (clumpy cube, 2^22), with the gather by quads (2 lookups per
+// source) 181 us and 1.63 ms.  The plain FP64 sums (1.66 -> 1.85 ms for Plummer,
+// 2^19) and the FP32 form (164 -> 169 us, binary) are not faster with it: they
+// are bound by their arithmetic, and the parts in flight cost a wavefront.
 struct M2lSum64 {
     double l1[3], l2[6], l3[10], a0, w[3];
     __device__ __forceinline__ void clear()
@@ -395,11 +396,37 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
                 m2l_src_eval<FORM>(cur, c0, c1, c2, L);
                 cur = nxt;
             }
+        } else if constexpr (REGROUP) {
+            // the next source's record and the index after it are in flight.
+            // All lanes of a unit stay in the loop (the gather needs whole
+            // quads): a lane past the piece's end reads the root's record and
+            // adds nothing
+            M2lSum64 S;
+            S.clear();
+            const double2 *A2 = (const double2 *)recA;
+            const int b0 = p0 + sub < p1 ? fl[p0 + sub] : 0;
+            QuadRecord rec;
+            rec.fetch(recQ, b0);
+            double2 cn = A2[NREC / 2 * (int64_t)b0];
+            int bn = p0 + sub + M2L_LANES < p1 ? fl[p0 + sub + M2L_LANES] : 0;
+            for (int k0 = p0; k0 < p1; k0 += M2L_LANES) {
+                int4 i0, i1, i2, i3;
+                rec.parts(i0, i1, i2, i3);
+                const double2 cxy = cn;
+                if (k0 + M2L_LANES < p1) {
+                    rec.fetch(recQ, bn);
+                    cn = A2[NREC / 2 * (int64_t)bn];
+                    bn = k0 + sub + 2 * M2L_LANES < p1 ? fl[k0 + sub + 2 * M2L_LANES] : 0;
+                }
+                const double2 q01 = as_double2(i0), q23 = as_double2(i1), q45 = as_double2(i2),
+                              czm = as_double2(i3);
+                const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+                if (k0 + sub < p1)
+                    S.add(c0 - cxy.x, c1 - cxy.y, c2 - czm.x, czm.y, Q);
+            }
+            S.total(L);
         } else {
             // the next source's index is loaded one interaction ahead
-            [[maybe_unused]] M2lSum64 S;
-            if constexpr (REGROUP)
-                S.clear();
             int bn = p0 + sub < p1 ? fl[p0 + sub] : 0;
             for (int k = p0 + sub; k < p1; k += M2L_LANES) {
                 const int b = bn;
@@ -410,13 +437,8 @@ __global__ __launch_bounds__(256) void k_m2l_leaf(
                 const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
                               q45 = *(const double2 *)(qb + 4);
                 const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
-                if constexpr (REGROUP)
-                    S.add(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q);
-                else
-                    m2l_acc<double, FORM>(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q, L);
+                m2l_acc<double, FORM>(c0 - cb.x, c1 - cb.y, c2 - cb.z, cb.w, Q, L);
             }
-            if constexpr (REGROUP)
-                S.total(L);
         }
 #pragma unroll
         for (int off = M2L_LANES / 2; off >= 1; off >>= 1)

@@ -184,6 +184,8 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
     double *rq = recQ + (int64_t)NREC * v;
     for (int k = 0; k < 6; ++k)
         rq[k] = Q[k];
+    rq[6] = c2;  // beside the quadrupole: what the FP64 far field reads with it
+    rq[7] = M;
     outA[0] = c0;
     outA[1] = c1;
     outA[2] = c2;
@@ -249,6 +251,8 @@ __device__ __forceinline__ void store_rec(double *recA, double *recQ, int p, con
     double *rq = recQ + (int64_t)NREC * p;
     for (int j = 0; j < 6; ++j)
         rq[j] = q[j];
+    rq[6] = a[2];
+    rq[7] = a[3];
 }
 
 __global__ __launch_bounds__(256) void k_combine_level(const int32_t *__restrict__ nodes, int cnt,
@@ -603,7 +607,8 @@ __global__ void k_import_records(int nnodes, const double *__restrict__ rec12,
         ra[REC_LEAF] = __longlong_as_double((long long)(uint64_t)(uint32_t)node_leaf[v]);
         for (int k = 0; k < 6; ++k)
             rq[k] = r[6 + k];
-        rq[6] = rq[7] = 0.0;
+        rq[6] = ra[2];
+        rq[7] = ra[3];
         if (want_fp32) {
             float *rf = recF + (int64_t)NREC * v;
             rf[0] = (float)r[0];

@@ -619,10 +619,10 @@ __global__ __launch_bounds__(256) void k_vjp_l2p(const double4 *__restrict__ pm,
 
 // 2a. M2L^T, sink side: 16 lanes per leaf over its far list, cbar_sink += rbar
 // (of the third order only for eq. (6)'s form, step 1 has the others: 150
-// instead of 310 instructions per pair).  The loads of the source records, one
-// L1 lookup per lane and 16 bytes, bound it: 290 -> 230 us (binary, 2^19
-// particles, 2.1e7 pairs), 2.19 -> 1.47 ms (Plummer, 2^19, 1.6e8 pairs).
-constexpr int M2LT_LANES = 16;  // lanes per sink leaf (8 lanes: 232 us, 1.51 ms)
+// instead of 310 instructions per pair).  290 -> 230 us (binary, 2^19 particles,
+// 2.1e7 pairs), bound by the L1 lookups of the source records then, and 197 us
+// with their gather by quads.
+constexpr int M2LT_LANES = 16;  // lanes per sink leaf (8 lanes: 232 against 230 us)
 
 template <int FORM, bool F32>
 __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
@@ -650,20 +650,43 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_sink(
     double rb[3] = {0.0, 0.0, 0.0};
     const int nk = valid ? max(0, min(far_cnt[g], cap_far)) : 0;
     const int32_t *fl = far_src + (int64_t)(valid ? g : 0) * cap_far;
-    int bn = sub < nk ? fl[sub] : 0;
-    for (int k = sub; k < nk; k += M2LT_LANES) {
-        const int b = bn;
-        if (k + M2LT_LANES < nk)
-            bn = fl[k + M2LT_LANES];
-        const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
-        const double *qb = recQ + (int64_t)NREC * b;
-        const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
-                      q45 = *(const double2 *)(qb + 4);
-        const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
-        const double r[3] = {c0 - cb.x, c1 - cb.y, c2 - cb.z};
-        if constexpr (vjp_regrouped<FORM, F32>) {
-            m2l_vjp_third(r, cb.w, Q, Lb + 9, t1, rb);
-        } else {
+    if constexpr (vjp_regrouped<FORM, F32>) {
+        // gathered by quads, the next source's record and the index after it in
+        // flight, as in the forward sums
+        const double2 *A2 = (const double2 *)recA;
+        const int b0 = sub < nk ? fl[sub] : 0;
+        QuadRecord rec;
+        rec.fetch(recQ, b0);
+        double2 cn = A2[NREC / 2 * (int64_t)b0];
+        int bn = sub + M2LT_LANES < nk ? fl[sub + M2LT_LANES] : 0;
+        for (int k0 = 0; k0 < nk; k0 += M2LT_LANES) {
+            int4 i0, i1, i2, i3;
+            rec.parts(i0, i1, i2, i3);
+            const double2 cxy = cn;
+            if (k0 + M2LT_LANES < nk) {
+                rec.fetch(recQ, bn);
+                cn = A2[NREC / 2 * (int64_t)bn];
+                bn = k0 + sub + 2 * M2LT_LANES < nk ? fl[k0 + sub + 2 * M2LT_LANES] : 0;
+            }
+            const double2 q01 = as_double2(i0), q23 = as_double2(i1), q45 = as_double2(i2),
+                          czm = as_double2(i3);
+            const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+            const double r[3] = {c0 - cxy.x, c1 - cxy.y, c2 - czm.x};
+            if (k0 + sub < nk)
+                m2l_vjp_third(r, czm.y, Q, Lb + 9, t1, rb);
+        }
+    } else {
+        int bn = sub < nk ? fl[sub] : 0;
+        for (int k = sub; k < nk; k += M2LT_LANES) {
+            const int b = bn;
+            if (k + M2LT_LANES < nk)
+                bn = fl[k + M2LT_LANES];
+            const double4 cb = *(const double4 *)(recA + (int64_t)NREC * b);
+            const double *qb = recQ + (int64_t)NREC * b;
+            const double2 q01 = *(const double2 *)qb, q23 = *(const double2 *)(qb + 2),
+                          q45 = *(const double2 *)(qb + 4);
+            const double Q[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+            const double r[3] = {c0 - cb.x, c1 - cb.y, c2 - cb.z};
             double Mb = 0.0, Qb[6] = {0, 0, 0, 0, 0, 0};
             m2l_vjp<FORM, F32>(r, cb.w, Q, Lb, rb, Mb, Qb);
         }
