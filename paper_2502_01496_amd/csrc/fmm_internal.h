@@ -124,6 +124,43 @@ __device__ __forceinline__ double2 as_double2(const int4 &x)
     return make_double2(__hiloint2double(x.y, x.x), __hiloint2double(x.w, x.z));
 }
 
+// Near field of few leaves (FP64): a team of NEAR_TEAM wavefronts takes a leaf
+// or piece, each a share of its blocks, where a wavefront per unit leaves most of
+// the chip's slots empty and the longest list is the time.  Forward, us, one
+// wavefront -> a team: Plummer 1000 particles 20.6 -> 11.5, 4096 61.8 -> 25.9,
+// 32768 (4096 leaves) 158 -> 134, 49152 (8192 leaves) 183 against 194; star 32768
+// 70.3 -> 60.7, 49152 78 against 92.  The whole reverse pass: 4096 particles
+// (512 leaves) 334 -> 273, 8192 397 -> 353, 16384 (2048 leaves) 502 -> 473 but
+// 364 against 372 for the clumpy cube, star 32768 476 against 506.  Teams of
+// eight: 4096 particles 23.4 and 288.
+constexpr int NEAR_TEAM = 4;
+constexpr int NEAR_TEAM_UNITS = 4096, NEAR_TEAM_UNITS_VJP = 1024;
+
+// First block of wavefront w's share of the blocks [p0, nb): multiples of 8.
+template <int TEAM>
+__device__ __forceinline__ int team_first(int p0, int nb, int w)
+{
+    if (TEAM == 1)
+        return w ? nb : p0;
+    const int share = (((nb - p0 + TEAM - 1) / TEAM) + 7) & ~7;
+    return min(nb, p0 + w * share);
+}
+
+// Sum of v over the wavefronts of a team, in their order, in the first one.
+template <int TEAM>
+__device__ __forceinline__ double team_sum(double v, double (*sh)[64], int w, int lane)
+{
+    if (TEAM == 1)
+        return v;
+    sh[w][lane] = v;
+    __syncthreads();
+    if (w == 0)
+        for (int i = 1; i < TEAM; ++i)
+            v += sh[i][lane];
+    __syncthreads();
+    return v;
+}
+
 // L2P, eq. (8)
 template <typename T>
 __device__ __forceinline__ void l2p(const T *L, T y0, T y1, T y2, T &a0, T &a1, T &a2)

@@ -988,7 +988,7 @@ __device__ __forceinline__ double m_over_r3_k(double r2, double m, double k15)
     return fma(my3 * e, fma(e, 1.875, k15), my3);
 }
 
-// Near field.  One wavefront per sink leaf.  The leaf's sinks are laid over
+// Near field.  One wavefront per sink leaf (TEAM for few).  The leaf's sinks are laid over
 // the lanes two by two, each pair of sinks over the g = floor(64 / pairs)
 // lanes of a group, and a step takes g source particles from LDS, one per lane
 // of the group (for 8 sinks: 4 groups, 16 sources, 128 pairs a step).  So every
@@ -1021,8 +1021,9 @@ __device__ __forceinline__ double m_over_r3_k(double r2, double m, double k15)
 //
 // The order of all additions depends on the lists only, so results are bitwise
 // reproducible.
-// One wavefront per workgroup: the leaves' near lists differ in length, and a
-// workgroup's slots are only freed when its last wavefront ends.
+// One wavefront per workgroup (the leaves' near lists differ in length, and a
+// workgroup's slots are only freed when its last wavefront ends), or a team of
+// TEAM, each with a share of the blocks and rings of its own, for few leaves.
 constexpr int P2P_SINKS = 16;  // sinks per pass, at most
 constexpr int P2P_RING = 128;  // sources a ring holds: less than g <= 64 left over, plus 64
 
@@ -1063,7 +1064,9 @@ struct NearRings {
     double hi[P2P_RING];
 };
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_rings(
+template <int TEAM>
+__global__ __launch_bounds__(64 * TEAM)
+    __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_rings(
     const double2 *__restrict__ pxy, const double2 *__restrict__ pzm,
     const double *__restrict__ phi, const double *__restrict__ lbox, const int32_t *__restrict__ first,
     const int32_t *__restrict__ count, const int32_t *__restrict__ leaf_node, int nunits,
@@ -1073,11 +1076,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     int per, double *part, int part_stride)
 {
     constexpr int RM = P2P_RING - 1;
-    __shared__ NearRings R;
+    __shared__ NearRings rings[TEAM];
+    __shared__ double team[TEAM][64];  // sums of the team's wavefronts
     const int unit = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
     if (unit >= nunits)
         return;
     const int lane = lane_id();
+    const int w = TEAM > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    NearRings &R = rings[w];
     const int grp = lane >> 3, slot = lane & 7;
     const int2 pc = pieces ? pieces[unit] : make_int2(unit, 0);
     const int leaf = pc.x;
@@ -1181,11 +1187,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                     a[3 * q + 2] -= fm * dz[q];
                 }
             };
-            for (int c0 = p0; c0 < nb; c0 += 64) {
+            const int wb = team_first<TEAM>(p0, nb, w), we = team_first<TEAM>(p0, nb, w + 1);
+            for (int c0 = wb; c0 < we; c0 += 64) {
                 // the particle ranges of 64 blocks, a lane each, the empty
                 // ones moved behind the others
                 int rx = 0, ry = 0;
-                if (c0 + lane < nb) {
+                if (c0 + lane < we) {
                     const int e = (c0 + lane) / nsub, u = (c0 + lane) - e * nsub;
                     const int bn = nl[e];
                     rx = first[bn] + 8 * u;
@@ -1270,10 +1277,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 #pragma unroll
             for (int q = 1; q < 6; ++q)
                 val = k == q ? a[q] : val;
-            tot += val;
+            tot += team_sum<TEAM>(val, team, w, lane);
         }
         const int q = k >= 3 ? 1 : 0, comp = k - 3 * q;
-        if (k < 6 && 2 * pr + q < cs) {
+        if (w == 0 && k < 6 && 2 * pr + q < cs) {
             const int si = sb + 2 * pr + q;
             if (pieces && nbf > per) {
                 part[(int64_t)unit * part_stride + 3 * si + comp] = tot;
@@ -1589,12 +1596,13 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s)
     const bool full = T.leaf_size == P2P_NS && T.n == (int64_t)P2P_NS * nl;
     if (t.p.precision == FMM_FP64) {
         // (lists_policy is set after the evaluation of a tree's new lists)
-        if (t.p.walk == FMM_WALK_PHANTOM)
-            k_p2p_rings<<<nu, 64, 0, s>>>(t.pxy, t.pzm, t.phi, t.lbox, t.first, t.count,
-                                          t.leaf_node, nu, t.near_cnt, t.near_src, (int)t.cap_near,
-                                          nsub, t.L, t.recA, t.perm, t.p.G, (double *)a, pl, per,
-                                          (double *)t.pnear.part, stride);
-        else
+        if (t.p.walk == FMM_WALK_PHANTOM) {
+            const int team = nu <= NEAR_TEAM_UNITS ? NEAR_TEAM : 1;
+            (team > 1 ? k_p2p_rings<NEAR_TEAM> : k_p2p_rings<1>)<<<nu, 64 * team, 0, s>>>(
+                t.pxy, t.pzm, t.phi, t.lbox, t.first, t.count, t.leaf_node, nu, t.near_cnt,
+                t.near_src, (int)t.cap_near, nsub, t.L, t.recA, t.perm, t.p.G, (double *)a, pl,
+                per, (double *)t.pnear.part, stride);
+        } else
             (full ? k_p2p_src_f64<false> : k_p2p_src_f64<true>)<<<
                 (nu + P2P_WAVES - 1) / P2P_WAVES, P2P_WG, 0, s>>>(
             t.pm, t.ph, t.first, t.count, t.leaf_node, nu, t.near_cnt, t.near_src,

@@ -1019,11 +1019,9 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
 // lists only.
 constexpr int VJP_NS = 8;        // uniform particles per pass
 constexpr int VJP_QCAP = 128;    // softened pairs a queue holds (a step adds <= 64)
-// One unit (leaf or piece) per wavefront and one wavefront per workgroup: the
-// units' lists differ in length, and a workgroup's slots are only freed when
-// its last wavefront ends.
-constexpr int VJP_WAVES = 1;
-constexpr int VJP_WG = 64 * VJP_WAVES;
+// One unit (leaf or piece) per workgroup, of one wavefront (the units' lists
+// differ in length, and a workgroup's slots are only freed when its last
+// wavefront ends) or, for few units, of a team.
 constexpr int VJP_BLOCKS = 256;  // blocks staged in LDS per chunk
 
 // Stage the non-empty blocks of list entries [c0, c0 + nc) (entry k: block
@@ -1107,7 +1105,9 @@ __device__ __forceinline__ double reduce_scatter32(const double *v, int lane)
 // (abar_i is wave-uniform, so the G term needs no per-pair product).  The
 // queues that a step fills past a multiple of 64 are evaluated after the
 // step, when its source data are no longer held.
-__global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_p2p_sink(
+template <int TEAM>
+__global__ __launch_bounds__(64 * TEAM)
+    __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_p2p_sink(
     const double4 *__restrict__ pm, const double4 *__restrict__ ph,
     const double *__restrict__ abt, const int32_t *__restrict__ first,
     const int32_t *__restrict__ count, const int32_t *__restrict__ leaf_node, int nunits,
@@ -1116,15 +1116,15 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     int part_stride)
 {
     constexpr int NS = VJP_NS;
-    __shared__ int2 rng[VJP_WAVES][VJP_BLOCKS + 8];
-    __shared__ int32_t que[VJP_WAVES][NS][VJP_QCAP];
-    __shared__ double4 shx[VJP_WAVES][NS];  // positions of the pass's sinks
-    __shared__ double4 sha[VJP_WAVES][NS];  // abar of the pass's sinks
-    __shared__ double4 sh3[VJP_WAVES][NS];  // -3 abar (the Newtonian D = -3 r^-5 folded in)
-    __shared__ double4 shh[VJP_WAVES][NS];  // h data of the pass's sinks
-    const int w = threadIdx.x >> 6;
-    const int unit =
-        __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x) * VJP_WAVES + w);
+    __shared__ int2 rng[TEAM][VJP_BLOCKS + 8];
+    __shared__ int32_t que[TEAM][NS][VJP_QCAP];
+    __shared__ double4 shx[TEAM][NS];  // positions of the pass's sinks
+    __shared__ double4 sha[TEAM][NS];  // abar of the pass's sinks
+    __shared__ double4 sh3[TEAM][NS];  // -3 abar (the Newtonian D = -3 r^-5 folded in)
+    __shared__ double4 shh[TEAM][NS];  // h data of the pass's sinks
+    __shared__ double team[TEAM][64];  // sums of the team's wavefronts
+    const int w = TEAM > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int unit = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
     if (unit >= nunits)
         return;
     const int lane = lane_id();
@@ -1193,8 +1193,9 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 #pragma unroll
             for (int q = 0; q < NS; ++q)
                 tail[q] = 0;
-            for (int c0 = p0; c0 < nb; c0 += VJP_BLOCKS) {
-                const int nc = min(nb - c0, VJP_BLOCKS);
+            const int wb = team_first<TEAM>(p0, nb, w), we = team_first<TEAM>(p0, nb, w + 1);
+            for (int c0 = wb; c0 < we; c0 += VJP_BLOCKS) {
+                const int nc = min(we - c0, VJP_BLOCKS);
                 const int ne = __builtin_amdgcn_readfirstlane(
                     stage_list_blocks(nl, c0, nc, nsub, first, count, lane, R));
                 __builtin_amdgcn_wave_barrier();
@@ -1250,13 +1251,13 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                 if (tail[q] & 63)
                     drain(q, tail[q] & ~63, tail[q] & 63);
             __builtin_amdgcn_wave_barrier();
-            const double e = reduce_scatter32(acc, lane);
+            const double e = team_sum<TEAM>(reduce_scatter32(acc, lane), team, w, lane);
             const double S = __shfl(e, lane & ~7);
             const double4 a = sha[w][qv];
             const double ak = kv == 1 ? a.x : (kv == 2 ? a.y : a.z);
             tot += -fma(ak, S, e);
         }
-        if (kv >= 1 && (lane & 1) == 0 && sb + qv < c) {
+        if (w == 0 && kv >= 1 && (lane & 1) == 0 && sb + qv < c) {
             if (split)
                 part[(int64_t)unit * part_stride + 3 * (sb + qv) + (kv - 1)] = tot;
             else
@@ -1270,7 +1271,9 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 // lanes the particles of the sink leaves of its transposed list.  Per source
 // q the lanes sum X = sum_i (G_ij abar_i + D_ij (d . abar_i) d) and
 // Y = sum_i G_ij (d . abar_i); a piece adds m_j X to xbar_j and -Y to mbar_j.
-__global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_p2p_src(
+template <int TEAM>
+__global__ __launch_bounds__(64 * TEAM)
+    __attribute__((amdgpu_waves_per_eu(3, 8))) void k_vjp_p2p_src(
     const double4 *__restrict__ pm, const double4 *__restrict__ ph,
     const double *__restrict__ abt, const int32_t *__restrict__ first,
     const int32_t *__restrict__ count, const int32_t *__restrict__ leaf_node, int nunits,
@@ -1279,13 +1282,13 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     int part_stride)
 {
     constexpr int NS = VJP_NS;
-    __shared__ int2 rng[VJP_WAVES][VJP_BLOCKS + 8];
-    __shared__ int32_t que[VJP_WAVES][NS][VJP_QCAP];
-    __shared__ double4 shx[VJP_WAVES][NS];  // positions of the pass's sources
-    __shared__ double4 shh[VJP_WAVES][NS];  // h data of the pass's sources
-    const int w = threadIdx.x >> 6;
-    const int unit =
-        __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x) * VJP_WAVES + w);
+    __shared__ int2 rng[TEAM][VJP_BLOCKS + 8];
+    __shared__ int32_t que[TEAM][NS][VJP_QCAP];
+    __shared__ double4 shx[TEAM][NS];  // positions of the pass's sources
+    __shared__ double4 shh[TEAM][NS];  // h data of the pass's sources
+    __shared__ double team[TEAM][64];  // sums of the team's wavefronts
+    const int w = TEAM > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int unit = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
     if (unit >= nunits)
         return;
     const int lane = lane_id();
@@ -1353,8 +1356,9 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 #pragma unroll
             for (int q = 0; q < NS; ++q)
                 tail[q] = 0;
-            for (int c0 = p0; c0 < nb; c0 += VJP_BLOCKS) {
-                const int nc = min(nb - c0, VJP_BLOCKS);
+            const int wb = team_first<TEAM>(p0, nb, w), we = team_first<TEAM>(p0, nb, w + 1);
+            for (int c0 = wb; c0 < we; c0 += VJP_BLOCKS) {
+                const int nc = min(we - c0, VJP_BLOCKS);
                 const int ne = __builtin_amdgcn_readfirstlane(
                     stage_list_blocks(tl, c0, nc, nsub, first, count, lane, R));
                 __builtin_amdgcn_wave_barrier();
@@ -1409,11 +1413,11 @@ __global__ __launch_bounds__(VJP_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                 if (tail[q] & 63)
                     drain(q, tail[q] & ~63, tail[q] & 63);
             __builtin_amdgcn_wave_barrier();
-            const double e = reduce_scatter32(acc, lane);
+            const double e = team_sum<TEAM>(reduce_scatter32(acc, lane), team, w, lane);
             const double mq = shx[w][qv].w;
             tot += kv < 3 ? mq * e : -e;
         }
-        if ((lane & 1) == 0 && sb + qv < c) {
+        if (w == 0 && (lane & 1) == 0 && sb + qv < c) {
             const int64_t jj = f + sb + qv;
             if (split)
                 part[(int64_t)unit * part_stride + 4 * (sb + qv) + kv] = tot;
@@ -2149,7 +2153,8 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         const bool pc = use_pieces(t);
         const int nu = pc ? (int)t.pnear.n : nl;
         const int stride = 3 * T.leaf_size;
-        k_vjp_p2p_sink<<<(nu + VJP_WAVES - 1) / VJP_WAVES, VJP_WG, 0, s>>>(
+        const int team = !fp32 && nu <= NEAR_TEAM_UNITS_VJP ? NEAR_TEAM : 1;
+        (team > 1 ? k_vjp_p2p_sink<NEAR_TEAM> : k_vjp_p2p_sink<1>)<<<nu, 64 * team, 0, s>>>(
             t.pm, t.ph, t.abt, t.first, t.count, t.leaf_node, nu, t.near_cnt, t.near_src,
             (int)t.cap_near, nsub, n, t.xbt, pc ? t.pnear.list : nullptr, per,
             (double *)t.pnear.part, stride);
@@ -2163,7 +2168,8 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         const bool pc = t.pnearT.n > nl;
         const int nu = pc ? (int)t.pnearT.n : nl;
         const int stride = 4 * T.leaf_size;
-        k_vjp_p2p_src<<<(nu + VJP_WAVES - 1) / VJP_WAVES, VJP_WG, 0, s>>>(
+        const int team = !fp32 && nu <= NEAR_TEAM_UNITS_VJP ? NEAR_TEAM : 1;
+        (team > 1 ? k_vjp_p2p_src<NEAR_TEAM> : k_vjp_p2p_src<1>)<<<nu, 64 * team, 0, s>>>(
             t.pm, t.ph, t.abt, t.first, t.count, t.leaf_node, nu, t.nearT.off, t.nearT.src, nsub,
             n, t.xbt, t.mbt, pc ? t.pnearT.list : nullptr, (int)t.vjp_src_piece_blocks,
             (double *)t.pnearT.part, stride);
