@@ -900,7 +900,7 @@ static fmm_status forces_mutual(Tree &t, void *a, bool walk, bool vjp_only, hipS
         t.pieces_valid = false;
         t.split_lists = mx * ((T.leaf_size + 7) / 8) > t.near_piece_blocks;
         t.has_lists = true;
-        t.has_transposed = false;
+        t.has_farT = t.has_transposed = false;
         t.lists_policy = FMM_WALK_MUTUAL;
         t.nsinks = T.nnodes;
         t.n_far = M.n_far;
@@ -1195,7 +1195,7 @@ fmm_status fmm_forces(fmm_tree *tree, void *a, int32_t flags, void *stream)
                         (long long)mf, (long long)mn, (long long)t.p.list_capacity);
         if (mf <= t.cap_far && mn <= t.cap_near) {
             t.has_lists = true;
-            t.has_transposed = false;
+            t.has_farT = t.has_transposed = false;
             t.lists_policy = t.p.walk;
             t.nsinks = t.topo.nleaves;
             t.n_far = t.n_near = -1;  // totals computed on demand
@@ -1635,7 +1635,7 @@ fmm_status fmm_debug_import(fmm_tree *tree, const double *x, const double *m, co
         return fail(FMM_ERR_HIP, "import failed: %s", hipGetErrorString(e));
     t.has_moments = true;
     t.has_lists = true;
-    t.has_transposed = false;
+    t.has_farT = t.has_transposed = false;
     t.lists_policy = FMM_WALK_PHANTOM;
     t.nsinks = (int)nl;
     t.n_far = tf;

@@ -12,6 +12,8 @@
 //   eq. (46): 4 M_l^2 N_a N_b / r^5 (U(a) + U(b)),   r = |c_a - c_b|.
 // Sums: per lane in list order, a fixed butterfly per sink, then one
 // workgroup over the sinks in a fixed order (deterministic, no atomics).
+#include <algorithm>
+
 #include "fmm_internal.h"
 
 namespace fmm {
@@ -26,25 +28,47 @@ __device__ __forceinline__ double wave_sum_d(double v)
     return v;
 }
 
-// Per node: T, U and N.  One wavefront per node; the leaves of the node's
-// subtree are consecutive in leaf order (pre-order ids, left child first),
-// from the leftmost to the rightmost descendant.
-__global__ __launch_bounds__(256) void k_asym_node(const double *__restrict__ recA,
-                                                   const int32_t *__restrict__ left,
-                                                   const int32_t *__restrict__ right,
-                                                   const int32_t *__restrict__ node_leaf,
-                                                   const int32_t *__restrict__ leaf_node,
-                                                   int nnodes, double *tun)
+// Minimum or maximum over the THREADS lanes of a workgroup.
+template <int THREADS, bool MAX>
+__device__ __forceinline__ double team_extreme(double v, double *sh)
 {
-    const int v = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (v >= nnodes)
-        return;
-    const int lane = lane_id();
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const double o = __shfl_xor(v, off);
+        v = MAX ? fmax(v, o) : fmin(v, o);
+    }
+    if (THREADS > 64) {
+        if (lane_id() == 0)
+            sh[threadIdx.x >> 6] = v;
+        __syncthreads();
+        for (int i = 0; i < THREADS / 64; ++i)
+            v = MAX ? fmax(v, sh[i]) : fmin(v, sh[i]);
+        __syncthreads();
+    }
+    return v;
+}
+
+// T, U and N of node v by THREADS lanes; the leaves of the node's subtree are
+// consecutive in leaf order (pre-order ids, left child first), from the leftmost
+// to the rightmost descendant.
+template <int THREADS>
+__device__ __forceinline__ void asym_node(int v, const double *__restrict__ recA,
+                                          const int32_t *__restrict__ left,
+                                          const int32_t *__restrict__ right,
+                                          const int32_t *__restrict__ node_leaf,
+                                          const int32_t *__restrict__ leaf_node, double *tun,
+                                          double *sh)
+{
+    const int lane = THREADS > 64 ? threadIdx.x : lane_id();
     int lo = v, hi = v;
-    while (left[lo] >= 0)
-        lo = left[lo];
-    while (right[hi] >= 0)
-        hi = right[hi];
+    for (int l = left[v], r = right[v]; l >= 0 || r >= 0;) {  // both descents together
+        if (l >= 0)
+            lo = l;
+        if (r >= 0)
+            hi = r;
+        l = l >= 0 ? left[l] : -1;
+        r = r >= 0 ? right[r] : -1;
+    }
     const int l0 = node_leaf[lo], l1 = node_leaf[hi];
     const int nlv = l1 - l0 + 1;
     double *o = tun + 3 * (int64_t)v;
@@ -57,24 +81,22 @@ __global__ __launch_bounds__(256) void k_asym_node(const double *__restrict__ re
         return;
     }
     double m1 = __builtin_huge_val();
-    for (int k = l0 + lane; k <= l1; k += 64)
+#pragma unroll 4
+    for (int k = l0 + lane; k <= l1; k += THREADS)
         m1 = fmin(m1, recA[(int64_t)NREC * leaf_node[k] + 3]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        m1 = fmin(m1, __shfl_xor(m1, off));
+    m1 = team_extreme<THREADS, false>(m1, sh);
     const double *rv = recA + (int64_t)NREC * v;
     const double cx = rv[0], cy = rv[1], cz = rv[2];
     double d2 = -1.0;
-    for (int k = l0 + lane; k <= l1; k += 64) {
+#pragma unroll 4
+    for (int k = l0 + lane; k <= l1; k += THREADS) {
         const double *ru = recA + (int64_t)NREC * leaf_node[k];
         if (ru[3] == m1) {
             const double dx = ru[0] - cx, dy = ru[1] - cy, dz = ru[2] - cz;
             d2 = fmax(d2, dx * dx + dy * dy + dz * dz);
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        d2 = fmax(d2, __shfl_xor(d2, off));
+    d2 = team_extreme<THREADS, true>(d2, sh);
     if (lane == 0) {
         const double l = sqrt(d2);
         const double rest = rv[3] - m1;
@@ -83,6 +105,34 @@ __global__ __launch_bounds__(256) void k_asym_node(const double *__restrict__ re
         o[1] = s * s * s * (N - 2.0) / ((N - 1.0) * (N - 1.0));
         o[2] = N;
     }
+}
+
+// The internal cells of the first ASYM_TOP levels by a workgroup each, all
+// other nodes by a wavefront each: the leaves of the root's subtree by one
+// wavefront were the whole time (148 us at 131072 particles, now 31 + 20).
+constexpr int ASYM_TOP = 6, ASYM_TOP_T = 1024;
+
+__global__ __launch_bounds__(ASYM_TOP_T) void k_asym_top(
+    const int32_t *__restrict__ int_nodes, const double *__restrict__ recA,
+    const int32_t *__restrict__ left, const int32_t *__restrict__ right,
+    const int32_t *__restrict__ node_leaf, const int32_t *__restrict__ leaf_node, double *tun)
+{
+    __shared__ double sh[ASYM_TOP_T / 64];
+    asym_node<ASYM_TOP_T>(int_nodes[blockIdx.x], recA, left, right, node_leaf, leaf_node, tun, sh);
+}
+
+__global__ __launch_bounds__(256) void k_asym_node(const double *__restrict__ recA,
+                                                   const int32_t *__restrict__ left,
+                                                   const int32_t *__restrict__ right,
+                                                   const int32_t *__restrict__ level,
+                                                   const int32_t *__restrict__ node_leaf,
+                                                   const int32_t *__restrict__ leaf_node,
+                                                   int nnodes, double *tun)
+{
+    const int v = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (v >= nnodes || (level[v] < ASYM_TOP && left[v] >= 0))
+        return;
+    asym_node<64>(v, recA, left, right, node_leaf, leaf_node, tun, nullptr);
 }
 
 // M_l of eq. (46): the given value, or the mean leaf mass (root mass over
@@ -243,12 +293,17 @@ hipError_t launch_asym(Tree &t, double m_leaf, double *out, hipStream_t s)
            *dout = part + 4 * (size_t)T.node_cap;
     const bool mutual = t.lists_policy == FMM_WALK_MUTUAL;
     if (!mutual) {
-        e = ensure_transposed(t, s);
+        e = ensure_far_transposed(t, s);
         if (e != hipSuccess)
             return e;
     }
-    k_asym_node<<<(nn + 3) / 4, 256, 0, s>>>(t.recA, t.left, t.right, t.node_leaf, t.leaf_node,
-                                             nn, tun);
+    // (int_nodes holds the internal cells level by level)
+    const int ntop = T.lvl_int_off[std::min<int>(ASYM_TOP, (int)T.lvl_int_off.size() - 1)];
+    if (ntop > 0)
+        k_asym_top<<<ntop, ASYM_TOP_T, 0, s>>>(t.int_nodes, t.recA, t.left, t.right, t.node_leaf,
+                                               t.leaf_node, tun);
+    k_asym_node<<<(nn + 3) / 4, 256, 0, s>>>(t.recA, t.left, t.right, t.level, t.node_leaf,
+                                             t.leaf_node, nn, tun);
     int nsinks;
     if (mutual) {
         nsinks = nn;

@@ -396,7 +396,8 @@ struct Tree {
         int64_t npairs = 0;
         int64_t src_cap = 0;      // entries src holds
     } farT, nearT;
-    bool has_transposed = false;
+    bool has_farT = false;        // farT is of the current lists
+    bool has_transposed = false;  // both, with their pieces
     std::vector<DevBuf> vjp_owned;
     int64_t vjp_pair_cap = 0;
     uint32_t *vk0 = nullptr, *vk1 = nullptr;
@@ -580,6 +581,7 @@ hipError_t launch_far_mutual(Tree &t, hipStream_t s);
 hipError_t launch_l2l_internal(Tree &t, hipStream_t s);
 hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStream_t s);
 hipError_t ensure_transposed(Tree &t, hipStream_t s);
+hipError_t ensure_far_transposed(Tree &t, hipStream_t s);  // leaf <- cell lists only
 int64_t com_max_active(int64_t n);  // active cells of a level of the centre-of-mass build
 void release_vjp(Tree &t);
 hipError_t launch_asym(Tree &t, double m_leaf, double *out, hipStream_t s);

@@ -2067,6 +2067,21 @@ static hipError_t vjp_mutual_far(Tree &t, hipStream_t s)
     return hipGetLastError();
 }
 
+// The transposed far lists alone (what the asymmetry estimates need).
+hipError_t ensure_far_transposed(Tree &t, hipStream_t s)
+{
+    hipError_t e = ensure_vjp_base(t);
+    if (e != hipSuccess || t.has_farT)
+        return e;
+    e = count_pairs_async(t, 0, t.far_cnt, t.cap_far, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e == hipSuccess)
+        e = transpose_lists(t, 0, t.far_cnt, t.far_src, t.cap_far, false, t.farT, s);
+    t.has_farT = e == hipSuccess;
+    return e;
+}
+
 // The mutual walk's far pairs are symmetric and need no transposition (its
 // near lists are symmetric too, but the source side of P2P^T reads the CSR
 // form).
@@ -2077,14 +2092,17 @@ hipError_t ensure_transposed(Tree &t, hipStream_t s)
         return e;
     // two readbacks: the numbers of pairs, the numbers of pieces
     const bool far = t.lists_policy != FMM_WALK_MUTUAL;
-    if (far)
+    const bool farT = far && !t.has_farT;
+    if (farT)
         e = count_pairs_async(t, 0, t.far_cnt, t.cap_far, s);
     if (e == hipSuccess)
         e = count_pairs_async(t, 1, t.near_cnt, t.cap_near, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (e == hipSuccess && far)
+    if (e == hipSuccess && farT) {
         e = transpose_lists(t, 0, t.far_cnt, t.far_src, t.cap_far, false, t.farT, s);
+        t.has_farT = e == hipSuccess;
+    }
     if (e == hipSuccess)
         e = transpose_lists(t, 1, t.near_cnt, t.near_src, t.cap_near, true, t.nearT, s);
     if (e == hipSuccess && far)
