@@ -16,9 +16,9 @@
 //      giving per axis the particles sorted by (x_d, rank);
 //   5. for cells larger than SUBTREE_MAX, one level at a time: the median of
 //      the longest axis is the middle entry of that axis's sorted segment, so
-//      the split is a stable partition of the four lists (three axis lists +
-//      the rank list); an entry's side follows from comparing its key
-//      (coordinate bits, rank) with that of the last left entry;
+//      the split is a stable partition of the three axis lists; an entry's side
+//      follows from comparing its key (coordinate bits, rank) with that of the
+//      last left entry;
 //   6. every cell of at most SUBTREE_MAX particles is finished by one
 //      workgroup in LDS (all levels below it), which writes the final order.
 //
@@ -150,10 +150,9 @@ __global__ void k_morton(const double *__restrict__ x, int64_t n, const uint64_t
 }
 
 // Coordinates in Morton-rank order, and the three axis keys (ordered bits,
-// value = rank) for the per-axis sorts; the rank list starts as the identity.
+// value = rank) for the per-axis sorts.
 __global__ void k_rank_gather(const double *__restrict__ x, int64_t n, const uint32_t *order,
-                              int32_t *r2o, double *xr, uint64_t *keys, uint32_t *vals,
-                              uint32_t *ranklist)
+                              int32_t *r2o, double *xr, uint64_t *keys, uint32_t *vals)
 {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n;
          r += (int64_t)gridDim.x * blockDim.x) {
@@ -166,7 +165,6 @@ __global__ void k_rank_gather(const double *__restrict__ x, int64_t n, const uin
             keys[d * n + r] = ordbits(v);
             vals[d * n + r] = (uint32_t)r;
         }
-        ranklist[r] = (uint32_t)r;
     }
 }
 
@@ -273,7 +271,7 @@ __device__ __forceinline__ int count_rank(const uint64_t *__restrict__ keys, int
 // Morton order; xr != null: also what k_rank_gather makes of it.
 __global__ __launch_bounds__(CR_THREADS) void k_rank_morton(
     const uint64_t *__restrict__ keys, const double *__restrict__ x, int n, uint32_t *order,
-    int32_t *r2o, double *xr, uint64_t *akeys, uint32_t *ranklist)
+    int32_t *r2o, double *xr, uint64_t *akeys)
 {
     const int e = blockIdx.x * 64 + lane_id();
     const int r = count_rank(keys, n, keys[min(e, n - 1)]);
@@ -283,7 +281,6 @@ __global__ __launch_bounds__(CR_THREADS) void k_rank_morton(
     if (!xr)
         return;
     r2o[r] = e;
-    ranklist[r] = (uint32_t)r;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const double v = x[3 * e + d];
@@ -591,7 +588,7 @@ constexpr int RUN_HALO = RUN_SHORT + 1;
 
 __global__ __launch_bounds__(RUN_BLOCK) void k_run_fix(const uint64_t *__restrict__ kin,
                                                        const uint32_t *__restrict__ vin,
-                                                       uint64_t *kout, uint32_t *vout, int64_t n,
+                                                       uint32_t *vout, int64_t n,
                                                        uint32_t *long_cnt, int64_t *long_list,
                                                        int64_t long_cap, uint32_t *err)
 {
@@ -600,7 +597,6 @@ __global__ __launch_bounds__(RUN_BLOCK) void k_run_fix(const uint64_t *__restric
     const int b = blockIdx.y, t = threadIdx.x;
     const uint64_t *k = kin + (int64_t)b * n;
     const uint32_t *v = vin + (int64_t)b * n;
-    uint64_t *ko = kout + (int64_t)b * n;
     uint32_t *vo = vout + (int64_t)b * n;
     for (int64_t base = (int64_t)blockIdx.x * RUN_BLOCK; base < n;
          base += (int64_t)gridDim.x * RUN_BLOCK) {
@@ -623,7 +619,6 @@ __global__ __launch_bounds__(RUN_BLOCK) void k_run_fix(const uint64_t *__restric
             const bool next_same = p + 1 < n && hi32(sk[i + 1]) == hp;
             if (!prev_same && !next_same) {
                 // a run of one entry (nearly all of them)
-                ko[p] = kp;
                 vo[p] = vp;
             } else {
                 // window indices: ia - 1 >= i - RUN_SHORT - 1 >= 0 and
@@ -657,7 +652,6 @@ __global__ __launch_bounds__(RUN_BLOCK) void k_run_fix(const uint64_t *__restric
                         const uint32_t lq = (uint32_t)sk[q], vq = sv[q];
                         r += (lq < lp || (lq == lp && vq < vp)) ? 1 : 0;
                     }
-                    ko[a + r] = kp;
                     vo[a + r] = vp;
                 }
             }
@@ -766,19 +760,17 @@ __global__ __launch_bounds__(RS_THREADS) void k_run_long(uint64_t *kin, uint32_t
             }
         }
         // four passes end in the input arrays: copy the run to the output
-        for (int64_t i = t; i < L; i += RS_THREADS) {
-            K[1][a + i] = K[0][a + i];
+        for (int64_t i = t; i < L; i += RS_THREADS)
             V[1][a + i] = V[0][a + i];
-        }
         __syncthreads();
     }
 }
 
-// Sort B arrays of (key, position) pairs held in (k0, v0); the result lands
-// in (k1, v1).  work: B * (n / (RUN_SHORT + 1) + 1) int64 for the long-run
-// list; long_cnt[0] counts the long runs, long_cnt[1] their entries.
-hipError_t sort_by_halves(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, int64_t n,
-                          int B, uint32_t *hist, uint32_t *tot, uint32_t *long_cnt,
+// Sort B arrays of (key, position) pairs held in (k0, v0); the sorted positions
+// land in vout, (k1, v1) is work space.  long_list: B * (n / (RUN_SHORT + 1) + 1)
+// entries; long_cnt[0] counts the long runs, long_cnt[1] their entries.
+hipError_t sort_by_halves(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t *vout,
+                          int64_t n, int B, uint32_t *hist, uint32_t *tot, uint32_t *long_cnt,
                           int64_t *long_list, uint32_t *err, hipStream_t s)
 {
     const int nblk = (int)((n + RS_TILE - 1) / RS_TILE);
@@ -798,8 +790,8 @@ hipError_t sort_by_halves(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1
                                                                tp, nblk);
     }
     const int gf = (int)std::min<int64_t>((n + 255) / 256, 4096);
-    k_run_fix<<<dim3(gf, B), 256, 0, s>>>(k0, v0, k1, v1, n, long_cnt, long_list, long_cap, err);
-    k_run_long<<<256, RS_THREADS, 0, s>>>(k0, v0, k1, v1, n, long_cnt, long_list, long_cap);
+    k_run_fix<<<dim3(gf, B), 256, 0, s>>>(k0, v0, vout, n, long_cnt, long_list, long_cap, err);
+    k_run_long<<<256, RS_THREADS, 0, s>>>(k0, v0, k1, vout, n, long_cnt, long_list, long_cap);
     return hipGetLastError();
 }
 
@@ -1089,13 +1081,13 @@ __global__ __launch_bounds__(SUBTREE_THREADS) void k_subtree(
     const int32_t *__restrict__ r2o, const int32_t *__restrict__ sub_root,
     const int32_t *__restrict__ first, const int32_t *__restrict__ count,
     const int32_t *__restrict__ right, const int32_t *__restrict__ level, int leaf_size,
-    int32_t *perm, int32_t *axis_out)
+    uint16_t *loc, int32_t *perm, int32_t *axis_out)
 {
     constexpr int PER = SUBTREE_MAX / SUBTREE_THREADS;  // positions per thread
     constexpr int WORDS = SUBTREE_MAX / 64;
     static_assert(WORDS <= 64, "one lane per word in the prefix sums");
     static_assert(SUBTREE_MAX <= 1 << 15, "node offsets and counts in 16 bits");
-    __shared__ uint32_t rk[SUBTREE_MAX];      // Morton ranks by local id, then caller indices
+    __shared__ uint32_t rk[SUBTREE_MAX];      // Morton ranks by local id
     __shared__ double xyz[3][SUBTREE_MAX];    // coordinates by local id
     __shared__ uint16_t lst[3][SUBTREE_MAX];  // local ids in the order of each axis
     __shared__ uint8_t flg[SUBTREE_MAX];      // by local id: goes to the left child
@@ -1108,45 +1100,12 @@ __global__ __launch_bounds__(SUBTREE_THREADS) void k_subtree(
     const int root = sub_root[blockIdx.x];
     const int64_t f0 = first[root];
     const int n0 = count[root];
-    const uint32_t *L = Lall + (int64_t)(level[root] & 1) * 4 * n;
+    const uint32_t *L = Lall + (int64_t)(level[root] & 1) * 3 * n;
 
+    // local id: the place in the first axis list; loc[rank] holds it for the
+    // ranks of the other two lists (one entry per particle, in global memory)
     uint32_t rd[PER][3];  // ranks of the axis lists at the thread's positions
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int p = t + j * SUBTREE_THREADS;
-        if (p < n0) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                rd[j][d] = L[d * n + f0 + p];
-            const uint32_t r = L[3 * n + f0 + p];
-            rk[p] = r;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                xyz[d][p] = xr[d * n + r];
-        }
-    }
-    if (t == 0)
-        snode[0] = 0;
-    __syncthreads();
-    // local id of a rank: its place in the ascending rank list
     int id[PER][3];
-#pragma unroll
-    for (int j = 0; j < PER; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-            id[j][d] = 0;
-    for (int step = SUBTREE_MAX / 2; step; step >>= 1)
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (t + j * SUBTREE_THREADS < n0) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const int q = id[j][d] + step;
-                    if (q <= n0 && rk[q - 1] < rd[j][d])
-                        id[j][d] = q;
-                }
-            }
-        }
     int cf[PER], cn[PER];  // first position and size of the position's cell (0: no position)
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -1156,15 +1115,29 @@ __global__ __launch_bounds__(SUBTREE_THREADS) void k_subtree(
         if (p < n0) {
 #pragma unroll
             for (int d = 0; d < 3; ++d)
-                lst[d][p] = (uint16_t)id[j][d];
+                rd[j][d] = L[d * n + f0 + p];
+            rk[p] = rd[j][0];
+            loc[rd[j][0]] = (uint16_t)p;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                xyz[d][p] = xr[d * n + rd[j][0]];
         }
     }
+    if (t == 0)
+        snode[0] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int p = t + j * SUBTREE_THREADS;
-        if (p < n0)
-            rk[p] = (uint32_t)r2o[rk[p]];
+        id[j][0] = p < n0 ? p : 0;
+#pragma unroll
+        for (int d = 1; d < 3; ++d)
+            id[j][d] = p < n0 ? loc[rd[j][d]] : 0;
+        if (p < n0) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                lst[d][p] = (uint16_t)id[j][d];
+        }
     }
     __syncthreads();
 
@@ -1265,15 +1238,21 @@ __global__ __launch_bounds__(SUBTREE_THREADS) void k_subtree(
                     id[j][d] = lst[d][t + j * SUBTREE_THREADS];
     }
 
-    // leaves: members in ascending local id (= ascending Morton rank)
+    // leaves: members in ascending Morton rank
+    uint32_t me[PER];
+    int32_t out[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int me = id[j][0];
+        me[j] = rk[id[j][0]];
+        out[j] = cn[j] > 0 ? r2o[me[j]] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
         int rank = 0;
         for (int q = 0; q < cn[j]; ++q)
-            rank += lst[0][cf[j] + q] < me;
+            rank += rk[lst[0][cf[j] + q]] < me[j];
         if (cn[j] > 0)
-            perm[f0 + cf[j] + rank] = (int32_t)rk[me];
+            perm[f0 + cf[j] + rank] = out[j];
     }
 }
 
@@ -1286,12 +1265,12 @@ hipError_t launch_morton_order(Tree &t, const double *x, hipStream_t s)
     if (n <= COUNT_SORT_MAX) {
         k_morton_few<<<1, CR_THREADS, 0, s>>>(x, (int)n, t.bbox, t.keys0, t.run_cnt + 2, t.err);
         k_rank_morton<<<(int)((n + 63) / 64), CR_THREADS, 0, s>>>(
-            t.keys0, x, (int)n, t.vals0, nullptr, nullptr, nullptr, nullptr);
+            t.keys0, x, (int)n, t.vals0, nullptr, nullptr, nullptr);
         return hipGetLastError();
     }
     const int gs = (int)std::min<int64_t>((n + 255) / 256, 2048);
     k_bbox_init<<<1, 64, 0, s>>>(t.bbox, t.err);
-    k_bbox<<<(int)std::min<int64_t>((n + 255) / 256, 256), 256, 0, s>>>(x, n, t.bbox, t.err);
+    k_bbox<<<(int)std::min<int64_t>((n + 1023) / 1024, 1024), 256, 0, s>>>(x, n, t.bbox, t.err);
     // Morton keys in (keys1, vals1) -> sorted into (keys0, vals0)
     k_morton<<<gs, 256, 0, s>>>(x, n, t.bbox, t.keys1, t.vals1);
     if (t.morton_full) {
@@ -1301,13 +1280,11 @@ hipError_t launch_morton_order(Tree &t, const double *x, hipStream_t s)
         hipError_t e = radix_sort_u64(t.keys1, t.vals1, t.keys0, t.vals0, n, 1, 8, t.rs_hist,
                                       t.rs_tot, s, 8);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(t.keys0, t.keys1, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess)
             e = hipMemcpyAsync(t.vals0, t.vals1, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
         return e;
     }
-    return sort_by_halves(t.keys1, t.vals1, t.keys0, t.vals0, n, 1, t.rs_hist, t.rs_tot,
-                          t.run_cnt + 2, t.run_list, t.err, s);
+    return sort_by_halves(t.keys1, t.vals1, t.keys0, t.vals1 + n, t.vals0, n, 1, t.rs_hist,
+                          t.rs_tot, t.run_cnt + 2, t.run_list, t.err, s);
 }
 
 hipError_t launch_build(Tree &t, const double *x, hipStream_t s)
@@ -1315,25 +1292,22 @@ hipError_t launch_build(Tree &t, const double *x, hipStream_t s)
     const Topology &T = t.topo;
     const int64_t n = T.n;
     const int gs = (int)std::min<int64_t>((n + 255) / 256, 2048);
-    // lists buffer 0: axis lists 0..2 and the rank list 3
-    uint32_t *L0 = t.lists, *L1 = t.lists + 4 * n;
+    // the two buffers of the axis lists
+    uint32_t *L0 = t.lists, *L1 = t.lists + 3 * n;
     if (n <= COUNT_SORT_MAX) {
         const int g = (int)((n + 63) / 64);
         k_morton_few<<<1, CR_THREADS, 0, s>>>(x, (int)n, t.bbox, t.keys0, t.run_cnt + 2, t.err);
-        k_rank_morton<<<g, CR_THREADS, 0, s>>>(t.keys0, x, (int)n, t.vals0, t.r2o, t.xr, t.keys1,
-                                               L0 + 3 * n);
+        k_rank_morton<<<g, CR_THREADS, 0, s>>>(t.keys0, x, (int)n, t.vals0, t.r2o, t.xr, t.keys1);
         k_rank_axes<<<dim3(g, 3), CR_THREADS, 0, s>>>(t.keys1, (int)n, L0);
     } else {
         hipError_t e = launch_morton_order(t, x, s);
         if (e != hipSuccess)
             return e;
-        k_rank_gather<<<gs, 256, 0, s>>>(x, n, t.vals0, t.r2o, t.xr, t.keys1, t.vals1, L0 + 3 * n);
-        // the three axis arrays (keys1, vals1) -> sorted into (keys0, vals0);
-        // the values are the Morton ranks, copied into list buffer 0.
-        e = sort_by_halves(t.keys1, t.vals1, t.keys0, t.vals0, n, 3, t.rs_hist, t.rs_tot,
+        k_rank_gather<<<gs, 256, 0, s>>>(x, n, t.vals0, t.r2o, t.xr, t.keys1, t.vals1);
+        // the three axis arrays (keys1, vals1), the values being the Morton
+        // ranks -> the axis lists
+        e = sort_by_halves(t.keys1, t.vals1, t.keys0, t.vals0, L0, n, 3, t.rs_hist, t.rs_tot,
                            t.run_cnt, t.run_list, t.err, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(L0, t.vals0, sizeof(uint32_t) * 3 * n, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess)
             return e;
     }
@@ -1342,26 +1316,26 @@ hipError_t launch_build(Tree &t, const double *x, hipStream_t s)
         const uint32_t *Ls = (l & 1) ? L1 : L0;
         uint32_t *Ld = (l & 1) ? L0 : L1;
         if (n >= LVL_BYRANK_MIN) {
-            uint8_t *byrank = t.side + 4 * n;
+            uint8_t *byrank = t.side + 3 * n;
             k_lvl_side<<<nb, LVL_THREADS, 0, s>>>(Ls, n, t.xr, t.blk_node + b0,
                                                   t.blk_start + b0, t.blk_end + b0, t.first,
                                                   t.count, t.axis, byrank);
-            k_lvl_count_byrank<<<dim3(nb, 4), LVL_THREADS, 0, s>>>(
+            k_lvl_count_byrank<<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
                 Ls, n, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0, t.first, t.count,
                 t.axis, byrank, t.side, t.lvl_cnt, T.max_lvl_blocks);
         } else {
-            k_lvl_count<<<dim3(nb, 4), LVL_THREADS, 0, s>>>(
+            k_lvl_count<<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
                 Ls, n, t.xr, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0, t.first,
                 t.count, t.axis, t.side, t.lvl_cnt, T.max_lvl_blocks);
         }
-        k_lvl_scatter<<<dim3(nb, 4), LVL_THREADS, 0, s>>>(
+        k_lvl_scatter<<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
             Ls, Ld, n, t.side, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0,
             t.blk_first + b0, t.first, t.count, t.lvl_cnt, T.max_lvl_blocks);
     }
     int nsub = (int)T.sub_root.size();
     k_subtree<<<nsub, SUBTREE_THREADS, 0, s>>>(t.lists, n, t.xr, t.r2o, t.sub_root, t.first,
-                                               t.count, t.right, t.level, T.leaf_size, t.perm,
-                                               t.axis);
+                                               t.count, t.right, t.level, T.leaf_size,
+                                               (uint16_t *)t.side, t.perm, t.axis);
     return hipGetLastError();
 }
 
