@@ -787,6 +787,10 @@ __device__ __forceinline__ float m4g_f32(float q, float hinv3, float u3)
 // gather in few steps.  The order of all additions depends on the lists
 // only.  Long lists are cut into pieces of `per` blocks as in the FP64
 // kernel.
+// It waits for its sources 40 % of the time with four wavefronts per SIMD; the
+// fifth costs a few spilled registers outside the steps and pays: 345 -> 329 us
+// (binary, 2^19 particles), 9.95 -> 9.32 ms (2^24), 1.63 -> 1.48 ms (Plummer,
+// 2^19).  Loading a step ahead with four took 360 us and 10.2 ms.
 __device__ __forceinline__ float rsq_pos_f(float x) { return __builtin_amdgcn_rsqf(x); }
 
 constexpr int P2P_RANGES_F32 = 256;    // blocks staged in LDS per chunk
@@ -813,7 +817,7 @@ __device__ __forceinline__ int skip_gap(int k, int front, int gap)
 }
 
 template <bool SKIP>
-__global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_p2p_src_f32(
+__global__ __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_p2p_src_f32(
     const float4 *__restrict__ pf, const float4 *__restrict__ pfh,
     const int32_t *__restrict__ first,
     const int32_t *__restrict__ count, const int32_t *__restrict__ leaf_node, int nleaves,
