@@ -174,8 +174,8 @@ __global__ void k_rank_gather(const double *__restrict__ x, int64_t n, const uin
 // sorts take some 15 launches each for one or two tiles, bound by the launches
 // and by the one or two workgroups of a launch; counting is n^2 comparisons
 // of two instructions over all CUs in one launch.  A whole build takes 45 us
-// (n = 1000), 87 (4096), 124 (8192) and 165 (12000) instead of 134, 178, 194
-// and 195 with the radix sorts; at 16384 it would be 219 against 202.
+// (n = 1000), 87 (4096), 124 (8192) and 165 (12288) instead of 134, 178, 194
+// and 182 with the radix sorts; at 16384 it would be 219 against 189.
 constexpr int COUNT_SORT_MAX = 12288;
 constexpr int CR_THREADS = 1024, CR_WAVES = CR_THREADS / 64;
 
@@ -400,7 +400,9 @@ hipError_t launch_rs_scan(uint32_t *hist, uint32_t *tot, int digits, int nblk, h
 // each digit's run to its global position with consecutive threads on
 // consecutive addresses.  VALS = false: keys only (no values loaded, staged
 // in LDS or written).
-template <typename K, int BITS, bool VALS>
+// FOLD: hist holds the counts of the tiles as they are (few tiles), and every
+// tile sums the rows itself.
+template <typename K, int BITS, bool VALS, bool FOLD>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(
     const K *__restrict__ kin, const uint32_t *__restrict__ vin, K *kout, uint32_t *vout,
     int64_t n, int shift, const uint32_t *__restrict__ hist, const uint32_t *__restrict__ tot,
@@ -435,8 +437,21 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(
     }
     // this tile's offsets within the digit runs and the digit totals, loaded
     // while the keys are in flight
-    const uint32_t gofs_t = t < NB ? hist[((int64_t)b * NB + t) * nblk + blk] : 0u;
-    const uint32_t dtot = t < NB ? tot[b * NB + t] : 0u;
+    uint32_t gofs_t = 0u, dtot = 0u;
+    if (t < NB) {
+        const uint32_t *row = hist + ((int64_t)b * NB + t) * nblk;
+        if constexpr (FOLD) {
+#pragma unroll 8
+            for (int i = 0; i < nblk; ++i) {
+                const uint32_t c = row[i];
+                gofs_t += i < blk ? c : 0u;
+                dtot += c;
+            }
+        } else {
+            gofs_t = row[blk];
+            dtot = tot[b * NB + t];
+        }
+    }
 #pragma unroll
     for (int r = 0; r < RS_ROUNDS; ++r) {
         const bool valid = wbase + r * 64 + lane < nv;
@@ -509,6 +524,38 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(
     }
 }
 
+// Up to this many tiles a pass has no scan launch: its tiles sum the rows of the
+// counts themselves.  The build (eight passes) of 30011 particles (8 tiles) takes
+// 208 instead of 231 us, of 131072 (32) 244 instead of 270, of 262144 (64) 294
+// instead of 310, of 300000 326 instead of 337; of 400000 376 either way, of
+// 524288 (128) it would be 411 against 402.
+constexpr int RS_FOLD_TILES = 64;
+
+// One pass: counts, scan, scatter (vin == nullptr: keys only).
+template <typename K, int BITS>
+static void radix_pass(const K *kin, const uint32_t *vin, K *kout, uint32_t *vout, int64_t n, int B,
+                       int shift, uint32_t *hist, uint32_t *tot, hipStream_t s)
+{
+    constexpr int NB = 1 << BITS;
+    const int nblk = (int)((n + RS_TILE - 1) / RS_TILE);
+    const bool fold = nblk <= RS_FOLD_TILES;
+    const dim3 g(nblk, B);
+    k_rs_hist<K, BITS><<<g, RS_THREADS, 0, s>>>(kin, n, shift, hist, nblk);
+    if (!fold)
+        k_rs_scan<<<dim3(NB, B), RS_SCAN_THREADS, 0, s>>>(hist, tot, nblk);
+    auto run = [&](auto kernel) {
+        kernel<<<g, RS_THREADS, 0, s>>>(kin, vin, kout, vout, n, shift, hist, tot, nblk);
+    };
+    if (vin && fold)
+        run(k_rs_scatter<K, BITS, true, true>);
+    else if (vin)
+        run(k_rs_scatter<K, BITS, true, false>);
+    else if (fold)
+        run(k_rs_scatter<K, BITS, false, true>);
+    else
+        run(k_rs_scatter<K, BITS, false, false>);
+}
+
 // Sort B arrays of n (key, value) pairs by the low BITS * passes key bits
 // (v0 == v1 == nullptr: keys only), BITS = 8 or 10 bits per pass.  The result
 // ends in (k0, v0) after an even number of passes, in (k1, v1) after an odd
@@ -527,15 +574,7 @@ static hipError_t radix_sort(K *k0, uint32_t *v0, K *k1, uint32_t *v1, int64_t n
         K *ki = (pass & 1) ? k1 : k0, *ko = (pass & 1) ? k0 : k1;
         uint32_t *vi = (pass & 1) ? v1 : v0, *vo = (pass & 1) ? v0 : v1;
         uint32_t *tp = tot + (int64_t)pass * B * NB;
-        dim3 g(nblk, B);
-        k_rs_hist<K, BITS><<<g, RS_THREADS, 0, s>>>(ki, n, shift, hist, nblk);
-        k_rs_scan<<<dim3(NB, B), RS_SCAN_THREADS, 0, s>>>(hist, tp, nblk);
-        if (vi)
-            k_rs_scatter<K, BITS, true><<<g, RS_THREADS, 0, s>>>(ki, vi, ko, vo, n, shift, hist,
-                                                                 tp, nblk);
-        else
-            k_rs_scatter<K, BITS, false><<<g, RS_THREADS, 0, s>>>(ki, vi, ko, vo, n, shift, hist,
-                                                                  tp, nblk);
+        radix_pass<K, BITS>(ki, vi, ko, vo, n, B, shift, hist, tp, s);
     }
     return hipGetLastError();
 }
@@ -783,11 +822,7 @@ hipError_t sort_by_halves(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1
         uint64_t *ki = (pass & 1) ? k1 : k0, *ko = (pass & 1) ? k0 : k1;
         uint32_t *vi = (pass & 1) ? v1 : v0, *vo = (pass & 1) ? v0 : v1;
         uint32_t *tp = tot + (int64_t)pass * B * 256;
-        dim3 g(nblk, B);
-        k_rs_hist<uint64_t, 8><<<g, RS_THREADS, 0, s>>>(ki, n, shift, hist, nblk);
-        k_rs_scan<<<dim3(256, B), RS_SCAN_THREADS, 0, s>>>(hist, tp, nblk);
-        k_rs_scatter<uint64_t, 8, true><<<g, RS_THREADS, 0, s>>>(ki, vi, ko, vo, n, shift, hist,
-                                                               tp, nblk);
+        radix_pass<uint64_t, 8>(ki, vi, ko, vo, n, B, shift, hist, tp, s);
     }
     const int gf = (int)std::min<int64_t>((n + 255) / 256, 4096);
     k_run_fix<<<dim3(gf, B), 256, 0, s>>>(k0, v0, vout, n, long_cnt, long_list, long_cap, err);
