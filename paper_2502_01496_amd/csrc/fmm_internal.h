@@ -59,6 +59,13 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
+// at + the number of lanes below this one that are set in m.
+__device__ __forceinline__ int below(uint64_t m, int at)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
+}
+
 // 1/sqrt(x) for finite x > 0: hardware estimate plus one second-order
 // correction, y' = y + y e (1/2 + 3/8 e) with e = 1 - x y^2.
 __device__ __forceinline__ double rsqrt_pos(double x)

@@ -1037,13 +1037,6 @@ __device__ __forceinline__ int lanes_per_pair(int pairs)
     return (int)((0x08090a0c10152040ull >> (8 * (pairs - 1))) & 0xffull);
 }
 
-// at + the number of lanes below this one that are set in m.
-__device__ __forceinline__ int below(uint64_t m, int at)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
-}
-
 // Rotation by N lanes within each row of 16 lanes.
 template <int N>
 __device__ __forceinline__ double row_ror(double v)

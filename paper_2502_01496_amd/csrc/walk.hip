@@ -41,14 +41,16 @@ __device__ __forceinline__ CellRec load_cell(const double *recA, int b)
     return {a.x, a.y, c2, q.x, q.y, kids.x, kids.y};
 }
 
-__device__ __forceinline__ bool opened(double ca0, double ca1, double ca2, double sa, double ha,
-                                       const CellRec &cb, double theta2, double r_kern)
+// kha, khb: R_kern h of the sink leaf and of the cell; their larger one is
+// R_kern max(h_a, h_b) to the bit (R_kern > 0, and rounding keeps the order).
+__device__ __forceinline__ bool opened(double ca0, double ca1, double ca2, double sa, double kha,
+                                       const CellRec &cb, double khb, double theta2)
 {
     const double dx = ca0 - cb.c0, dy = ca1 - cb.c1, dz = ca2 - cb.c2;
-    const double sb = cb.sb, hb = cb.hb;
+    const double sb = cb.sb;
     const double r2 = (dx * dx + dy * dy) + dz * dz;
     const bool open4 = sb * sb > theta2 * r2;
-    const double tt = (sa + sb) + r_kern * (ha > hb ? ha : hb);
+    const double tt = (sa + sb) + fmax(kha, khb);
     const bool open5 = r2 < tt * tt;
     return open4 || open5;
 }
@@ -67,6 +69,12 @@ __device__ __forceinline__ bool opened(double ca0, double ca1, double ca2, doubl
 // k_walk_heavy (its counts read -2 until then): the few groups whose leaves
 // see most of the tree would otherwise hold one wavefront for thousands of
 // dependent steps.
+//
+// Instructions bound it (some 200 per step; reading the records by quads, a
+// quarter of the L1 lookups for 50 instructions more, took 186 us where the
+// lane's own loads take 158): places by mbcnt on top of the count, R_kern h
+// ahead of the leaves.  158 -> 145 us (binary, 2^19 particles), 1.26 -> 1.21 ms
+// (clumpy cube, 2^22), 5.59 -> 5.45 ms (2^24).
 constexpr int WG = 4;
 constexpr int WALK_WAVES = 1;  // one wavefront per workgroup
 
@@ -84,8 +92,7 @@ __global__ __launch_bounds__(64 * WALK_WAVES) void k_walk_group(
     if (g0 >= nleaves)
         return;
     const int ng = min(WG, nleaves - g0);
-    const uint64_t lt = lanemask_lt();
-    double ca0[WG], ca1[WG], ca2[WG], sa[WG], ha[WG];
+    double ca0[WG], ca1[WG], ca2[WG], sa[WG], kha[WG];
 #pragma unroll
     for (int g = 0; g < WG; ++g) {
         const double *ra = recA + (int64_t)NREC * leaf_node[g0 + min(g, ng - 1)];
@@ -93,7 +100,7 @@ __global__ __launch_bounds__(64 * WALK_WAVES) void k_walk_group(
         ca1[g] = ra[1];
         ca2[g] = ra[2];
         sa[g] = ra[4];
-        ha[g] = ra[5];
+        kha[g] = r_kern * ra[5];
     }
     int nf[WG], nn[WG];
 #pragma unroll
@@ -119,24 +126,25 @@ __global__ __launch_bounds__(64 * WALK_WAVES) void k_walk_group(
         // the record is read once for all leaves of the group (idle lanes
         // read the root's)
         const CellRec cb = load_cell(recA, b);
+        const double khb = r_kern * cb.hb;
         const int lb = cb.left, rgt = cb.right;
         uint32_t open = 0;
 #pragma unroll
         for (int g = 0; g < WG; ++g) {
             const bool live = (m >> g) & 1u;
             const bool op =
-                opened(ca0[g], ca1[g], ca2[g], sa[g], ha[g], cb, theta2, r_kern) && live;
+                opened(ca0[g], ca1[g], ca2[g], sa[g], kha[g], cb, khb, theta2) && live;
             const bool far = live && !op;
             const bool nea = op && lb < 0;
             open |= (op ? 1u : 0u) << g;
             const uint64_t mf = __ballot(far), mn = __ballot(nea);
             if (far) {
-                const int k = nf[g] + __popcll(mf & lt);
+                const int k = below(mf, nf[g]);
                 if (k < cap_far)
                     far_src[(int64_t)(g0 + g) * cap_far + k] = b;
             }
             if (nea) {
-                const int k = nn[g] + __popcll(mn & lt);
+                const int k = below(mn, nn[g]);
                 if (k < cap_near)
                     near_src[(int64_t)(g0 + g) * cap_near + k] = b;
             }
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(64 * WALK_WAVES) void k_walk_group(
             break;
         }
         if (desc) {
-            const int k = sp + 2 * __popcll(md & lt);
+            const int k = sp + 2 * below(md, 0);
             stk[w][k] = rgt;
             msk[w][k] = (uint8_t)open;
             stk[w][k + 1] = lb;
@@ -208,12 +216,11 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
     __shared__ int32_t wpre[HEAVY_WAVES][2 * WG + 1];  // the same, summed over earlier wavefronts
     __shared__ int32_t wtot[2 * WG + 1];               // and over all of them
     const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-    const uint64_t lt = lanemask_lt();
     const int nh = *nheavy;
     for (int h = blockIdx.x; h < nh; h += gridDim.x) {
         const int g0 = heavy[h] * WG;
         const int ng = min(WG, nleaves - g0);
-        double ca0[WG], ca1[WG], ca2[WG], sa[WG], ha[WG];
+        double ca0[WG], ca1[WG], ca2[WG], sa[WG], kha[WG];
 #pragma unroll
         for (int g = 0; g < WG; ++g) {
             const double *ra = recA + (int64_t)NREC * leaf_node[g0 + min(g, ng - 1)];
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
             ca1[g] = ra[1];
             ca2[g] = ra[2];
             sa[g] = ra[4];
-            ha[g] = ra[5];
+            kha[g] = r_kern * ra[5];
         }
         int nf[WG], nn[WG];  // the same in every thread
 #pragma unroll
@@ -242,6 +249,7 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
             const uint32_t m = act ? msk[base + t] : 0u;
             sp = base;
             const CellRec cb = load_cell(recA, b);
+            const double khb = r_kern * cb.hb;
             const int lb = cb.left, rgt = cb.right;
             uint32_t open = 0;
             uint64_t mf[WG], mn[WG];
@@ -250,7 +258,7 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
             for (int g = 0; g < WG; ++g) {
                 const bool live = (m >> g) & 1u;
                 const bool op =
-                    opened(ca0[g], ca1[g], ca2[g], sa[g], ha[g], cb, theta2, r_kern) && live;
+                    opened(ca0[g], ca1[g], ca2[g], sa[g], kha[g], cb, khb, theta2) && live;
                 far[g] = live && !op;
                 nea[g] = op && lb < 0;
                 open |= (op ? 1u : 0u) << g;
@@ -283,12 +291,12 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
 #pragma unroll
             for (int g = 0; g < WG; ++g) {
                 if (far[g]) {
-                    const int k = nf[g] + wpre[w][g] + __popcll(mf[g] & lt);
+                    const int k = below(mf[g], nf[g] + wpre[w][g]);
                     if (k < cap_far)
                         far_src[(int64_t)(g0 + g) * cap_far + k] = b;
                 }
                 if (nea[g]) {
-                    const int k = nn[g] + wpre[w][WG + g] + __popcll(mn[g] & lt);
+                    const int k = below(mn[g], nn[g] + wpre[w][WG + g]);
                     if (k < cap_near)
                         near_src[(int64_t)(g0 + g) * cap_near + k] = b;
                 }
@@ -300,7 +308,7 @@ __global__ __launch_bounds__(64 * HEAVY_WAVES) void k_walk_heavy(
                 break;
             }
             if (desc) {
-                const int k = sp + 2 * (bd + __popcll(md & lt));
+                const int k = sp + 2 * below(md, bd);
                 stk[k] = rgt;
                 msk[k] = (uint8_t)open;
                 stk[k + 1] = lb;
@@ -362,7 +370,7 @@ __global__ __launch_bounds__(256) void k_walk_p(
         const bool active = (mask >> lane) & 1ull;
         bool descend = false;
         if (active) {
-            if (!opened(ca0, ca1, ca2, sa, ha, cb, theta2, r_kern)) {
+            if (!opened(ca0, ca1, ca2, sa, r_kern * ha, cb, r_kern * cb.hb, theta2)) {
                 if (nf < cap_far)
                     fo[nf] = b;
                 ++nf;
