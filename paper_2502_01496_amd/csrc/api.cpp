@@ -415,10 +415,6 @@ static fmm_status create_tree(int64_t n, const fmm_params &p, Tree **out)
     A(dalloc(*t, &t->pm, n + 1));  // + the null source record
     A(dalloc(*t, &t->hs, n));
     A(dalloc(*t, &t->ph, n + 1));
-    A(dalloc(*t, &t->pxy, n));
-    A(dalloc(*t, &t->pzm, n));
-    A(dalloc(*t, &t->phi, n));
-    A(dalloc(*t, &t->lbox, LBOX * (size_t)t->topo.leaf_cap));
     A(dalloc(*t, &t->pf, n));
     A(dalloc(*t, &t->pfh, n));
     A(dalloc(*t, &t->recA, NREC * nn));
@@ -436,6 +432,17 @@ static fmm_status create_tree(int64_t n, const fmm_params &p, Tree **out)
     A(dalloc(*t, &t->walk_heavy, (size_t)(n + 3) / 4 + 1));  // groups of four leaves
     A(dalloc(*t, &t->L, NLOC * nn));
     A(dalloc(*t, &t->Lf, NLOC * nn));
+    // the near field of an FP64 tree's leaf <- cell lists reads four arrays of
+    // its own; they take buffers that such a tree has no other use for: those
+    // of the FP32 form and, once the tree is built, the sort's keys
+    static_assert(sizeof(*t->pxy) == sizeof(*t->pf) && sizeof(*t->pzm) == sizeof(*t->pfh) &&
+                      sizeof(*t->phi) <= sizeof(*t->keys0) &&
+                      LBOX * sizeof(*t->lbox) <= NLOC * sizeof(*t->Lf),
+                  "the arrays fit the buffers that they share");
+    t->pxy = (double2 *)t->pf;
+    t->pzm = (double2 *)t->pfh;
+    t->phi = (double *)t->keys0;
+    t->lbox = (double *)t->Lf;
     A(dalloc(*t, &t->red, 16 + 16 * 512));
     if (e == hipSuccess)
         e = hipHostMalloc((void **)&t->h_flags, 16 * sizeof(int32_t), hipHostMallocDefault);
@@ -912,8 +919,13 @@ static fmm_status forces_mutual(Tree &t, void *a, bool walk, bool vjp_only, hipS
     }
     if (t.split_lists && !t.pieces_valid) {
         fmm_status st = build_pieces(t, s, false);
-        if (st != FMM_OK)
+        if (st == FMM_ERR_ALLOC) {
+            // no room for the pieces: whole lists give the same bits
+            (void)hipGetLastError();
+            t.split_lists = false;
+        } else if (st != FMM_OK) {
             return st;
+        }
     }
     if (!vjp_only || t.p.precision == FMM_FP64) {
         StageTimer tm(t, s, 3);

@@ -358,7 +358,7 @@ struct Tree {
     double4 *ph = nullptr;        // 1/h, 1/h^3, 4 h^2, h
     // the same for the FP64 near field of the leaf <- cell lists, which reads a
     // particle per lane: 64 consecutive records of 16 or 8 bytes are one
-    // contiguous access
+    // contiguous access (in the buffers of pf, pfh and keys0)
     double2 *pxy = nullptr, *pzm = nullptr;  // x, y; z, m
     double *phi = nullptr;        // 1/h
     float4 *pf = nullptr;         // FP32 form: offset from the leaf centre of mass, m
@@ -369,7 +369,8 @@ struct Tree {
     double *recQ = nullptr;       // per node: Qxx, Qxy, Qxz, Qyy, Qyz, Qzz, c_z, M
     float *recF = nullptr;        // per node FP32 mirror: M, Q[6], 0
     double *lbox = nullptr;       // LBOX per leaf: bounding box of its particles (centre,
-                                  // half widths), their largest 4 h^2, 0
+                                  // half widths), their largest 4 h^2, 0; written for the
+                                  // same trees as pxy (in the buffer of Lf)
     uint64_t *s2bits = nullptr;
     uint64_t *s2part = nullptr;   // depth x ceil(n/64) per-wavefront maxima
     int32_t *big_nodes = nullptr;

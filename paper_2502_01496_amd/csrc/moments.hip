@@ -160,7 +160,8 @@ __device__ __forceinline__ void leaf_p2m(const double4 *__restrict__ pm,
                 hm = hh[j] > hm ? hh[j] : hm;
             }
     }
-    B.store(box, hm);
+    if (box)
+        B.store(box, hm);
     double c0 = S0 / M, c1 = S1 / M, c2 = S2 / M;
     double Q[6] = {0, 0, 0, 0, 0, 0};
     for (int k0 = 0; k0 < c; k0 += U) {
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(256) void k_leaf_moments(
     if (lf >= nleaves)
         return;
     double a[5], q[6];
-    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ, lbox + (int64_t)LBOX * lf, want_fp32,
+    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ, lbox ? lbox + (int64_t)LBOX * lf : nullptr, want_fp32,
              pf, a, q);
 }
 
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256) void k_sub_moments(
     const int lf0 = sm_leaf[2 * s], lf1 = sm_leaf[2 * s + 1];
     for (int lf = lf0 + t; lf < lf1; lf += 256) {
         const int v = leaf_node[lf];
-        leaf_p2m(pm, hs, v, first, count, recA, recQ, lbox + (int64_t)LBOX * lf, want_fp32, pf,
+        leaf_p2m(pm, hs, v, first, count, recA, recQ, lbox ? lbox + (int64_t)LBOX * lf : nullptr, want_fp32, pf,
                  sA[v - r], sQ[v - r]);
     }
     const int32_t *g = sm_lvl + s * (SM_MAXL + 1);
@@ -660,15 +661,18 @@ __global__ void k_import_boxes(const double4 *__restrict__ pm, const double *__r
     B.store(lbox + (int64_t)LBOX * lf, hm);
 }
 
+// The arrays that only the FP64 near field of the leaf <- cell lists reads are
+// written for a tree that takes it (else nullptr: their buffers hold the FP32
+// form then).
+static bool wants_lane_arrays(const Tree &t)
+{
+    return t.p.precision == FMM_FP64 && t.p.walk == FMM_WALK_PHANTOM;
+}
+static double2 *lane_arrays(const Tree &t) { return wants_lane_arrays(t) ? t.pxy : nullptr; }
+static double *leaf_boxes(const Tree &t) { return wants_lane_arrays(t) ? t.lbox : nullptr; }
+
 // fmm_debug_import: tree-order particles from the imported permutation (with
 // the data checks of a moments call), then the imported cell records.
-// The arrays that only the near field of the leaf <- cell lists reads are
-// written for a tree that takes it (else nullptr).
-static double2 *lane_arrays(const Tree &t)
-{
-    return t.p.precision == FMM_FP64 && t.p.walk == FMM_WALK_PHANTOM ? t.pxy : nullptr;
-}
-
 hipError_t launch_import(Tree &t, const double *x, const double *m, const double *h,
                          const double *rec12, hipStream_t s)
 {
@@ -683,8 +687,9 @@ hipError_t launch_import(Tree &t, const double *x, const double *m, const double
     k_import_records<<<(T.nnodes + 255) / 256, 256, 0, s>>>(T.nnodes, rec12, t.left, t.right,
                                                            t.node_leaf, t.recA, t.recQ, want32,
                                                            t.recF);
-    k_import_boxes<<<(T.nleaves + 255) / 256, 256, 0, s>>>(t.pm, t.hs, t.leaf_node, T.nleaves,
-                                                          t.first, t.count, t.lbox);
+    if (leaf_boxes(t))
+        k_import_boxes<<<(T.nleaves + 255) / 256, 256, 0, s>>>(
+            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, leaf_boxes(t));
     if (want32)
         k_import_offsets<<<(T.nleaves + 255) / 256, 256, 0, s>>>(T.nleaves, t.leaf_node, t.first,
                                                                  t.count, t.recA, t.pm, t.pf);
@@ -706,7 +711,7 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
         // the subtrees in one launch, then the cells above them level by level
         k_sub_moments<<<(int)T.sub_root.size(), 256, 0, s>>>(
             t.pm, t.hs, t.leaf_node, t.first, t.count, t.sub_root, t.sm_leaf, t.sm_lvl,
-            (const int2 *)t.sm_nodes, t.recA, t.recQ, t.lbox, want32, t.pf);
+            (const int2 *)t.sm_nodes, t.recA, t.recQ, leaf_boxes(t), want32, t.pf);
         if (T.top_fused) {
             if (!T.top_nodes.empty())
                 k_top_moments<<<1, 1024, 0, s>>>(t.top_slot_node, (int)T.sub_root.size(),
@@ -722,7 +727,7 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
         }
     } else {
         k_leaf_moments<<<(T.nleaves + 255) / 256, 256, 0, s>>>(
-            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, t.lbox, want32, t.pf);
+            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, leaf_boxes(t), want32, t.pf);
         for (int l = T.depth - 2; l >= 0; --l) {
             int o = T.lvl_int_off[l], cnt = T.lvl_int_off[l + 1] - o;
             if (cnt > 0)

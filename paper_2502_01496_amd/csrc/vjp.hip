@@ -1677,11 +1677,18 @@ static void vfree(Tree &t, std::initializer_list<void **> ptrs)
     }
 }
 
+static void vfree_piece_order(Tree &t)
+{
+    vfree(t, {(void **)&t.pkey, (void **)&t.pkey1, (void **)&t.pid, (void **)&t.porder,
+              (void **)&t.phist});
+    t.porder_cap = 0;
+}
+
 static void vfree_pieces(Tree &t)
 {
-    vfree(t, {(void **)&t.pnode, (void **)&t.ppart, (void **)&t.pkey, (void **)&t.pkey1,
-              (void **)&t.pid, (void **)&t.porder, (void **)&t.phist});
-    t.piece_cap = t.porder_cap = 0;
+    vfree_piece_order(t);
+    vfree(t, {(void **)&t.pnode, (void **)&t.ppart});
+    t.piece_cap = 0;
 }
 
 static void vfree_transpose(Tree &t)
@@ -1913,6 +1920,26 @@ static hipError_t count_m2lt_pieces_async(Tree &t, hipStream_t s)
     return hipMemcpyAsync(t.h_pairs + 2, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
 }
 
+// The buffers of the pieces' order by sinks.  The order changes no result, so
+// without the memory for it the pieces run as they stand.
+static void ensure_piece_order(Tree &t, int64_t cp)
+{
+    const int64_t nblk = (cp + RS_TILE - 1) / RS_TILE;
+    vfree_piece_order(t);
+    hipError_t e = hipSuccess;
+    for (uint32_t **b : {&t.pkey, &t.pkey1, &t.pid, &t.porder})
+        if (e == hipSuccess)
+            e = tree_malloc(t, (void **)b, cp * sizeof(uint32_t));
+    if (e == hipSuccess)
+        e = tree_malloc(t, (void **)&t.phist, RS_MAX_DIGITS * (nblk + 1) * sizeof(uint32_t));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        vfree_piece_order(t);
+        return;
+    }
+    t.porder_cap = cp;
+}
+
 // The table of those pieces, once their number is known.
 static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
 {
@@ -1926,27 +1953,24 @@ static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
         e = hipStreamSynchronize(s);
         if (e != hipSuccess)
             return e;
-        vfree_pieces(t);
-        const int64_t cp = np + np / 4 + 256;
-        const int64_t nblk = (cp + RS_TILE - 1) / RS_TILE;
-        e = tree_malloc(t, (void **)&t.pnode, cp * sizeof(int32_t));
-        if (e == hipSuccess)
-            e = tree_malloc(t, (void **)&t.ppart, 10 * cp * sizeof(double));
-        for (uint32_t **b : {&t.pkey, &t.pkey1, &t.pid, &t.porder})
-            if (e == hipSuccess && sorted)
-                e = tree_malloc(t, (void **)b, cp * sizeof(uint32_t));
-        if (e == hipSuccess && sorted)
-            e = tree_malloc(t, (void **)&t.phist, RS_MAX_DIGITS * (nblk + 1) * sizeof(uint32_t));
-        if (e != hipSuccess) {
+        const int64_t cp = std::max(t.piece_cap, np + np / 4 + 256);
+        if (np > t.piece_cap) {
             vfree_pieces(t);
-            return e;
+            e = tree_malloc(t, (void **)&t.pnode, cp * sizeof(int32_t));
+            if (e == hipSuccess)
+                e = tree_malloc(t, (void **)&t.ppart, 10 * cp * sizeof(double));
+            if (e != hipSuccess) {
+                vfree_pieces(t);
+                return e;
+            }
+            t.piece_cap = cp;
         }
-        t.piece_cap = cp;
-        t.porder_cap = sorted ? cp : 0;
+        if (sorted)
+            ensure_piece_order(t, cp);
     }
     t.npieces = np;
     k_piece_fill<<<g, 256, 0, s>>>(t.poff, nn, t.pnode);
-    if (sorted) {
+    if (sorted && t.porder) {
         // one pass of the radix sort: at most 1024 ranges of sinks
         int kshift = 0;
         while ((T.nleaves - 1) >> kshift >= RS_MAX_DIGITS)
@@ -2118,10 +2142,10 @@ hipError_t ensure_transposed(Tree &t, hipStream_t s)
         e = count_p2pt_pieces_async(t, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (e == hipSuccess && far)
-        e = fill_m2lt_pieces(t, s);
     if (e == hipSuccess)
         e = fill_p2pt_pieces(t, s);
+    if (e == hipSuccess && far)  // last: the order of its pieces may be left out
+        e = fill_m2lt_pieces(t, s);
     if (e == hipSuccess)
         t.has_transposed = true;
     return e;
