@@ -208,8 +208,8 @@ __global__ __launch_bounds__(256) void k_leaf_moments(
     if (lf >= nleaves)
         return;
     double a[5], q[6];
-    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ, lbox ? lbox + (int64_t)LBOX * lf : nullptr, want_fp32,
-             pf, a, q);
+    leaf_p2m(pm, hs, leaf_node[lf], first, count, recA, recQ,
+             lbox ? lbox + (int64_t)LBOX * lf : nullptr, want_fp32, pf, a, q);
 }
 
 // M2M for the internal nodes of one level (children were done by the
@@ -299,8 +299,8 @@ __global__ __launch_bounds__(256) void k_sub_moments(
     const int lf0 = sm_leaf[2 * s], lf1 = sm_leaf[2 * s + 1];
     for (int lf = lf0 + t; lf < lf1; lf += 256) {
         const int v = leaf_node[lf];
-        leaf_p2m(pm, hs, v, first, count, recA, recQ, lbox ? lbox + (int64_t)LBOX * lf : nullptr, want_fp32, pf,
-                 sA[v - r], sQ[v - r]);
+        leaf_p2m(pm, hs, v, first, count, recA, recQ, lbox ? lbox + (int64_t)LBOX * lf : nullptr,
+                 want_fp32, pf, sA[v - r], sQ[v - r]);
     }
     const int32_t *g = sm_lvl + s * (SM_MAXL + 1);
     for (int k = 0; k < SM_MAXL; ++k) {
@@ -426,97 +426,186 @@ __global__ __launch_bounds__(256) void k_node_s2(const double4 *__restrict__ pm,
 // sizes are floor(c / 2^k) or one more (c mod 2^k of them); every cell above
 // the first depth K at which ceil(c / 2^K) <= L splits, and at depth K - 1
 // those holding more than L particles split once more.
-__device__ __forceinline__ int med_leaves(int c, int L)
+static int med_leaves(int c, int L)
 {
     if (c <= L)
         return 1;
-    const int a = 31 - __clz(c), b = 31 - __clz(L);
+    const int a = 31 - __builtin_clz(c), b = 31 - __builtin_clz(L);
     const int k = ((uint64_t)L << (a - b)) >= (uint64_t)c ? a - b : a - b + 1;  // K >= 1
     const int km = k - 1;
     const int q = c >> km, r = c & ((1 << km) - 1);
     return (1 << km) + (q + 1 > L ? r : 0) + (q > L ? (1 << km) - r : 0);
 }
 
-// k_node_s2 for the count-median tree: its pre-order ids follow from the
-// split rule (the right child of v is v + 2 leaves(left child)), so a
-// particle's path needs no memory reads, and the centres of S2_BATCH levels
-// are loaded together.  Same reductions and outputs as k_node_s2.
+__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return b > a ? b : a; }
+
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, false);
+    return (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo;
+}
+
+// Two maxima at once, over the lanes that differ in bit BIT (32 or 16) of the
+// lane: lanes with the bit clear keep a's, those with the bit set keep b's.
+template <int BIT>
+__device__ __forceinline__ uint64_t max_halves(uint64_t a, uint64_t b)
+{
+    const bool up = lane_id() & BIT;
+    const uint64_t send = up ? a : b, keep = up ? b : a;
+    return max_u64(keep, __shfl_xor(send, BIT));
+}
+
+// Maxima over the wavefront of eight values per lane.  The eight lanes of
+// lane >> 3 = 4 i + 2 j + k all return that of value 4 i + 2 j + k.
+__device__ __forceinline__ uint64_t wave_max8(const uint64_t *v)
+{
+    uint64_t w[4], x[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        w[j] = max_halves<32>(v[j], v[j + 4]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        x[j] = max_halves<16>(w[j], w[j + 2]);
+    const bool up = lane_id() & 8;
+    uint64_t m = max_u64(up ? x[1] : x[0], dpp_u64<0x128>(up ? x[0] : x[1]));  // row_ror:8
+    m = max_u64(m, dpp_u64<0xb1>(m));   // quad_perm: lane ^ 1
+    m = max_u64(m, dpp_u64<0x4e>(m));   // lane ^ 2
+    return max_u64(m, dpp_u64<0x141>(m));  // row_half_mirror: the other quad
+}
+
+// Leaves of the cells of each level of a count-median tree, which hold
+// n >> level particles or one more.
+struct MedLevels {
+    int2 leaves[32];
+};
+
+static MedLevels med_levels(int64_t n, int L)
+{
+    MedLevels M = {};
+    for (int k = 1; k < 32; ++k)  // (the root is nobody's child)
+        M.leaves[k] = make_int2(med_leaves((int)(n >> k), L), med_leaves((int)(n >> k) + 1, L));
+    return M;
+}
+
+// One step down the count-median tree from cell v = [f, f + c) of level lvl
+// towards position p: the right child of v is v + 2 leaves(left child).
+__device__ __forceinline__ void med_step(int64_t p, int n, const MedLevels &M, int lvl, int &v,
+                                         int &f, int &c)
+{
+    const int nl = (c + 1) >> 1;
+    const int2 lv = M.leaves[lvl + 1];
+    const int leaves = nl > (n >> (lvl + 1)) ? lv.y : lv.x;
+    const bool left = p < (int64_t)f + nl;
+    v += left ? 1 : 2 * leaves;
+    f += left ? 0 : nl;
+    c = left ? nl : c - nl;
+}
+
+// k_node_s2 for the count-median tree: its pre-order ids follow from the split
+// rule, so a particle's path needs no memory reads.  Same outputs as k_node_s2.
+//
+// The cells that hold the whole wavefront (all but the last few levels) are
+// found once per wavefront, in scalar registers, and their maxima are formed
+// eight levels at a time, with the lanes shared out among the levels as they
+// are folded: 20 cross-lane words for eight levels, where a butterfly per level
+// takes 96, which bounded the kernel: 31.6 -> 20.5 us at 2^19 particles, 207 ->
+// 118 at 2^22, 915 -> 500 at 2^24.  Below them, the segmented maxima of S2_BATCH
+// levels, over no more lanes than the level's cells have.  Half of what is left
+// is VALU issue.  (Plain stores for cells within a wavefront, in place of the
+// atomics: no faster, 125 -> 128 us.)
 constexpr int S2_BATCH = 4;
 
 __global__ __launch_bounds__(256) void k_node_s2_med(const double4 *__restrict__ pm, int64_t n,
                                                      const double *__restrict__ recA, int leaf_size,
-                                                     uint64_t *s2bits, uint64_t *part,
-                                                     int64_t nwaves)
+                                                     const MedLevels M, uint64_t *s2bits,
+                                                     uint64_t *part, int64_t nwaves)
 {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t wave = p >> 6;
+    const int64_t wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = lane_id();
+    const int64_t p0 = wave * 64, p = p0 + lane;
     bool alive = p < n;
     const double4 xp = alive ? pm[p] : make_double4(0, 0, 0, 0);
     int v = 0, f = 0, c = (int)n;
-    for (int lvl = 0; __ballot(alive) != 0ull; lvl += S2_BATCH) {
-        int vb[S2_BATCH];
-        bool ab[S2_BATCH];
+    int lvl = 0;
+    // cells that hold positions p0 .. p0 + 63, from the root on
+    bool whole = p0 + 64 <= n;
+    while (whole) {
+        int vb[8], nb = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            vb[j] = v;  // (past the last one: read again, not stored)
+            if (!whole)
+                continue;
+            ++nb;
+            if (c <= leaf_size) {
+                whole = alive = false;
+                continue;
+            }
+            int v1 = v, f1 = f, c1 = c;
+            med_step(p0, (int)n, M, min(lvl + j, 30), v1, f1, c1);
+            whole = p0 + 64 <= (int64_t)f1 + c1;
+            if (whole) {
+                v = v1;
+                f = f1;
+                c = c1;
+            }
+        }
+        uint64_t d2[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const double *ra = recA + (int64_t)NREC * vb[j];
+            const double dx = xp.x - ra[0], dy = xp.y - ra[1], dz = xp.z - ra[2];
+            d2[j] = (uint64_t)__double_as_longlong((dx * dx + dy * dy) + dz * dz);
+        }
+        const uint64_t m = wave_max8(d2);
+        const int q = lane >> 3;
+        if ((lane & 7) == 0 && q < nb)
+            part[(int64_t)(lvl + q) * nwaves + wave] = m;
+        lvl += nb;
+    }
+    if (alive && lvl > 0)
+        med_step(p, (int)n, M, lvl - 1, v, f, c);
+    for (; __ballot(alive) != 0ull; lvl += S2_BATCH) {
+        int vb[S2_BATCH], fb[S2_BATCH], cb[S2_BATCH];  // cell, its particles (0: no cell)
 #pragma unroll
         for (int j = 0; j < S2_BATCH; ++j) {
-            ab[j] = alive;
             vb[j] = v;
+            fb[j] = f;
+            cb[j] = alive ? c : 0;
             if (alive) {
-                if (c > leaf_size) {
-                    const int nl = (c + 1) >> 1;
-                    if (p < f + nl) {
-                        v += 1;
-                        c = nl;
-                    } else {
-                        v += 2 * med_leaves(nl, leaf_size);
-                        f += nl;
-                        c -= nl;
-                    }
-                } else {
+                if (c > leaf_size)
+                    med_step(p, (int)n, M, min(lvl + j, 30), v, f, c);
+                else
                     alive = false;
-                }
             }
         }
         double cx[S2_BATCH], cy[S2_BATCH], cz[S2_BATCH];
 #pragma unroll
         for (int j = 0; j < S2_BATCH; ++j) {
-            const double *ra = recA + (int64_t)NREC * (ab[j] ? vb[j] : 0);
+            const double *ra = recA + (int64_t)NREC * (cb[j] ? vb[j] : 0);
             cx[j] = ra[0];
             cy[j] = ra[1];
             cz[j] = ra[2];
         }
 #pragma unroll
         for (int j = 0; j < S2_BATCH; ++j) {
-            const int key = ab[j] ? vb[j] : -1;
-            uint64_t val = 0ull;
-            if (ab[j]) {
-                const double dx = xp.x - cx[j], dy = xp.y - cy[j], dz = xp.z - cz[j];
-                const double d2 = (dx * dx + dy * dy) + dz * dz;
-                val = (uint64_t)__double_as_longlong(d2);
+            if (__ballot(cb[j] != 0) == 0ull)
+                break;
+            const double dx = xp.x - cx[j], dy = xp.y - cy[j], dz = xp.z - cz[j];
+            const double d2 = (dx * dx + dy * dy) + dz * dz;
+            uint64_t val = cb[j] ? (uint64_t)__double_as_longlong(d2) : 0ull;
+            // segmented inclusive max over the lanes of a cell, which are
+            // contiguous and no more than its particles
+            const int back = (int)min(p - fb[j], (int64_t)lane);
+            for (int off = 1; off < 64 && __ballot(cb[j] > off) != 0ull; off <<= 1) {
+                const uint64_t ov = __shfl_up(val, off);
+                if (off <= back)
+                    val = max_u64(val, ov);
             }
-            const int k0 = __shfl(key, 0);
-            const bool uniform = __ballot(key == k0 && key >= 0) == ~0ull;
-            if (uniform) {
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) {
-                    const uint64_t ov = __shfl_xor(val, off);
-                    val = ov > val ? ov : val;
-                }
-                if (lane == 63)
-                    part[(int64_t)(lvl + j) * nwaves + wave] = val;
-            } else if (__ballot(key >= 0) != 0ull) {
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const uint64_t ov = __shfl_up(val, off);
-                    const int ok = __shfl_up(key, off);
-                    if (lane >= off && ok == key)
-                        val = ov > val ? ov : val;
-                }
-                const int nk = __shfl_down(key, 1);
-                const bool tail = (lane == 63) || (nk != key);
-                if (key >= 0 && tail)
-                    atomicMax((unsigned long long *)&s2bits[key], (unsigned long long)val);
-            }
+            if (cb[j] && (lane == 63 || p + 1 == (int64_t)fb[j] + cb[j]))
+                atomicMax((unsigned long long *)&s2bits[vb[j]], (unsigned long long)val);
         }
     }
 }
@@ -727,7 +816,8 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
         }
     } else {
         k_leaf_moments<<<(T.nleaves + 255) / 256, 256, 0, s>>>(
-            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, leaf_boxes(t), want32, t.pf);
+            t.pm, t.hs, t.leaf_node, T.nleaves, t.first, t.count, t.recA, t.recQ, leaf_boxes(t),
+            want32, t.pf);
         for (int l = T.depth - 2; l >= 0; --l) {
             int o = T.lvl_int_off[l], cnt = T.lvl_int_off[l + 1] - o;
             if (cnt > 0)
@@ -742,7 +832,8 @@ hipError_t launch_moments(Tree &t, const double *x, const double *m, const doubl
                                                          t.s2part, nwaves);
     else
         k_node_s2_med<<<(int)((n + 255) / 256), 256, 0, s>>>(t.pm, n, t.recA, T.leaf_size,
-                                                             t.s2bits, t.s2part, nwaves);
+                                                             med_levels(n, T.leaf_size), t.s2bits,
+                                                             t.s2part, nwaves);
     const int nbig = T.nbig;
     if (nbig > 0)
         k_node_s2_fold<<<(nbig + 3) / 4, 256, 0, s>>>(t.big_nodes, nbig, t.first, t.count,
