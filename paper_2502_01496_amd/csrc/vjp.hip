@@ -941,8 +941,11 @@ __global__ __launch_bounds__(256) void k_vjp_l2l_level(const int32_t *__restrict
 // takes v), so the cells that took v as source are v's own partners and one
 // pass over the CSR range of v does both sides: cbar_v += rbar of (v <- b)
 // with Lbar_v, and Mbar_v, Qbar_v, cbar_v -= rbar of (b <- v) with Lbar_b.
-// 16 lanes per cell, all cells.
-template <int FORM, bool F32>
+// 16 lanes per cell, all cells.  The plain sums for FP64 trees too: regrouped,
+// with both sides' cotangents expanded, the whole reverse pass takes 2844
+// against 2819 us (binary, 2^19 particles) and 6.00 against 5.87 ms (clumpy
+// cube, 2^20).
+template <int FORM>
 __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
     const double *__restrict__ recA, const double *__restrict__ recQ, int nnodes,
     const int64_t *__restrict__ fstart, const int64_t *__restrict__ fend,
@@ -960,8 +963,6 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
 #pragma unroll
     for (int k = 0; k < 19; ++k)
         Lb[k] = Lbar[(int64_t)NLOC * vv + k];
-    if constexpr (vjp_regrouped<FORM, F32>)
-        lbar_full(Lb);
     double rs[3] = {0.0, 0.0, 0.0}, rt[3] = {0.0, 0.0, 0.0}, Mb = 0.0,
            Qb[6] = {0, 0, 0, 0, 0, 0};
     const int64_t e0 = valid ? fstart[v] : 0, e1 = valid ? fend[v] : 0;
@@ -970,15 +971,9 @@ __global__ __launch_bounds__(256) void k_vjp_m2l_mutual(
         const double *rb = recA + (int64_t)NREC * b;
         const double r[3] = {rv[0] - rb[0], rv[1] - rb[1], rv[2] - rb[2]};
         double Mx = 0.0, Qx[6] = {0, 0, 0, 0, 0, 0};
-        m2l_vjp<FORM, F32>(r, rb[3], recQ + (int64_t)NREC * b, Lb, rs, Mx, Qx);
+        m2l_vjp<FORM, true>(r, rb[3], recQ + (int64_t)NREC * b, Lb, rs, Mx, Qx);
         const double q[3] = {-r[0], -r[1], -r[2]};
-        double Lx[19];
-#pragma unroll
-        for (int k = 0; k < 19; ++k)
-            Lx[k] = Lbar[(int64_t)NLOC * b + k];
-        if constexpr (vjp_regrouped<FORM, F32>)
-            lbar_full(Lx);
-        m2l_vjp<FORM, F32>(q, Mv, Qv, Lx, rt, Mb, Qb);
+        m2l_vjp<FORM, true>(q, Mv, Qv, Lbar + (int64_t)NLOC * b, rt, Mb, Qb);
     }
     double acc[13] = {rs[0], rs[1], rs[2], rt[0], rt[1], rt[2], Mb,
                       Qb[0], Qb[1], Qb[2], Qb[3], Qb[4], Qb[5]};
@@ -2088,13 +2083,10 @@ static hipError_t vjp_mutual_far(Tree &t, hipStream_t s)
         kernel<<<g, 256, 0, s>>>(t.recA, t.recQ, T.nnodes, M.fstart, M.fend, M.far_sorted, mask,
                                  t.Lbar, t.nadj);
     };
-    const bool fp32 = t.p.precision == FMM_FP32;
     if (t.p.expansion == FMM_EXPANSION_DEHNEN)
-        run(k_vjp_m2l_mutual<FMM_EXPANSION_DEHNEN, false>);
-    else if (fp32)
-        run(k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM, true>);
+        run(k_vjp_m2l_mutual<FMM_EXPANSION_DEHNEN>);
     else
-        run(k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM, false>);
+        run(k_vjp_m2l_mutual<FMM_EXPANSION_PHANTOM>);
     return hipGetLastError();
 }
 
