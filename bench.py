@@ -409,7 +409,9 @@ def run_one(args, x_np, m_np, h_np, prec, census=True, walk=0, steps=None, sinks
                "leaf_size": args.leaf_size}
     if dom:
         achieved = kern[dom][0] / 1e12
-        ktag = {"p2p": "k_p2p_src", "m2l": "k_m2l_node" if walk else "k_m2l_leaf"}[dom] + \
+        # (the FP64 near field of the leaf <- cell lists has a kernel of its own)
+        p2p = "k_p2p_src" if prec or walk else "k_p2p_rings"
+        ktag = {"p2p": p2p, "m2l": "k_m2l_node" if walk else "k_m2l_leaf"}[dom] + \
             "_" + ("f32" if prec else "f64")
         roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": peak / 1e12,
                 "unit": "TFLOP/s", "frac": round(achieved * 1e12 / peak, 4),
