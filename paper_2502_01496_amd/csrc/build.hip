@@ -968,6 +968,12 @@ __global__ __launch_bounds__(LVL_THREADS) void k_lvl_count(
 // particles or more, whose coordinate arrays miss in L2; smaller ones gather
 // the coordinates and save the extra launch per level.
 constexpr int64_t LVL_BYRANK_MIN = int64_t(1) << 20;
+// Above LVL_BITS_ABOVE particles the lookups read a bit per particle, packed by
+// k_side_bits: the bytes then come near an XCD's L2 (4 MiB) and the lookups miss
+// it, the bits fit up to 2^25 particles.  Over the levels of a build, lookups and
+// packing: 1402 -> 1044 + 65 us (2^24 particles), 280 -> 190 + 55 us (2^22); at
+// 2^21 the 5 us of packing a level are as much as they save.
+constexpr int64_t LVL_BITS_ABOVE = int64_t(1) << 21;
 __global__ __launch_bounds__(LVL_THREADS) void k_lvl_side(
     const uint32_t *__restrict__ L, int64_t n, const double *__restrict__ xr,
     const int32_t *blk_node, const int32_t *blk_start, const int32_t *blk_end,
@@ -994,8 +1000,25 @@ __global__ __launch_bounds__(LVL_THREADS) void k_lvl_side(
     }
 }
 
+// The sides by rank, a bit each instead of a byte.
+__global__ __launch_bounds__(256) void k_side_bits(const uint4 *__restrict__ byrank, int64_t nw,
+                                                   uint32_t *bits)
+{
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= nw)
+        return;
+    const uint4 a = byrank[2 * i], b = byrank[2 * i + 1];
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)  // byte j of a word to bit j
+        m |= (((w[k] & 0x01010101u) * 0x01020408u) >> 24 & 0xfu) << (4 * k);
+    bits[i] = m;
+}
+
 // Sides of a chunk of one list from the sides by rank (stored per position
 // for the scatter) and the chunk's left count.
+template <bool BITS>
 __global__ __launch_bounds__(LVL_THREADS) void k_lvl_count_byrank(
     const uint32_t *__restrict__ L, int64_t n, const int32_t *blk_node,
     const int32_t *blk_start, const int32_t *blk_end, const int32_t *first,
@@ -1022,7 +1045,8 @@ __global__ __launch_bounds__(LVL_THREADS) void k_lvl_count_byrank(
             r[k] = Ld[min(s0 + t + k * LVL_THREADS, e0 - 1)];
 #pragma unroll
         for (int k = 0; k < PER; ++k)
-            g[k] = byrank[r[k]];
+            g[k] = BITS ? ((const uint32_t *)byrank)[r[k] >> 5] >> (r[k] & 31) & 1u
+                        : byrank[r[k]];
     }
     uint8_t *sd = side + d * n;
     uint32_t c = 0;
@@ -1374,13 +1398,20 @@ hipError_t launch_build(Tree &t, const double *x, hipStream_t s)
         const uint32_t *Ls = (l & 1) ? L1 : L0;
         uint32_t *Ld = (l & 1) ? L0 : L1;
         if (n >= LVL_BYRANK_MIN) {
-            uint8_t *byrank = t.side + 3 * n;
+            uint8_t *byrank = (uint8_t *)t.keys0;  // (the sorts are done)
             k_lvl_side<<<nb, LVL_THREADS, 0, s>>>(Ls, n, t.xr, t.blk_node + b0,
                                                   t.blk_start + b0, t.blk_end + b0, t.first,
                                                   t.count, t.axis, byrank);
-            k_lvl_count_byrank<<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
-                Ls, n, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0, t.first, t.count,
-                t.axis, byrank, t.side, t.lvl_cnt, T.max_lvl_blocks);
+            const bool bits = n > LVL_BITS_ABOVE;
+            const int64_t nw = (n + 31) / 32;
+            if (bits)
+                k_side_bits<<<(int)((nw + 255) / 256), 256, 0, s>>>((const uint4 *)byrank, nw,
+                                                                    (uint32_t *)t.keys1);
+            (bits ? k_lvl_count_byrank<true> : k_lvl_count_byrank<false>)
+                <<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
+                    Ls, n, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0, t.first, t.count,
+                    t.axis, bits ? (const uint8_t *)t.keys1 : byrank, t.side, t.lvl_cnt,
+                    T.max_lvl_blocks);
         } else {
             k_lvl_count<<<dim3(nb, 3), LVL_THREADS, 0, s>>>(
                 Ls, n, t.xr, t.blk_node + b0, t.blk_start + b0, t.blk_end + b0, t.first,
