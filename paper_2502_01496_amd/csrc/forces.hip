@@ -1005,7 +1005,8 @@ __device__ __forceinline__ double m_over_r3_k(double r2, double m, double k15)
 // Each is tested against the bounding box of the leaf: one whose distance from
 // the box is beyond the softening supports of eqs. (14)-(15) of itself and of
 // every sink is Newtonian for all of them and goes to one ring buffer, the
-// others go to a second one.  A step over the first ring is m / r^3 without a
+// others go to a second one.  (The box holds its particles however it rounds,
+// so a pair at r = 0 never reaches the first ring, whose steps divide by r.)  A step over the first ring is m / r^3 without a
 // test; a step over the second one takes the M4 kernel, which is exact on both
 // sides of the support, if any of its pairs is inside one.  A ring is emptied
 // g sources at a time, the rest stays for the next 64, so missing particles

@@ -108,12 +108,18 @@ struct LeafBox {
         hi1 = fmax(hi1, q.y);
         hi2 = fmax(hi2, q.z);
     }
+    // The half widths are those about the rounded centre, 4 units in the last
+    // place wider: the particles of the leaf then lie inside (their distance
+    // from the box is 0, whatever their supports), and the distance of any
+    // other point from the box, as the near field forms it, is no larger than
+    // that from the nearest of them but for its own relative rounding.
     __device__ __forceinline__ void store(double *o, double hmax) const
     {
-        ((double4 *)o)[0] = make_double4(0.5 * (lo0 + hi0), 0.5 * (lo1 + hi1), 0.5 * (lo2 + hi2),
-                                         0.5 * (hi0 - lo0));
-        ((double4 *)o)[1] = make_double4(0.5 * (hi1 - lo1), 0.5 * (hi2 - lo2), 4.0 * hmax * hmax,
-                                         0.0);
+        const double b0 = 0.5 * (lo0 + hi0), b1 = 0.5 * (lo1 + hi1), b2 = 0.5 * (lo2 + hi2);
+        constexpr double W = 1.0 + 4.0 * 2.220446049250313e-16;
+        ((double4 *)o)[0] = make_double4(b0, b1, b2, W * fmax(hi0 - b0, b0 - lo0));
+        ((double4 *)o)[1] = make_double4(W * fmax(hi1 - b1, b1 - lo1), W * fmax(hi2 - b2, b2 - lo2),
+                                         4.0 * hmax * hmax, 0.0);
     }
 };
 
