@@ -139,9 +139,10 @@ __device__ __forceinline__ double2 as_double2(const int4 &x)
 // 70.3 -> 60.7, 49152 78 against 92.  The whole reverse pass: 4096 particles
 // (512 leaves) 334 -> 273, 8192 397 -> 353, 16384 (2048 leaves) 502 -> 473 but
 // 364 against 372 for the clumpy cube, star 32768 476 against 506.  Teams of
-// eight: 4096 particles 23.4 and 288.
+// eight: 4096 particles 23.4 and 288.  The rule looks at the tree's leaves, not at
+// the units of a launch: a list gives the same sums whole and in pieces.
 constexpr int NEAR_TEAM = 4;
-constexpr int NEAR_TEAM_UNITS = 4096, NEAR_TEAM_UNITS_VJP = 1024;
+constexpr int NEAR_TEAM_LEAVES = 4096, NEAR_TEAM_LEAVES_VJP = 1024;
 
 // First block of wavefront w's share of the blocks [p0, nb): multiples of 8.
 template <int TEAM>

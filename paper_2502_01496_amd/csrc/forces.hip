@@ -1595,7 +1595,7 @@ hipError_t launch_near(Tree &t, void *a, hipStream_t s)
     if (t.p.precision == FMM_FP64) {
         // (lists_policy is set after the evaluation of a tree's new lists)
         if (t.p.walk == FMM_WALK_PHANTOM) {
-            const int team = nu <= NEAR_TEAM_UNITS ? NEAR_TEAM : 1;
+            const int team = nl <= NEAR_TEAM_LEAVES ? NEAR_TEAM : 1;
             (team > 1 ? k_p2p_rings<NEAR_TEAM> : k_p2p_rings<1>)<<<nu, 64 * team, 0, s>>>(
                 t.pxy, t.pzm, t.phi, t.lbox, t.first, t.count, t.leaf_node, nu, t.near_cnt,
                 t.near_src, (int)t.cap_near, nsub, t.L, t.recA, t.perm, t.p.G, (double *)a, pl,

@@ -2194,7 +2194,7 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         const bool pc = use_pieces(t);
         const int nu = pc ? (int)t.pnear.n : nl;
         const int stride = 3 * T.leaf_size;
-        const int team = !fp32 && nu <= NEAR_TEAM_UNITS_VJP ? NEAR_TEAM : 1;
+        const int team = !fp32 && nl <= NEAR_TEAM_LEAVES_VJP ? NEAR_TEAM : 1;
         (team > 1 ? k_vjp_p2p_sink<NEAR_TEAM> : k_vjp_p2p_sink<1>)<<<nu, 64 * team, 0, s>>>(
             t.pm, t.ph, t.abt, t.first, t.count, t.leaf_node, nu, t.near_cnt, t.near_src,
             (int)t.cap_near, nsub, n, t.xbt, pc ? t.pnear.list : nullptr, per,
@@ -2209,7 +2209,7 @@ hipError_t launch_vjp(Tree &t, const void *abar, void *xbar, void *mbar, hipStre
         const bool pc = t.pnearT.n > nl;
         const int nu = pc ? (int)t.pnearT.n : nl;
         const int stride = 4 * T.leaf_size;
-        const int team = !fp32 && nu <= NEAR_TEAM_UNITS_VJP ? NEAR_TEAM : 1;
+        const int team = !fp32 && nl <= NEAR_TEAM_LEAVES_VJP ? NEAR_TEAM : 1;
         (team > 1 ? k_vjp_p2p_src<NEAR_TEAM> : k_vjp_p2p_src<1>)<<<nu, 64 * team, 0, s>>>(
             t.pm, t.ph, t.abt, t.first, t.count, t.leaf_node, nu, t.nearT.off, t.nearT.src, nsub,
             n, t.xbt, t.mbt, pc ? t.pnearT.list : nullptr, (int)t.vjp_src_piece_blocks,
