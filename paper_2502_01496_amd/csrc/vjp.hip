@@ -1965,7 +1965,7 @@ static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
     }
     t.npieces = np;
     k_piece_fill<<<g, 256, 0, s>>>(t.poff, nn, t.pnode);
-    if (sorted && t.porder) {
+    if (np > 0 && sorted && t.porder) {
         // one pass of the radix sort: at most 1024 ranges of sinks
         int kshift = 0;
         while ((T.nleaves - 1) >> kshift >= RS_MAX_DIGITS)
