@@ -203,7 +203,7 @@ void build_topology(int64_t n, int leaf_size, Topology &T)
     T.leaf_cap = T.nleaves;
 }
 
-hipError_t tree_malloc(Tree &t, void **p, size_t bytes)
+hipError_t tree_malloc_optional(Tree &t, void **p, size_t bytes)
 {
     *p = nullptr;
     bytes = std::max<size_t>(bytes, 256);
@@ -224,6 +224,36 @@ hipError_t tree_malloc(Tree &t, void **p, size_t bytes)
     t.held_bytes += (int64_t)bytes;
     *p = q;
     return hipSuccess;
+}
+
+// Release the workspace that only saves time: the order of the reverse pass's
+// pieces and the pieces of a mutual walk's near lists (the same bits without
+// either).  False if there is none.
+static bool give_way(Tree &t)
+{
+    const bool pieces = t.p.walk == FMM_WALK_MUTUAL && t.pnear.np;
+    if ((!pieces && !t.porder) || hipDeviceSynchronize() != hipSuccess)
+        return false;
+    release_piece_order(t);
+    if (pieces) {
+        for (Tree::Pieces *P : {&t.pnear, &t.pfar}) {
+            for (void *q : {(void *)P->np, (void *)P->off, (void *)P->tsum, (void *)P->list, P->part})
+                tree_free(t, q);
+            *P = Tree::Pieces();
+        }
+        t.pieces_valid = false;
+    }
+    return true;
+}
+
+hipError_t tree_malloc(Tree &t, void **p, size_t bytes)
+{
+    hipError_t e = tree_malloc_optional(t, p, bytes);
+    if (e == hipErrorOutOfMemory && give_way(t)) {
+        (void)hipGetLastError();
+        e = tree_malloc_optional(t, p, bytes);
+    }
+    return e;
 }
 
 void tree_free(Tree &t, void *p)
@@ -728,21 +758,28 @@ static fmm_status bad_input(uint32_t errbits)
                 (errbits & 4) ? " smoothing lengths not positive and finite" : "");
 }
 
+// A mutual walk's near lists can be evaluated whole, so their pieces are optional.
+static auto piece_malloc(const Tree &t)
+{
+    return t.p.walk == FMM_WALK_MUTUAL ? tree_malloc_optional : tree_malloc;
+}
+
 // Workspace of the list pieces that does not depend on the lists: pieces per
 // leaf, their offsets and the scan workspace (all or nothing).
 static fmm_status ensure_piece_base(Tree &t)
 {
+    const auto take = piece_malloc(t);
     if (t.pnear.np)
         return FMM_OK;
     const int64_t nl = t.topo.leaf_cap;
     hipError_t e = hipSuccess;
     for (Tree::Pieces *P : {&t.pnear, &t.pfar}) {
         if (e == hipSuccess)
-            e = tree_malloc(t, (void **)&P->np, nl * sizeof(int32_t));
+            e = take(t, (void **)&P->np, nl * sizeof(int32_t));
         if (e == hipSuccess)
-            e = tree_malloc(t, (void **)&P->off, (nl + 1) * sizeof(int64_t));
+            e = take(t, (void **)&P->off, (nl + 1) * sizeof(int64_t));
         if (e == hipSuccess)
-            e = tree_malloc(t, (void **)&P->tsum, count_scan_workspace((int)nl) * sizeof(int64_t));
+            e = take(t, (void **)&P->tsum, count_scan_workspace((int)nl) * sizeof(int64_t));
     }
     if (e == hipSuccess && !t.h_piece)
         e = hipHostMalloc((void **)&t.h_piece, 2 * sizeof(int64_t), hipHostMallocDefault);
@@ -800,9 +837,10 @@ static fmm_status build_pieces(Tree &t, hipStream_t s, bool have_totals)
             P.part = nullptr;
             P.cap = 0;
             const int64_t cap = np + np / 4 + 64;
-            hipError_t e = tree_malloc(t, (void **)&P.list, cap * sizeof(int2));
+            const auto take = piece_malloc(t);
+            hipError_t e = take(t, (void **)&P.list, cap * sizeof(int2));
             if (e == hipSuccess)
-                e = tree_malloc(t, &P.part, cap * strides[k]);
+                e = take(t, &P.part, cap * strides[k]);
             if (e != hipSuccess) {
                 tree_free(t, P.list);
                 P.list = nullptr;

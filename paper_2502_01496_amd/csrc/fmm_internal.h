@@ -289,8 +289,11 @@ struct Tree;
 // memory goes through these two: they apply the caller's allocator hooks and
 // byte limit (fmm_params) and keep the count fmm_tree_device_bytes reports.
 // tree_malloc returns hipErrorOutOfMemory when the limit would be exceeded
-// or a hook returns NULL; tree_free(nullptr) is a no-op.
+// or a hook returns NULL; tree_free(nullptr) is a no-op.  Workspace that a call
+// can do without is taken with tree_malloc_optional, and tree_malloc releases it
+// (waiting for the device) where the memory would not suffice otherwise.
 hipError_t tree_malloc(Tree &t, void **p, size_t bytes);
+hipError_t tree_malloc_optional(Tree &t, void **p, size_t bytes);
 void tree_free(Tree &t, void *p);
 
 // Mutual walk state: pair frontier, far / near pair buffers (sorted by
@@ -437,6 +440,8 @@ struct Tree {
     uint32_t *pkey = nullptr, *pkey1 = nullptr, *pid = nullptr, *porder = nullptr,
              *phist = nullptr;
     int64_t porder_cap = 0;
+    int64_t porder_refused = INT64_MAX;  // pieces whose order found no memory or gave way
+    bool piece_ordered = false;          // porder is of the current pieces
 
     MutualLists mw;
     int64_t mw_init_cap = 0;        // test hook: FMM_MI355_MW_CAP sets small first capacities
@@ -593,6 +598,7 @@ hipError_t ensure_transposed(Tree &t, hipStream_t s);
 hipError_t ensure_far_transposed(Tree &t, hipStream_t s);  // leaf <- cell lists only
 int64_t com_max_active(int64_t n);  // active cells of a level of the centre-of-mass build
 void release_vjp(Tree &t);
+void release_piece_order(Tree &t);
 hipError_t launch_asym(Tree &t, double m_leaf, double *out, hipStream_t s);
 void release_asym(Tree &t);
 hipError_t launch_kick_drift(double *x, double *v, const void *a, int a_fp32, int64_t n,

@@ -1677,6 +1677,14 @@ static void vfree_piece_order(Tree &t)
     vfree(t, {(void **)&t.pkey, (void **)&t.pkey1, (void **)&t.pid, (void **)&t.porder,
               (void **)&t.phist});
     t.porder_cap = 0;
+    t.piece_ordered = false;
+}
+
+void release_piece_order(Tree &t)
+{
+    if (t.porder)
+        t.porder_refused = t.npieces > 0 ? t.npieces : t.porder_cap;
+    vfree_piece_order(t);
 }
 
 static void vfree_pieces(Tree &t)
@@ -1915,21 +1923,24 @@ static hipError_t count_m2lt_pieces_async(Tree &t, hipStream_t s)
     return hipMemcpyAsync(t.h_pairs + 2, total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
 }
 
-// The buffers of the pieces' order by sinks.  The order changes no result, so
-// without the memory for it the pieces run as they stand.
-static void ensure_piece_order(Tree &t, int64_t cp)
+// The buffers of the order by sinks of np pieces, for cp.  The order changes no
+// result, so without the memory for it the pieces run as they stand (and as many
+// or more of them are not tried again).
+static void ensure_piece_order(Tree &t, int64_t np, int64_t cp)
 {
     const int64_t nblk = (cp + RS_TILE - 1) / RS_TILE;
     vfree_piece_order(t);
     hipError_t e = hipSuccess;
     for (uint32_t **b : {&t.pkey, &t.pkey1, &t.pid, &t.porder})
         if (e == hipSuccess)
-            e = tree_malloc(t, (void **)b, cp * sizeof(uint32_t));
+            e = tree_malloc_optional(t, (void **)b, cp * sizeof(uint32_t));
     if (e == hipSuccess)
-        e = tree_malloc(t, (void **)&t.phist, RS_MAX_DIGITS * (nblk + 1) * sizeof(uint32_t));
+        e = tree_malloc_optional(t, (void **)&t.phist,
+                                 RS_MAX_DIGITS * (nblk + 1) * sizeof(uint32_t));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         vfree_piece_order(t);
+        t.porder_refused = np;
         return;
     }
     t.porder_cap = cp;
@@ -1943,8 +1954,8 @@ static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
     const int g = (nn + 255) / 256;
     hipError_t e = hipSuccess;
     const int64_t np = t.h_pairs[2];
-    const bool sorted = m2lt_sorted(t);
-    if (np > t.piece_cap || (sorted && np > t.porder_cap)) {
+    const bool order = m2lt_sorted(t) && (np <= t.porder_cap || np < t.porder_refused);
+    if (np > t.piece_cap || (order && np > t.porder_cap)) {
         e = hipStreamSynchronize(s);
         if (e != hipSuccess)
             return e;
@@ -1960,12 +1971,13 @@ static hipError_t fill_m2lt_pieces(Tree &t, hipStream_t s)
             }
             t.piece_cap = cp;
         }
-        if (sorted)
-            ensure_piece_order(t, cp);
+        if (order && np > t.porder_cap)
+            ensure_piece_order(t, np, cp);
     }
     t.npieces = np;
+    t.piece_ordered = np > 0 && order && t.porder;
     k_piece_fill<<<g, 256, 0, s>>>(t.poff, nn, t.pnode);
-    if (np > 0 && sorted && t.porder) {
+    if (t.piece_ordered) {
         // one pass of the radix sort: at most 1024 ranges of sinks
         int kshift = 0;
         while ((T.nleaves - 1) >> kshift >= RS_MAX_DIGITS)
@@ -2058,7 +2070,7 @@ static void vjp_m2l(Tree &t, hipStream_t s)
         k_vjp_m2l_src_piece<FORM, F32>
             <<<(int)((t.npieces * vjpm_lanes(F32) + 63) / 64), 64, 0, s>>>(
             t.recA, t.recQ, t.farT.off, t.farT.src, t.Lleaf, t.topo.leaf_cap, t.pnode, t.poff,
-            m2lt_sorted(t) ? t.porder : nullptr, t.npieces, t.ppart);
+            t.piece_ordered ? t.porder : nullptr, t.npieces, t.ppart);
 }
 
 // Mutual walk: forward totals of the internal cells, L2L^T level by level
