@@ -895,16 +895,6 @@ __device__ __forceinline__ Split node_split(const uint32_t *L, int64_t n, const 
     return S;
 }
 
-// Side of the entry at position p of list d (rank r): 1 = left child.
-__device__ __forceinline__ uint32_t goes_left(const Split &S, const double *xr, int64_t n, int d,
-                                              int64_t p, uint32_t r)
-{
-    if (d == S.ax)
-        return p - S.f < S.nl ? 1u : 0u;
-    const uint64_t o = ordbits(xr[S.ax * n + r]);
-    return (o < S.ob || (o == S.ob && r <= S.rm)) ? 1u : 0u;
-}
-
 // Sides of a chunk of one list (also stored per position for the scatter)
 // and the chunk's left count.  A chunk holds at most LVL_CHUNK entries, PER
 // per thread: the entries are loaded before the split is found and the
