@@ -140,7 +140,10 @@ __device__ __forceinline__ double2 as_double2(const int4 &x)
 // (512 leaves) 334 -> 273, 8192 397 -> 353, 16384 (2048 leaves) 502 -> 473 but
 // 364 against 372 for the clumpy cube, star 32768 476 against 506.  Teams of
 // eight: 4096 particles 23.4 and 288.  The rule looks at the tree's leaves, not at
-// the units of a launch: a list gives the same sums whole and in pieces.
+// the units of a launch, so that a list gives the same sums whole and in pieces;
+// in pieces, kept forces and reverse pass of such trees with a wavefront per
+// piece -> a team: clumpy cube 32768 193 -> 134, Plummer 32768 222 -> 203, 20000 (4096
+// leaves) 158 -> 146, the reverse pass of Plummer 8192 (1024 leaves) 207 -> 164.
 constexpr int NEAR_TEAM = 4;
 constexpr int NEAR_TEAM_LEAVES = 4096, NEAR_TEAM_LEAVES_VJP = 1024;
 
@@ -372,7 +375,7 @@ struct Tree {
     double *recA = nullptr;       // per node: cx, cy, cz, M, s, hmax, 0, 0
     double *recQ = nullptr;       // per node: Qxx, Qxy, Qxz, Qyy, Qyz, Qzz, c_z, M
     float *recF = nullptr;        // per node FP32 mirror: M, Q[6], 0
-    double *lbox = nullptr;       // LBOX per leaf: bounding box of its particles (centre,
+    double *lbox = nullptr;       // LBOX per leaf: box that holds its particles (centre,
                                   // half widths), their largest 4 h^2, 0; written for the
                                   // same trees as pxy (in the buffer of Lf)
     uint64_t *s2bits = nullptr;

@@ -34,9 +34,12 @@
 // Every accumulator has exactly one owning thread (no floating-point
 // atomics), so the result is bitwise reproducible.  The arithmetic is FP64.
 // The results of FP32 trees are these sums rounded to FP32, where any other
-// order of additions shows as a unit in the last place here and there; they
+// order of additions shows as a unit in the last place here and there.  They
 // are kept to the bit, so the far field's kernels have the plain sums for FP32
-// trees (F32 = true) beside the regrouped ones, and both share the layout.
+// trees (F32 = true) beside the regrouped ones, and both share the layout.  That
+// is a choice: nothing but those last places asks for it, and the clumpy cube of
+// 2^22 particles pays 2.34 against 1.68 ms (sink side) and 4.43 against 3.34
+// (source side) for it.
 #include "fmm_internal.h"
 
 namespace fmm {
