@@ -2,7 +2,7 @@
 limit that holds a time series' lists, but not with that workspace beside them,
 a later call whose lists are longer still succeeds, with the bits of a tree
 without a limit.  The order of the reverse pass's pieces (leaf <- cell lists)
-and the pieces of a mutual walk's near lists."""
+and the pieces of a mutual walk's near lists (also to its reverse pass)."""
 import numpy as np
 import pytest
 import torch
@@ -57,7 +57,6 @@ def test_mutual_pieces_give_way(monkeypatch):
     n = 4096
     x, m, h = W.plummer(n, 67)
     X, Mt, H0, H1 = to_dev(x, m, h, np.full(n, 2.0 * np.abs(x).max()))
-    AB = torch.from_numpy(W.cotangent(n, 68)).cuda()
 
     def series(limit, piece=None):
         if piece:
@@ -82,4 +81,28 @@ def test_mutual_pieces_give_way(monkeypatch):
     assert whole1 + 1024 > split0 > whole0 + 1024  # the first call's pieces fit the limit
     _, less, got = series(whole1 + 1024)
     assert less <= whole1 + 1024
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_mutual_pieces_give_way_to_the_reverse_pass():
+    n = 4096
+    x, m, h = W.plummer(n, 67)
+    X, Mt, H = to_dev(x, m, h)
+    AB = torch.from_numpy(W.cotangent(n, 68)).cuda()
+
+    def run(limit):
+        t = F.fmm_build_tree(X, F.default_params(leaf_size=10, walk=F.FMM_WALK_MUTUAL,
+                                                 device_bytes_limit=limit))
+        try:
+            a = _forces(t, X, Mt, H)
+            XB, MB = torch.empty_like(X), torch.empty_like(Mt)
+            F.fmm_forces_vjp(t, AB, XB, MB)
+            return F.fmm_tree_device_bytes(t), [a, XB, MB]
+        finally:
+            F.fmm_tree_free(t)
+
+    held, ref = run(0)
+    less, got = run(held - 1)
+    say(f"[gpu limit] mutual reverse pass: {held} B without a limit, {less} B under {held - 1} B")
+    assert less < held
     assert all(torch.equal(a, b) for a, b in zip(got, ref))
